@@ -535,7 +535,7 @@ void plan_upward(lens_plan *P, hipStream_t st) {
         c.out32[c.nlev] = static_cast<float *>(P->mp32[l - c.nlev].ptr);
         ++c.nlev;
       }
-      launch_m2m_chain(c, st);
+      launch_m2m_chain(c, T, st);
       l -= c.nlev;
     }
   }
@@ -653,7 +653,10 @@ void downward_enqueue(const lens_plan &P, const LocalSet &ls, hipStream_t st) {
     L2LChain c{};
     c.level = l - 1;
     c.p = P.p;
-    c.nlev = std::min(kMaxL2LChain, std::min(first_fused, L + 1) - l);
+    // the first chain takes the odd levels, so that the finest one (with the
+    // most top boxes, a workgroup each) goes down three
+    const int left = std::min(first_fused, L + 1) - l;
+    c.nlev = left % kMaxL2LChain ? left % kMaxL2LChain : kMaxL2LChain;
     for (int j = 0; j <= c.nlev; ++j) {
       c.win[j] = ls.win[l - 1 + j];
       c.loc[j] = ls.at(l - 1 + j);

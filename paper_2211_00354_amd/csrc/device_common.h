@@ -83,4 +83,19 @@ __device__ __forceinline__ cplxf cmadf(cplxf a, cplxf b, cplxf acc) {
     }                                        \
   } while (0)
 
+// Operators on MFMA are compiled per K-step count (OpTables::ks).
+#define LENS_KS_DISPATCH(ks, KERNEL_LAUNCH)                                        \
+  do {                                                                             \
+    switch (ks) {                                                                  \
+      case 2: { constexpr int KS = 2; KERNEL_LAUNCH; break; }                      \
+      case 4: { constexpr int KS = 4; KERNEL_LAUNCH; break; }                      \
+      case 6: { constexpr int KS = 6; KERNEL_LAUNCH; break; }                      \
+      case 8: { constexpr int KS = 8; KERNEL_LAUNCH; break; }                      \
+      case 10: { constexpr int KS = 10; KERNEL_LAUNCH; break; }                    \
+      case 12: { constexpr int KS = 12; KERNEL_LAUNCH; break; }                    \
+      case 16: { constexpr int KS = 16; KERNEL_LAUNCH; break; }                    \
+      default: { constexpr int KS = 20; KERNEL_LAUNCH; break; }                    \
+    }                                                                              \
+  } while (0)
+
 }  // namespace lensfmm

@@ -70,76 +70,103 @@ __global__ __launch_bounds__(kThreads) void k_l2l(DownArgs a, const double *__re
   a.loc[2 * idx + 1] = acc.im;
 }
 
-// L2L down up to three levels in one launch: a 64-thread workgroup owns one
-// box of the chain's top level (its locals final) and its descendants: at
-// depth j, thread t < 4^j takes descendant (t mod 2^j, t div 2^j) of the
-// 2^j x 2^j block, adds the shifted locals of its parent (the previous
-// depth's result, kept in LDS) to its own M2L locals and stores them.  A box
-// outside its level's window is skipped; its children lie outside theirs.
-//
-// The shift needs no table: with the child centre at d = (a - 1/2) +
-// i(c - 1/2) parent half-sides from the parent's (child (2x + a, 2y + c)),
-// the child gets c_j += sum_{l>=j} C(l,j) d^(l-j) 2^-l b_l, the coefficients
-// of B(w + d) for B(w) = sum_l 2^-l b_l w^l, formed by Horner-style synthetic
-// division (p(p-1)/2 updates b_j += d b_(j+1), exact products).
-template <int PMAX>
-__global__ __launch_bounds__(64) void k_l2l_tile(L2LChain c) {
-  __shared__ double2 bufA[16 * PMAX];  // depth-2 results
-  __shared__ double2 bufB[4 * PMAX];   // depth-1 results
-  const int lane = threadIdx.x;
-  const int p = c.p;
+// L2L down up to three levels in one launch, as FP64 MFMAs: a workgroup owns
+// one box of the chain's top level (its locals final) and its 4 + 16 + 64
+// descendants.  At depth j the 4^(j-1) parents (the previous depth's result,
+// kept in LDS) are the rows of one 16-row M-tile, and each of the four waves
+// forms the children of one quadrant, C[parents][2p] = A[parents][2p] L_q,
+// adds their M2L locals and stores them.  A box outside its level's window is
+// skipped; its children lie outside theirs, and the rows of a product do not
+// mix.  The kernel is bound by latency: the operators and the M2L locals of
+// every depth are loaded before the first product, so one memory round trip is
+// paid per launch (16 top boxes, p = 20: 9.5 us, against 34 with a thread per
+// box that shifts it by synthetic division).
+template <int KS>
+__global__ __launch_bounds__(kThreads) void k_l2l_chain(L2LChain c, const double *__restrict__ frag) {
+  constexpr int NT = (KS + 3) / 4, REC = 4 * KS + 1;
+  constexpr bool KEEP = KS <= 12;  // operators in registers for every depth
+  __shared__ double buf1[4 * REC], buf2[16 * REC];
+  const int quad = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int qx = quad & 1, qy = quad >> 1;
+  const int twop = 2 * c.p;
   const int64_t rb = blockIdx.x;
   const int64_t RX = c.win[0].bx0 + rb % c.win[0].nbx, RY = c.win[0].by0 + rb / c.win[0].nbx;
-  for (int j = 1; j <= c.nlev; ++j) {
-    const int side = 1 << j;
-    if (lane < side * side) {
-      const int dx = lane % side, dy = lane / side;
-      const int64_t X = RX * side + dx, Y = RY * side + dy;
-      const Window &w = c.win[j];
-      if (X >= w.bx0 && X < w.bx0 + w.nbx && Y >= w.by0 && Y < w.by0 + w.nby) {
-        double2 *dst = reinterpret_cast<double2 *>(c.loc[j]) + ((Y - w.by0) * w.nbx + (X - w.bx0)) * p;
-        const double dr = (double)(X & 1) - 0.5, di = (double)(Y & 1) - 0.5;
-        cplx b[PMAX];
-        // parent from global memory (depth 1) or LDS, through separate loads
-        // so that no pointer mixes the two address spaces
-        auto load = [&](auto parent_coef) {
+
+  // the child (in this wave's quadrant) of parent `row` at depth j, or nullptr
+  auto child = [&](int j, int row) -> double * {
+    const int sp = 1 << (j - 1);
+    if (row >= sp * sp) return nullptr;
+    const Window &w = c.win[j];
+    const int64_t X = (RX << j) + 2 * (row & (sp - 1)) + qx - w.bx0;
+    const int64_t Y = (RY << j) + 2 * (row >> (j - 1)) + qy - w.by0;
+    if (X < 0 || Y < 0 || X >= w.nbx || Y >= w.nby) return nullptr;
+    return c.loc[j] + (Y * w.nbx + X) * twop;
+  };
+  const double *bsrc = frag + (size_t)quad * KS * NT * 64 + lane;
+  double bk[KEEP ? KS * NT : 1];
+  if (KEEP) {
 #pragma unroll
-          for (int l = 0; l < PMAX; ++l)
-            if (l < p) {
-              const double2 v = parent_coef(l);
-              b[l] = cplx{ldexp(v.x, -l), ldexp(v.y, -l)};
-            }
-        };
-        if (j == 1) {
-          const double2 *root = reinterpret_cast<const double2 *>(c.loc[0]) + rb * p;
-          load([&](int l) { return root[l]; });
-        } else {
-          const double2 *lp = (j == 2 ? bufB : bufA) + ((dy >> 1) * (side >> 1) + (dx >> 1)) * PMAX;
-          load([&](int l) { return lp[l]; });
-        }
+    for (int q = 0; q < KS * NT; ++q) bk[q] = bsrc[q * 64];
+  }
+  double old[6][NT];  // depth 1 and 2: register 0; depth 3: registers 0..3
+  auto fetch = [&](int j, int r, double (&o)[NT]) {
+    const double *d = j <= c.nlev ? child(j, kq + 4 * r) : nullptr;
 #pragma unroll
-        for (int k = 0; k + 1 < PMAX; ++k)
-          if (k + 1 < p) {
+    for (int nt = 0; nt < NT; ++nt) {
+      const int n = nt * 16 + i;
+      o[nt] = d && n < twop ? d[n] : 0.0;
+    }
+  };
+  fetch(1, 0, old[0]);
+  fetch(2, 0, old[1]);
 #pragma unroll
-            for (int i = PMAX - 2; i >= k; --i)
-              if (i + 1 < p) {
-                b[i].re = fma(dr, b[i + 1].re, fma(-di, b[i + 1].im, b[i].re));
-                b[i].im = fma(dr, b[i + 1].im, fma(di, b[i + 1].re, b[i].im));
-              }
-          }
-        double2 *keep = j == 1 ? bufB : bufA;
+  for (int r = 0; r < 4; ++r) fetch(3, r, old[2 + r]);
+
+  const double *root = c.loc[0] + rb * twop;
+  auto depth = [&](auto J, const double *par, double *keep) {
+    constexpr int j = decltype(J)::value, rows = j == 3 ? 16 : (j == 2 ? 4 : 1);
+    d4v acc[NT];
 #pragma unroll
-        for (int i = 0; i < PMAX; ++i)
-          if (i < p) {
-            const double2 v = dst[i];
-            const double2 r = make_double2(v.x + b[i].re, v.y + b[i].im);
-            dst[i] = r;
-            if (j < c.nlev) keep[lane * PMAX + i] = r;
-          }
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = d4v{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int k = 4 * ks + kq;
+      double av = 0.0;
+      if (i < rows && k < twop) {
+        if constexpr (j == 1) av = root[k]; else av = par[i * REC + k];
+      }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const double bv = KEEP ? bk[ks * NT + nt] : bsrc[(ks * NT + nt) * 64];
+        acc[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[nt], 0, 0, 0);
       }
     }
-    __syncthreads();
-  }
+#pragma unroll
+    for (int r = 0; r < (j == 3 ? 4 : 1); ++r) {
+      const int row = kq + 4 * r;
+      double *d = child(j, row);
+      if (!d) continue;
+      // row (py, px) of the parents: child (2 py + qy, 2 px + qx) of the next depth
+      constexpr int sp = 1 << (j - 1);
+      const int idx = (2 * (row >> (j - 1)) + qy) * (2 * sp) + 2 * (row & (sp - 1)) + qx;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int n = nt * 16 + i;
+        if (n >= twop) continue;
+        const double v = old[j == 3 ? 2 + r : j - 1][nt] + acc[nt][r];
+        d[n] = v;
+        if (j < 3) keep[idx * REC + n] = v;
+      }
+    }
+  };
+  depth(std::integral_constant<int, 1>{}, nullptr, buf1);
+  if (c.nlev < 2) return;  // uniform
+  __syncthreads();
+  depth(std::integral_constant<int, 2>{}, buf1, buf2);
+  if (c.nlev < 3) return;
+  __syncthreads();
+  depth(std::integral_constant<int, 3>{}, buf2, nullptr);
 }
 
 // --------------------------------------------------------- M2L on MFMA
@@ -678,9 +705,8 @@ void launch_l2l_chain(const L2LChain &c, const OpTables &t, hipStream_t stream) 
   if (c.nlev < 1 || c.nlev > kMaxL2LChain) fail(LENS_EINVAL, "L2L chain: bad level count");
   const int64_t n = c.win[0].count();
   if (n == 0) return;
-  LENS_PMAX_DISPATCH(c.p, hipLaunchKernelGGL((k_l2l_tile<PM>), dim3((unsigned)n), dim3(64), 0,
-                                             stream, c));
-  (void)t;
+  LENS_KS_DISPATCH(t.ks, hipLaunchKernelGGL((k_l2l_chain<KS>), dim3((unsigned)n), dim3(kThreads), 0,
+                                            stream, c, t.l2l_frag));
   LENS_HIP(hipGetLastError());
 }
 

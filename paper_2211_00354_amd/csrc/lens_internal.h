@@ -125,7 +125,6 @@ int64_t box_starts_coarse_len(int64_t nbox);
 // Expansion operator tables (host-built, uploaded once per order).
 struct OpTables {
   int p = 0;
-  double *m2m = nullptr;   // [4][p][p] complex, M[q][l][k]
   double *l2l = nullptr;   // [4][p][p] complex, L[q][j][l]
   double *m2l = nullptr;   // [49][p][p] complex, stored T[tau][k][l]
   float *m2l32 = nullptr;  // same in FP32
@@ -134,6 +133,7 @@ struct OpTables {
   double *bfrag64 = nullptr;
   float *bfrag32 = nullptr;
   double *l2l_frag = nullptr;  // L2L as FP64 MFMA B fragments: [4][ks][nt][64]
+  double *m2m_frag = nullptr;  // M2M likewise, inputs in pairs (see build_shift_bfrag)
 };
 const OpTables &op_tables(int p, hipStream_t stream);
 // The tables of order p on the current device if already built, else
@@ -145,7 +145,8 @@ void build_m2m_table(int p, std::vector<double> &out);
 void build_l2l_table(int p, std::vector<double> &out);
 void build_m2l_table(int p, std::vector<double> &out);
 void build_m2l_bfrag(int p, std::vector<double> &out, int &ks_count, int &nt_count);
-void build_l2l_bfrag(int p, int ks_count, int nt_count, std::vector<double> &out);
+void build_shift_bfrag(const std::vector<double> &table, int p, int ks_count, int nt_count,
+                       bool paired, std::vector<double> &out);
 
 // Upward pass (upward.hip)
 // (mp32 outputs are optional FP32 copies of the same coefficients)
@@ -186,7 +187,7 @@ struct M2MChain {
   float *out32[kMaxM2MChain];
 };
 int m2m_chain_levels(int level);  // most levels one launch can take from `level` down
-void launch_m2m_chain(const M2MChain &c, hipStream_t stream);
+void launch_m2m_chain(const M2MChain &c, const OpTables &t, hipStream_t stream);
 
 // Downward pass (downward.hip): local expansions of `win` at `level` from the
 // parent's locals (level >= 3) and the multipoles of the interaction list.

@@ -147,20 +147,23 @@ void build_m2l_bfrag(int p, std::vector<double> &out, int &ks_count, int &nt_cou
         }
 }
 
-// L2L operators as MFMA B fragments, one per child quadrant q, same layout
-// and padding as the M2L fragments: b'[2j+o] += sum_{2l+i} B[2l+i][2j+o] b[2l+i]
-// with the complex L[q][j][l] (zero for l < j) in real form.
-void build_l2l_bfrag(int p, int ks_count, int nt_count, std::vector<double> &out) {
-  std::vector<double> Lt;
-  build_l2l_table(p, Lt);
+// L2L (or M2M) operators as MFMA B fragments, one per child quadrant q, same
+// layout and padding as the M2L fragments: b'[2j+o] += sum_{2l+i}
+// B[2l+i][2j+o] b[2l+i] with the complex operator in real form, from its
+// table Lt (input index l major, as build_l2l_table and build_m2m_table give).
+// paired: K-steps 2h and 2h + 1 hold the even and odd inputs 8h + 2 (lane/16)
+// and 8h + 2 (lane/16) + 1 instead of 4 inputs in order each.
+void build_shift_bfrag(const std::vector<double> &Lt, int p, int ks_count, int nt_count, bool paired,
+                       std::vector<double> &out) {
   out.assign((size_t)4 * ks_count * nt_count * 64, 0.0);
   for (int q = 0; q < 4; ++q)
     for (int ks = 0; ks < ks_count; ++ks)
       for (int nt = 0; nt < nt_count; ++nt)
         for (int lane = 0; lane < 64; ++lane) {
-          const int k = 4 * ks + lane / 16, n = 16 * nt + lane % 16;
+          const int k = paired ? 8 * (ks / 2) + 2 * (lane / 16) + ks % 2 : 4 * ks + lane / 16;
+          const int n = 16 * nt + lane % 16;
           const int l = k / 2, pin = k % 2, j = n / 2, pout = n % 2;
-          if (l >= p || j >= p || l < j) continue;
+          if (l >= p || j >= p) continue;
           const size_t o = (((size_t)q * p + l) * p + j) * 2;
           const double tr = Lt[o], ti = Lt[o + 1];
           const double v = pin == 0 ? (pout == 0 ? tr : ti) : (pout == 0 ? -ti : tr);
@@ -200,10 +203,10 @@ const OpTables &op_tables(int p, hipStream_t stream) {
   OpTables t;
   t.p = p;
   std::vector<double> h;
-  build_m2m_table(p, h);
-  t.m2m = upload(h);
-  build_l2l_table(p, h);
-  t.l2l = upload(h);
+  std::vector<double> m2m, l2l;
+  build_m2m_table(p, m2m);
+  build_l2l_table(p, l2l);
+  t.l2l = upload(l2l);
   build_m2l_table(p, h);
   t.m2l = upload(h);
   std::vector<float> hf(h.begin(), h.end());
@@ -213,8 +216,10 @@ const OpTables &op_tables(int p, hipStream_t stream) {
   t.bfrag64 = upload(bf);
   std::vector<float> bf32(bf.begin(), bf.end());
   t.bfrag32 = upload(bf32);
-  build_l2l_bfrag(p, t.ks, t.nt, bf);
+  build_shift_bfrag(l2l, p, t.ks, t.nt, false, bf);
   t.l2l_frag = upload(bf);
+  build_shift_bfrag(m2m, p, t.ks, t.nt, true, bf);
+  t.m2m_frag = upload(bf);
   return g_tabs.emplace(key, t).first->second;  // device tables live until exit
 }
 

@@ -10,6 +10,9 @@
 //
 // Coefficients are box-size rescaled: a~_k = sum_{i in box} m_i w_i^k,
 // w_i = (z_i - c)/s, stored box-major as [box][p] complex (re, im).
+#include <algorithm>
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace lensfmm {
@@ -19,73 +22,32 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWave = 64;
 
-// P2M at `level` (<= L) straight from the stars, for the boxes of `win`:
-// one thread per (box, coefficient k), so consecutive threads write
-// consecutive coefficients; output [win][p], row-major in the window.  A box
-// at `level` covers 2^(L-level) rows of leaf boxes, each a contiguous range
-// of the sorted stars.  w^k by binary powering.
-template <int QDIM>
-__global__ __launch_bounds__(kThreads) void k_p2m(Geometry g, int level, Window win,
-                                                  const double *__restrict__ sxy,
-                                                  const double *__restrict__ sq,
-                                                  const int32_t *__restrict__ leaf_start, int p,
-                                                  double *__restrict__ mp, float *__restrict__ mp32) {
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (idx >= win.count() * p) return;
-  const int64_t b = idx / p;
-  const int k = (int)(idx - b * p);
-  const int64_t ix = win.bx0 + b % win.nbx, iy = win.by0 + b / win.nbx;
-  const double s = ldexp(g.side, -level);
-  const double inv_s = 1.0 / s;
-  const double cx = g.x0 + ((double)ix + 0.5) * s;
-  const double cy = g.y0 + ((double)iy + 0.5) * s;
-  const int sh = g.L - level;
-  const int64_t nL = int64_t(1) << g.L;
-  const int64_t span = int64_t(1) << sh;
-  cplx acc = {0.0, 0.0};
-  for (int64_t r = 0; r < span; ++r) {
-    const int64_t row = (iy << sh) + r;
-    const int32_t i0 = leaf_start[row * nL + (ix << sh)];
-    const int32_t i1 = leaf_start[row * nL + (ix << sh) + span];
-    for (int32_t i = i0; i < i1; ++i) {
-      const cplx w = {(sxy[2 * (int64_t)i] - cx) * inv_s, (sxy[2 * (int64_t)i + 1] - cy) * inv_s};
-      cplx pw = {1.0, 0.0}, base = w;
-      for (int e = k; e; e >>= 1) {
-        if (e & 1) pw = cmul(pw, base);
-        base = cmul(base, base);
-      }
-      if (QDIM == 1) {
-        const double m = sq[i];
-        acc.re = fma(m, pw.re, acc.re);
-        acc.im = fma(m, pw.im, acc.im);
-      } else {
-        acc = cmad(cplx{sq[2 * (int64_t)i], sq[2 * (int64_t)i + 1]}, pw, acc);
-      }
-    }
-  }
-  mp[2 * idx] = acc.re;
-  mp[2 * idx + 1] = acc.im;
-  if (mp32) {
-    mp32[2 * idx] = (float)acc.re;
-    mp32[2 * idx + 1] = (float)acc.im;
-  }
+typedef double d4v __attribute__((ext_vector_type(4)));
+
+// Orders the LDS accesses of a converged wave (its lanes exchange data
+// through LDS without a workgroup barrier).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Wave-cooperative P2M of one box (wave-uniform ix, iy): the box's leaf rows
-// are taken 64 at a time, their source counts scanned across the wave so
-// that the lanes share the rows' sources evenly (lane t takes sources t,
-// t+64, ... of the concatenated rows), each lane accumulating all p
-// coefficients with running powers m w^k into acc; the 64 partial
-// expansions are then summed by a fixed cross-lane butterfly (every lane
-// ends with the total, in the same order on every run).
-template <int PMAX, int QDIM>
-__device__ __forceinline__ void p2m_wave_box(const Geometry &g, int level, int64_t ix, int64_t iy,
-                                             const double *__restrict__ sxy,
-                                             const double *__restrict__ sq,
-                                             const int32_t *__restrict__ leaf_start, int p,
-                                             int32_t *row_first, int32_t *row_pre,
-                                             cplx (&acc)[PMAX]) {
-  const int lane = threadIdx.x;
+// Group-cooperative P2M of one box by GL neighbouring lanes of a wave (every
+// lane of the group calls with the same box; `on` false: an empty box).  The
+// box at `level` covers 2^(L-level) rows of leaf boxes, each a contiguous
+// range of the sorted sources: they are taken GL rows at a time, their source
+// counts scanned across the group so that its lanes share the sources evenly
+// (lane t takes sources t, t + GL, ... of the concatenated rows), each lane
+// accumulating all p coefficients with running powers m w^k into v (re, im
+// interleaved), the next source's loads issued before the current powers.
+template <int PMAX, int QDIM, int GL>
+__device__ __forceinline__ void p2m_group_sum(const Geometry &g, int level, int64_t ix, int64_t iy,
+                                              bool on, const double *__restrict__ sxy,
+                                              const double *__restrict__ sq,
+                                              const int32_t *__restrict__ leaf_start, int p,
+                                              int32_t *row_first, int32_t *row_pre,
+                                              double (&v)[2 * PMAX]) {
+  const int lane = threadIdx.x & 63, gl = lane & (GL - 1), g0 = lane - gl;
   const double s = ldexp(g.side, -level);
   const double inv_s = 1.0 / s;
   const double cx = g.x0 + ((double)ix + 0.5) * s;
@@ -94,56 +56,104 @@ __device__ __forceinline__ void p2m_wave_box(const Geometry &g, int level, int64
   const int64_t nL = int64_t(1) << g.L;
   const int64_t span = int64_t(1) << sh;
 #pragma unroll
-  for (int k = 0; k < PMAX; ++k) acc[k] = cplx{0.0, 0.0};
-  for (int64_t rb = 0; rb < span; rb += kWave) {
+  for (int k = 0; k < 2 * PMAX; ++k) v[k] = 0.0;
+  for (int64_t rb = 0; rb < span; rb += GL) {  // the same count for every group
     int32_t first = 0, cnt = 0;
-    if (rb + lane < span) {
-      const int64_t row = (iy << sh) + rb + lane;
+    if (on && rb + gl < span) {
+      const int64_t row = (iy << sh) + rb + gl;
       first = leaf_start[row * nL + (ix << sh)];
       cnt = leaf_start[row * nL + (ix << sh) + span] - first;
     }
-    // inclusive scan of the row counts across the wave
-    int32_t inc = cnt;
+    int32_t inc = cnt;  // inclusive scan of the row counts across the group
 #pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      const int32_t v = __shfl_up(inc, d);
-      if (lane >= d) inc += v;
+    for (int d = 1; d < GL; d <<= 1) {
+      const int32_t x = __shfl_up(inc, d, GL);
+      if (gl >= d) inc += x;
     }
-    const int32_t total = __shfl(inc, kWave - 1);
-    __syncthreads();  // the previous batch's reads are done
+    const int32_t total = __shfl(inc, GL - 1, GL);
+    wave_sync();  // the previous batch's reads are done
     row_first[lane] = first;
     row_pre[lane] = inc - cnt;
-    __syncthreads();
-    for (int32_t t = lane; t < total; t += kWave) {
-      // the row holding source t: the last row whose prefix is <= t
-      int lo = 0, hi = kWave - 1;
+    wave_sync();
+    auto source = [&](int32_t t) -> int64_t {
+      // the last row whose prefix is <= t (rows past the batch have prefix
+      // == total > t, so it is a real row)
+      int lo = 0, hi = span > 1 ? GL - 1 : 0;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (row_pre[mid] <= t) lo = mid; else hi = mid - 1;
+        if (row_pre[g0 + mid] <= t) lo = mid; else hi = mid - 1;
       }
-      // rows past the batch have prefix == total > t, so lo is a real row
-      const int64_t i = (int64_t)row_first[lo] + (t - row_pre[lo]);
-      const cplx w = {(sxy[2 * i] - cx) * inv_s, (sxy[2 * i + 1] - cy) * inv_s};
-      cplx pw = QDIM == 1 ? cplx{sq[i], 0.0} : cplx{sq[2 * i], sq[2 * i + 1]};
+      return (int64_t)row_first[g0 + lo] + (t - row_pre[g0 + lo]);
+    };
+    double nx = 0.0, ny = 0.0, qr = 0.0, qi = 0.0;
+    auto fetch = [&](int32_t t) {
+      const int64_t i = source(t);
+      nx = sxy[2 * i];
+      ny = sxy[2 * i + 1];
+      qr = sq[QDIM * i];
+      if (QDIM == 2) qi = sq[2 * i + 1];
+    };
+    if (gl < total) fetch(gl);
+    for (int32_t t = gl; t < total; t += GL) {
+      const cplx w = {(nx - cx) * inv_s, (ny - cy) * inv_s};
+      cplx pw = {qr, qi};
+      if (t + GL < total) fetch(t + GL);
 #pragma unroll
       for (int k = 0; k < PMAX; ++k)
         if (k < p) {
-          acc[k].re += pw.re;
-          acc[k].im += pw.im;
+          v[2 * k] += pw.re;
+          v[2 * k + 1] += pw.im;
           pw = cmul(pw, w);
         }
     }
   }
+}
+
+// Sums v over the D * 2 lanes whose indices differ in bits D, D/2, ..., 1,
+// halving the values each lane keeps while their number is even (the lanes
+// with the bit set keep the upper half): the lane ends with v[0, VEND) =
+// elements [base, base + VEND) of the total, in a fixed order on every run.
+// Returns whether this lane stores them (of lanes with equal results, one).
+template <int V, int D, int N>
+__device__ __forceinline__ bool group_reduce(double (&v)[N], int lane, int &base) {
+  if constexpr (D == 0) {
+    return true;
+  } else if constexpr (V % 2 == 0) {
+    constexpr int H = V / 2;
+    const bool up = lane & D;
 #pragma unroll
-  for (int k = 0; k < PMAX; ++k)
-    if (k < p) {
-      double re = acc[k].re, im = acc[k].im;
+    for (int k = 0; k < H; ++k) {
+      const double send = up ? v[k] : v[k + H], own = up ? v[k + H] : v[k];
+      v[k] = own + __shfl_xor(send, D);
+    }
+    if (up) base += H;
+    return group_reduce<H, D / 2>(v, lane, base);
+  } else {
 #pragma unroll
-      for (int d = kWave / 2; d >= 1; d >>= 1) {
-        re += __shfl_xor(re, d);
-        im += __shfl_xor(im, d);
-      }
-      acc[k] = cplx{re, im};
+    for (int k = 0; k < V; ++k) v[k] += __shfl_xor(v[k], D);
+    const bool mine = !(lane & D);
+    return group_reduce<V, D / 2>(v, lane, base) && mine;
+  }
+}
+constexpr int group_values(int v, int gl) {
+  for (; gl > 1; gl >>= 1)
+    if (v % 2 == 0) v /= 2;
+  return v;
+}
+
+// Reduces the group's partial sums and stores box b's coefficients.
+template <int PMAX, int GL>
+__device__ __forceinline__ void p2m_group_store(double (&v)[2 * PMAX], bool on, int64_t b, int p,
+                                                double *__restrict__ mp, float *__restrict__ mp32) {
+  constexpr int VEND = group_values(2 * PMAX, GL);
+  int base = 0;
+  const bool mine = group_reduce<2 * PMAX, GL / 2>(v, (int)(threadIdx.x & 63), base);
+  if (!on || !mine) return;
+#pragma unroll
+  for (int k = 0; k < VEND; ++k)
+    if (base + k < 2 * p) {
+      mp[b * 2 * p + base + k] = v[k];
+      if (mp32) mp32[b * 2 * p + base + k] = (float)v[k];
     }
 }
 
@@ -194,13 +204,13 @@ __device__ __forceinline__ cplx m2m_coeff(const ChildLevel &c, int64_t ix, int64
 // A box holding more than kCrowdedBox sources is formed by M2M from its
 // four children when the level below has them; one holding more than
 // kWaveBox sources (and no formed children) is formed by the whole wave
-// (p2m_wave_box) rather than by its own lane.
+// rather than by its own lane.
 constexpr int64_t kCrowdedBox = 32;
 constexpr int64_t kWaveBox = 256;
 
 // The rescaled multipole of a box from its four formed children, in one
 // lane: each child's coefficients are shifted to the parent's centre by the
-// synthetic division of k_m2m_tile below (p(p-1)/2 updates
+// synthetic division (p(p-1)/2 updates
 // a_j += d a_(j-1), d = (+-1/2, +-1/2) in child-size units) and the four
 // are summed, then scaled by 2^-l.
 template <int PMAX>
@@ -250,7 +260,7 @@ __device__ __forceinline__ void m2m_lane(const ChildLevel &c, int64_t ix, int64_
 // its own lane, so a wave of crowded boxes shifts them side by side), and a
 // box of more than kWaveBox sources without them is left to the whole wave,
 // which forms such boxes one after another -- or, with `defer`, to a second
-// pass of k_p2m_wave (a wave per box), this pass storing zeros for them.
+// pass of k_p2m_group (a wave per box), this pass storing zeros for them.
 // The kernel is bound by memory
 // latency (a few sources per lane): a box of one or two leaf rows keeps its
 // source ranges in registers and the next source's loads are issued before
@@ -350,189 +360,252 @@ __global__ __launch_bounds__(kWave) void k_p2m_box(Geometry g, int level, Window
       stage[lane * STR + 2 * k] = acc[k].re;
       stage[lane * STR + 2 * k + 1] = acc[k].im;
     }
-  // the boxes left to the whole wave, one at a time (a wave-uniform loop),
-  // unless a second pass (k_p2m_wave) forms them, a wave each, afterwards
-  uint64_t todo = defer ? 0ull : __ballot(b < nbox && by_wave);
-  while (todo) {
-    const int owner = __builtin_ctzll(todo);
-    todo &= todo - 1;
-    const int64_t ob = b0 + owner;
-    p2m_wave_box<PMAX, QDIM>(g, level, win.bx0 + ob % win.nbx, win.by0 + ob / win.nbx, sxy, sq,
-                             leaf_start, p, row_first, row_pre, acc);
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < PMAX; ++k)
-        if (k < p) {
-          stage[owner * STR + 2 * k] = acc[k].re;
-          stage[owner * STR + 2 * k + 1] = acc[k].im;
-        }
-    }
-  }
   __syncthreads();
   const int twop = 2 * p;
   const int64_t nb = nbox - b0 < kWave ? nbox - b0 : kWave;
+  // the boxes left to the whole wave (bit = lane), unless a second pass
+  // (k_p2m_group) forms them, a wave each, afterwards
+  uint64_t todo = defer ? 0ull : __ballot(b < nbox && by_wave);
   for (int e = lane; e < nb * twop; e += kWave) {
     const int bl = e / twop, c = e - bl * twop;
+    if ((todo >> bl) & 1) continue;
     const double v = stage[bl * STR + c];
     mp[b0 * twop + e] = v;
     if (mp32) mp32[b0 * twop + e] = (float)v;
   }
+  if (todo) {  // one at a time, a wave-uniform loop
+    double v[2 * PMAX];
+    while (todo) {
+      const int owner = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int64_t ob = b0 + owner;
+      p2m_group_sum<PMAX, QDIM, kWave>(g, level, win.bx0 + ob % win.nbx, win.by0 + ob / win.nbx, true,
+                                       sxy, sq, leaf_start, p, row_first, row_pre, v);
+      p2m_group_store<PMAX, kWave>(v, true, ob, p, mp, mp32);
+    }
+  }
 }
 
-// P2M for levels whose boxes hold many sources on average: one wave per box
-// of `win` (p2m_wave_box; deterministic, and no LDS buffer limits the waves
-// per CU beyond the 512-byte row table).
-template <int PMAX, int QDIM>
-__global__ __launch_bounds__(kWave) void k_p2m_wave(Geometry g, int level, Window win,
-                                                    const double *__restrict__ sxy,
-                                                    const double *__restrict__ sq,
-                                                    const int32_t *__restrict__ leaf_start, int p,
-                                                    double *__restrict__ mp, float *__restrict__ mp32,
-                                                    ChildLevel child, int64_t only_above) {
+// P2M with GL lanes per box (64 / GL boxes per wave): for levels whose boxes
+// hold many sources, or are too few to fill the chip with a lane each.
+// Occupancy is heavy-tailed in clustered fields: a box of more than 8 GL
+// sources is formed by M2M from its children when the level below has them,
+// and one of more than 64 GL without them, where GL < 64, by the whole wave
+// after its other boxes.
+// only_above >= 0: the second pass behind k_p2m_box, which left this kernel
+// its boxes of more than only_above sources without formed children.
+template <int PMAX, int QDIM, int GL>
+__global__ __launch_bounds__(kWave) void k_p2m_group(Geometry g, int level, Window win,
+                                                     const double *__restrict__ sxy,
+                                                     const double *__restrict__ sq,
+                                                     const int32_t *__restrict__ leaf_start, int p,
+                                                     double *__restrict__ mp, float *__restrict__ mp32,
+                                                     ChildLevel child, int64_t only_above) {
   __shared__ int32_t row_first[kWave], row_pre[kWave];
-  const int lane = threadIdx.x;
-  const int64_t b = blockIdx.x;
-  const int64_t ix = win.bx0 + b % win.nbx, iy = win.by0 + b / win.nbx;
-  cplx acc[PMAX];
-  bool by_m2m = false;
-  const bool ready = children_ready(child, ix, iy);
-  // only_above >= 0: the second pass behind k_p2m_box, which left this
-  // kernel its boxes of more than only_above sources without formed children
-  if (only_above >= 0 && ready) return;
-  if (ready || only_above >= 0) {
-    // the box's source count, its leaf rows spread over the wave
+  const int lane = threadIdx.x, gl = lane & (GL - 1);
+  const int64_t b = (int64_t)blockIdx.x * (kWave / GL) + lane / GL;
+  bool on = b < win.count();
+  const int64_t ix = on ? win.bx0 + b % win.nbx : 0, iy = on ? win.by0 + b / win.nbx : 0;
+  const bool ready = on && children_ready(child, ix, iy);
+  // the box's source count, its leaf rows spread over the group (where it
+  // decides how the box is formed)
+  int64_t cnt = 0;
+  if (on && (GL < kWave || ready || only_above >= 0)) {
     const int sh = g.L - level;
     const int64_t nL = int64_t(1) << g.L;
     const int64_t span = int64_t(1) << sh;
-    int64_t cnt = 0;
-    for (int64_t r = lane; r < span; r += kWave) {
+    for (int64_t r = gl; r < span; r += GL) {
       const int64_t row = (iy << sh) + r;
       cnt += leaf_start[row * nL + (ix << sh) + span] - leaf_start[row * nL + (ix << sh)];
     }
-#pragma unroll
-    for (int d = kWave / 2; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d);
-    if (cnt <= only_above) return;  // wave-uniform
-    by_m2m = ready && cnt > kCrowdedBox;
   }
-  if (by_m2m) {  // from the children, one coefficient per lane
-    if (lane < p) {
-      const cplx a = m2m_coeff(child, ix, iy, p, lane);
-      mp[b * 2 * p + 2 * lane] = a.re;
-      mp[b * 2 * p + 2 * lane + 1] = a.im;
+#pragma unroll
+  for (int d = GL / 2; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d);
+  if (only_above >= 0) {
+    on = on && !ready && cnt > only_above;
+    if (!__any(on)) return;  // wave-uniform
+  }
+  const bool by_m2m = on && ready && cnt > 8 * GL;
+  const bool by_wave = GL < kWave && on && !by_m2m && cnt > 64 * GL;
+  double v[2 * PMAX];
+  p2m_group_sum<PMAX, QDIM, GL>(g, level, ix, iy, on && !by_m2m && !by_wave, sxy, sq, leaf_start, p,
+                                row_first, row_pre, v);
+  p2m_group_store<PMAX, GL>(v, on && !by_m2m && !by_wave, b, p, mp, mp32);
+  if (by_m2m) {
+    for (int l = gl; l < p; l += GL) {
+      const cplx a = m2m_coeff(child, ix, iy, p, l);
+      mp[b * 2 * p + 2 * l] = a.re;
+      mp[b * 2 * p + 2 * l + 1] = a.im;
       if (mp32) {
-        mp32[b * 2 * p + 2 * lane] = (float)a.re;
-        mp32[b * 2 * p + 2 * lane + 1] = (float)a.im;
+        mp32[b * 2 * p + 2 * l] = (float)a.re;
+        mp32[b * 2 * p + 2 * l + 1] = (float)a.im;
       }
     }
-    return;
   }
-  p2m_wave_box<PMAX, QDIM>(g, level, ix, iy, sxy, sq, leaf_start, p, row_first, row_pre, acc);
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < PMAX; ++k)
-      if (k < p) {
-        mp[b * 2 * p + 2 * k] = acc[k].re;
-        mp[b * 2 * p + 2 * k + 1] = acc[k].im;
-        if (mp32) {
-          mp32[b * 2 * p + 2 * k] = (float)acc[k].re;
-          mp32[b * 2 * p + 2 * k + 1] = (float)acc[k].im;
-        }
-      }
+  if constexpr (GL < kWave) {
+    uint64_t todo = __ballot(by_wave && gl == 0);
+    while (todo) {
+      const int owner = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int64_t ob = (int64_t)blockIdx.x * (kWave / GL) + owner / GL;
+      p2m_group_sum<PMAX, QDIM, kWave>(g, level, win.bx0 + ob % win.nbx, win.by0 + ob / win.nbx, true,
+                                       sxy, sq, leaf_start, p, row_first, row_pre, v);
+      p2m_group_store<PMAX, kWave>(v, true, ob, p, mp, mp32);
+    }
   }
 }
 
-// M2M for up to four consecutive levels in one launch.  A 256-thread
+// M2M for up to four consecutive levels in one launch, as FP64 MFMAs.  A
 // workgroup owns a T x T tile of parent boxes at the finest level of the
-// launch (T = min(8, boxes per side)); four neighbouring lanes take the four
-// children of one parent, each shifting its child's p coefficients (held in
-// registers) to the parent's centre, and the four shifted expansions are
-// summed across the lanes.  The tile's parents are kept in LDS and the next
-// coarser level's (T/2)^2 parents formed from them, and so on, so a tile of
+// launch (T = min(8, boxes per side)); its parents are the rows of 16-row
+// M-tiles, C[parents][2p] = sum_q A_q[children][2p] M_q over the four child
+// quadrants q.  64 parents are four M-tiles, a wave each; their (T/2)^2
+// parents and the coarser ones are one M-tile, its N-tiles of 16 outputs
+// spread over the waves, with the children read back from LDS.  So a tile of
 // 8 x 8 boxes yields its 4 x 4, 2 x 2 and 1 x 1 ancestors in the same launch.
-//
-// The shift needs no table: in child-size units the child centre sits at
-// d = (a - 1/2) + i(c - 1/2) from the parent's (quadrant q = a + 2c, child
-// (2x + a, 2y + c)), and the parent's rescaled coefficients are
-// a_l = 2^-l sum_q sum_{k<=l} C(l,k) d^(l-k) a_k(child q).  The binomial sums
-// are formed by repeated synthetic division (p(p-1)/2 updates
-// a_j += d a_(j-1)); d's parts are +-1/2, so every product in them is exact.
-template <int PMAX>
-__global__ __launch_bounds__(kThreads) void k_m2m_tile(M2MChain c) {
-  __shared__ double2 bufA[64 * PMAX];  // stage 0 and 2 results
-  __shared__ double2 bufB[16 * PMAX];  // stage 1 results
-  const int tid = threadIdx.x;
-  const int q = tid & 3, par = tid >> 2;  // child quadrant, parent in the tile
-  const int p = c.p;
+// The products are short against a memory round trip, so the loads are
+// ordered by hand: every child coefficient of the tile first, the next
+// quadrant's operator while one multiplies, and the coarser stages' operator
+// (the same for all of them) once (64 workgroups, p = 20: 18 us, against 41
+// with a lane per child shifting it by synthetic division).
+template <int KS>
+__global__ __launch_bounds__(kThreads) void k_m2m_chain(M2MChain c, const double *__restrict__ frag) {
+  constexpr int NT = (KS + 3) / 4, REC = 4 * KS + 1;
+  __shared__ double bufA[64 * REC];  // stage 0 and 2 results
+  __shared__ double bufB[16 * REC];  // stage 1 results
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int twop = 2 * c.p;
   const int64_t n = int64_t(1) << c.level;
   const int T = n < 8 ? (int)n : 8;
   const int64_t tiles = n / T;
   const int64_t tbx = blockIdx.x % tiles, tby = blockIdx.x / tiles;
-  const double dr = (q & 1) - 0.5, di = (q >> 1) - 0.5;
-  for (int st = 0; st < c.nlev; ++st) {
-    const int Ts = T >> st;      // parents per tile side at this stage
-    const int64_t ns = n >> st;  // boxes per side at this level
-    // whole waves stay in step for the cross-lane sums below
-    if ((tid & ~63) < 4 * Ts * Ts) {
-      const bool on = par < Ts * Ts;
-      const int tx = on ? par % Ts : 0, ty = on ? par / Ts : 0;
-      cplx a[PMAX];
-      if (st == 0) {
-        const int64_t cb = (2 * (tby * T + ty) + (q >> 1)) * (2 * n) + 2 * (tbx * T + tx) + (q & 1);
-        const double2 *src = reinterpret_cast<const double2 *>(c.child) + cb * p;
+
+  auto store = [&](int st, int mt, int nt, const d4v &acc) {
+    const int Ts = T >> st, P = Ts * Ts, lts = 31 - __builtin_clz(Ts);
+    const int64_t ns = n >> st;
+    const int col = nt * 16 + i;
+    double *keep = st == 1 ? bufB : bufA;
 #pragma unroll
-        for (int k = 0; k < PMAX; ++k)
-          if (k < p) {
-            const double2 v = on ? src[k] : make_double2(0.0, 0.0);
-            a[k] = cplx{v.x, v.y};
-          }
-      } else {
-        const double2 *src = (st == 2 ? bufB : bufA) + ((2 * ty + (q >> 1)) * (2 * Ts) + 2 * tx + (q & 1)) * PMAX;
+    for (int r = 0; r < 4; ++r) {
+      const int par = mt * 16 + kq + 4 * r;
+      if (par >= P || col >= twop) continue;
+      const int64_t box = (tby * Ts + (par >> lts)) * ns + tbx * Ts + (par & (Ts - 1));
+      c.out[st][box * twop + col] = acc[r];
+      if (c.out32[st]) c.out32[st][box * twop + col] = (float)acc[r];
+      if (st + 1 < c.nlev) keep[par * REC + col] = acc[r];
+    }
+  };
+  // coefficients of the four children of parent `par` at stage 0.  The
+  // K-steps of the product take the coefficients in the order 8 h + 2 kq,
+  // 8 h + 2 kq + 1 (the operator's fragments are built to match), so that a
+  // lane reads them in pairs of 16 bytes
+  double av[4][KS];
+  {
+    const int P = T * T, par = (P == 64 ? wv * 16 : 0) + i, lts = 31 - __builtin_clz(T);
+    const bool on = par < P;
+    const int tx = on ? par & (T - 1) : 0, ty = on ? par >> lts : 0;
 #pragma unroll
-        for (int k = 0; k < PMAX; ++k)
-          if (k < p) {
-            const double2 v = on ? src[k] : make_double2(0.0, 0.0);
-            a[k] = cplx{v.x, v.y};
-          }
-      }
+    for (int q = 0; q < 4; ++q) {
+      const int64_t cb = (2 * (tby * T + ty) + (q >> 1)) * (2 * n) + 2 * (tbx * T + tx) + (q & 1);
+      const double2 *src = reinterpret_cast<const double2 *>(c.child + cb * twop);
 #pragma unroll
-      for (int k = 0; k + 1 < PMAX; ++k)
-        if (k + 1 < p) {
-#pragma unroll
-          for (int j = PMAX - 1; j > k; --j)
-            if (j < p) {
-              a[j].re = fma(dr, a[j - 1].re, fma(-di, a[j - 1].im, a[j].re));
-              a[j].im = fma(dr, a[j - 1].im, fma(di, a[j - 1].re, a[j].im));
-            }
-        }
-      // sum over the four children (lanes 4i .. 4i+3), in a fixed order
-#pragma unroll
-      for (int l = 0; l < PMAX; ++l)
-        if (l < p) {
-          double re = a[l].re + __shfl_xor(a[l].re, 1);
-          double im = a[l].im + __shfl_xor(a[l].im, 1);
-          re += __shfl_xor(re, 2);
-          im += __shfl_xor(im, 2);
-          a[l] = cplx{ldexp(re, -l), ldexp(im, -l)};
-        }
-      if (on && q == 0) {
-        const int64_t box = (tby * Ts + ty) * ns + tbx * Ts + tx;
-        double2 *gout = reinterpret_cast<double2 *>(c.out[st]) + box * p;
-        float2 *gout32 = c.out32[st] ? reinterpret_cast<float2 *>(c.out32[st]) + box * p : nullptr;
-        double2 *keep = st == 1 ? bufB : bufA;
-#pragma unroll
-        for (int l = 0; l < PMAX; ++l)
-          if (l < p) {
-            gout[l] = make_double2(a[l].re, a[l].im);
-            if (gout32) gout32[l] = make_float2((float)a[l].re, (float)a[l].im);
-            if (st + 1 < c.nlev) keep[par * PMAX + l] = make_double2(a[l].re, a[l].im);
-          }
+      for (int h = 0; h < KS / 2; ++h) {
+        const double2 v = on && 4 * h + kq < c.p ? src[4 * h + kq] : make_double2(0.0, 0.0);
+        av[q][2 * h] = v.x;
+        av[q][2 * h + 1] = v.y;
       }
     }
+  }
+  int st = 0;
+  if (T == 8) {
+    // 64 parents, a wave per M-tile, N-tiles NH at a time
+    constexpr int NH = KS <= 12 ? NT : 1;
+    for (int n0 = 0; n0 < NT; n0 += NH) {
+      d4v acc[NH];
+      double b[2][KS * NH];
+      auto load_b = [&](int q, double (&dst)[KS * NH]) {
+        const double *bs = frag + ((size_t)q * KS * NT + n0) * 64 + lane;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int h = 0; h < NH; ++h) dst[ks * NH + h] = bs[(ks * NT + h) * 64];
+      };
+      load_b(0, b[0]);
+#pragma unroll
+      for (int h = 0; h < NH; ++h) acc[h] = d4v{0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q < 3) load_b(q + 1, b[(q + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int h = 0; h < NH; ++h)
+            acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q][ks], b[q & 1][ks * NH + h], acc[h], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int h = 0; h < NH; ++h) store(0, wv, n0 + h, acc[h]);
+    }
+    st = 1;
+    if (c.nlev == 1) return;  // uniform
+  }
+  // at most 16 parents: one M-tile, wave wv takes N-tiles wv, wv + 4
+  double b[4][KS];
+  auto load_nt = [&](int nt) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) b[q][ks] = frag[((size_t)(q * KS + ks) * NT + nt) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (wv < NT) load_nt(wv);
+  for (; st < c.nlev; ++st) {
     __syncthreads();
+    const int Ts = T >> st, P = Ts * Ts, lts = 31 - __builtin_clz(Ts);
+    if (st > 0) {
+      const bool on = i < P;
+      const int tx = on ? i & (Ts - 1) : 0, ty = on ? i >> lts : 0;
+      const double *kids = st == 2 ? bufB : bufA;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double *src = kids + ((2 * ty + (q >> 1)) * (2 * Ts) + 2 * tx + (q & 1)) * REC;
+#pragma unroll
+        for (int h = 0; h < KS / 2; ++h) {
+          const int k = 8 * h + 2 * kq;
+          av[q][2 * h] = on && k < twop ? src[k] : 0.0;
+          av[q][2 * h + 1] = on && k < twop ? src[k + 1] : 0.0;
+        }
+      }
+    }
+    for (int nt = wv; nt < NT; nt += kThreads / 64) {
+      if (NT > 4 && (nt != wv || st > 0)) load_nt(nt);
+      d4v acc = d4v{0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q][ks], b[q][ks], acc, 0, 0, 0);
+      store(st, 0, nt, acc);
+    }
   }
 }
 
-inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
+// Lanes per box (1, 4, 16 or 64) of a P2M level of `boxes` boxes holding
+// `mean` sources each.  A lane per box is the fastest while the boxes fill the
+// chip (2 waves per SIMD: 131072 lanes) with up to ~64 sources each; fewer
+// boxes get as many lanes as fill it, but no more than they have sources
+// (p = 17: 192 boxes of ~300 sources 7.7 us with 64 lanes, 154 with one; 256
+// boxes of 8, p = 12, 10.9 with 4, 29 with one).  Fuller boxes get a lane per
+// 16 sources (16384 boxes of 305: 84 us with 16 lanes, 156 with 64 and a
+// butterfly over all coefficients), or per 4 in clustered fields, whose
+// boxes differ so much that a wave's groups would wait for the fullest.
+int p2m_lanes(int64_t boxes, double mean, bool clustered) {
+  const double fill = 131072.0 / (double)boxes;
+  const double want = mean > 64.0 ? std::max(mean / (clustered ? 4.0 : 16.0), std::min(mean, fill)) : std::min(mean, fill);
+  return want >= 32.0 ? 64 : (want >= 8.0 ? 16 : (want >= 2.0 ? 4 : 1));
+}
 
 }  // namespace
 
@@ -541,56 +614,42 @@ void launch_p2m(Geometry g, int level, Window win, const double *sxy, const doub
                 const int32_t *leaf_start, int p, double *mp, float *mp32, double win_sources,
                 bool clustered, Window child_win, const double *child_mp, hipStream_t stream) {
   const ChildLevel child{child_win, child_mp};
-  const int64_t n = win.count() * p;
-  if (n == 0) return;
-  // boxes of ~128 sources or more (on average over the window): a wave per
-  // box (below that a thread per box, crowded boxes by M2M in their lanes,
-  // measured faster on a galaxy halo's levels of 24 and 91 stars per box)
-  auto wave_per_box = [&](int64_t only_above) {
-    const unsigned nb = (unsigned)win.count();
+  const int64_t boxes = win.count();
+  if (boxes == 0) return;
+  auto group = [&](auto gl_c, int64_t only_above) {
+    constexpr int GL = decltype(gl_c)::value;
+    const unsigned nb = (unsigned)((boxes * GL + kWave - 1) / kWave);
     if (qdim == 2)
-      LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_wave<PM, 2>), dim3(nb), dim3(kWave), 0, stream,
-                                               g, level, win, sxy, sq, leaf_start, p, mp, mp32,
+      LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_group<PM, 2, GL>), dim3(nb), dim3(kWave), 0,
+                                               stream, g, level, win, sxy, sq, leaf_start, p, mp, mp32,
                                                child, only_above));
     else
-      LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_wave<PM, 1>), dim3(nb), dim3(kWave), 0, stream,
-                                               g, level, win, sxy, sq, leaf_start, p, mp, mp32,
+      LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_group<PM, 1, GL>), dim3(nb), dim3(kWave), 0,
+                                               stream, g, level, win, sxy, sq, leaf_start, p, mp, mp32,
                                                child, only_above));
     LENS_HIP(hipGetLastError());
   };
-  const double mean = win_sources / (double)win.count();
-  if (mean > 128.0) {
-    wave_per_box(-1);
-    return;
-  }
-  // otherwise a thread per box (all coefficients), unless p exceeds the
-  // register budget of that kernel's largest instance.  In a clustered
-  // field whose leaf boxes hold a few sources on average, those of more
-  // than kWaveBox sources get a wave each in a second pass rather than their
-  // lane's wave one after another (above the leaf level such boxes are
-  // formed from their children).
-  if (p <= 24) {
-    const int defer = (clustered && mean > 2.0 && child_mp == nullptr) ? 1 : 0;
-    const unsigned nb = (unsigned)((win.count() + kWave - 1) / kWave);
-    if (qdim == 2)
-      LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_box<PM, 2>), dim3(nb), dim3(kWave), 0, stream,
-                                               g, level, win, sxy, sq, leaf_start, p, mp, mp32,
-                                               child, defer));
-    else
-      LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_box<PM, 1>), dim3(nb), dim3(kWave), 0, stream,
-                                               g, level, win, sxy, sq, leaf_start, p, mp, mp32,
-                                               child, defer));
-    LENS_HIP(hipGetLastError());
-    if (defer) wave_per_box(kWaveBox);
-    return;
-  }
+  const double mean = win_sources / (double)boxes;
+  const int gl = p2m_lanes(boxes, mean, clustered);
+  if (gl == 64) return group(std::integral_constant<int, 64>{}, -1);
+  if (gl == 16) return group(std::integral_constant<int, 16>{}, -1);
+  if (gl == 4) return group(std::integral_constant<int, 4>{}, -1);
+  // A thread per box.  In a clustered field whose leaf boxes hold a few
+  // sources on average, those of more than kWaveBox sources get a wave each
+  // in a second pass rather than their lane's wave one after another (above
+  // the leaf level such boxes are formed from their children).
+  const int defer = (clustered && mean > 2.0 && child_mp == nullptr) ? 1 : 0;
+  const unsigned nb = (unsigned)((boxes + kWave - 1) / kWave);
   if (qdim == 2)
-    hipLaunchKernelGGL(k_p2m<2>, dim3(blocks_for(n)), dim3(kThreads), 0, stream, g, level, win,
-                       sxy, sq, leaf_start, p, mp, mp32);
+    LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_box<PM, 2>), dim3(nb), dim3(kWave), 0, stream,
+                                             g, level, win, sxy, sq, leaf_start, p, mp, mp32,
+                                             child, defer));
   else
-    hipLaunchKernelGGL(k_p2m<1>, dim3(blocks_for(n)), dim3(kThreads), 0, stream, g, level, win,
-                       sxy, sq, leaf_start, p, mp, mp32);
+    LENS_PMAX_DISPATCH(p, hipLaunchKernelGGL((k_p2m_box<PM, 1>), dim3(nb), dim3(kWave), 0, stream,
+                                             g, level, win, sxy, sq, leaf_start, p, mp, mp32,
+                                             child, defer));
   LENS_HIP(hipGetLastError());
+  if (defer) group(std::integral_constant<int, 64>{}, kWaveBox);
 }
 
 int m2m_chain_levels(int level) {
@@ -603,13 +662,14 @@ int m2m_chain_levels(int level) {
   return k;
 }
 
-void launch_m2m_chain(const M2MChain &c, hipStream_t stream) {
+void launch_m2m_chain(const M2MChain &c, const OpTables &t, hipStream_t stream) {
   if (c.nlev < 1 || c.nlev > m2m_chain_levels(c.level))
     fail(LENS_EINVAL, "M2M chain: bad level count");
   const int64_t n = int64_t(1) << c.level;
   const int64_t T = n < 8 ? n : 8;
   const unsigned blocks = (unsigned)((n / T) * (n / T));
-  LENS_PMAX_DISPATCH(c.p, hipLaunchKernelGGL((k_m2m_tile<PM>), dim3(blocks), dim3(kThreads), 0, stream, c));
+  LENS_KS_DISPATCH(t.ks, hipLaunchKernelGGL((k_m2m_chain<KS>), dim3(blocks), dim3(kThreads), 0, stream,
+                                            c, t.m2m_frag));
   LENS_HIP(hipGetLastError());
 }
 

@@ -45,3 +45,24 @@ def test_m2l_forms_agree_bit_for_bit(lf, p, precision):
         # truncation: the interaction list's ratio is at most 0.55, 0.55^30 = 2e-8
         # of a box's field; sums cancel below that
         assert float((whole - ref).norm() / ref.norm()) < 1e-8
+
+
+@pytest.mark.parametrize("p", [24, 26, 36, 40])
+@pytest.mark.parametrize("n,leaf", [(40, 2), (3000, 3), (3000, 5), (20000, 4), (20000, 7), (300000, 6)])
+def test_p2m_lanes_and_shift_chains(lf, n, leaf, p):
+    # 16 to 16384 leaf boxes of a fraction of a source to ~75 each (P2M with
+    # 1, 4, 16 and 64 lanes per box), 1 to 6 levels of M2M and L2L above them,
+    # and one leaf box of 3000 more sources with no level below it.  Truncation:
+    # a source of the interaction list is at least 2 sides from the target's
+    # centre, the target at most 0.71, the multipole's sources within 0.71 of
+    # theirs, so terms fall by (1.41 / 2)^p at worst and by ~0.55^p on the mean
+    # over a box; the field's own scale divides out.
+    f = wl.random_field(n, 30.0, seed=43 + leaf, masses="powerlaw", kappa_s=0.1, gamma=0.2)
+    rng = np.random.default_rng(5)
+    xy = np.concatenate([f.xy, np.array([7.3, -4.1]) + 0.02 * rng.standard_normal((3000, 2))])
+    m = np.concatenate([f.m, np.full(3000, 0.01)])
+    g = lf.Grid(-32.0, -32.0, 1.0, 1.0, 64, 64)
+    kw = dict(grid=g, kappa_s=f.kappa_s, gamma=f.gamma)
+    ref = lf.deflect(dev(xy), dev(m), method="direct", **kw)
+    y = lf.deflect(dev(xy), dev(m), precision="fp64", p=p, leaf_level=leaf, **kw)
+    assert float((y - ref).norm() / ref.norm()) < 4 * 0.55 ** p
