@@ -862,8 +862,7 @@ void fmm_grid_rows(lens_plan &P, const lens_grid &grid, int64_t j0, int64_t j1, 
 
 // Explicit rays: sorted by leaf box of the window, evaluated box by box,
 // written back in the caller's order.  The downward pass over the window of
-// bb is separate, so that repeated evaluations at moving points inside bb
-// (Newton steps) share it.
+// bb is separate: the image finder's Newton steps share it.
 struct ExplicitLocals {
   Window wl;
   double *loc = nullptr;
@@ -2657,18 +2656,51 @@ lens_status lens_find_images(lens_plan *plan, const lens_field *field, const len
       } keep{std::move(cbufs), st};
       if (n == 0) return;
       // Newton refinement
-      double *yc = sc.get<double>((size_t)n * 2), *dc = sc.get<double>((size_t)n * 2);
-      double *res = sc.get<double>((size_t)n), *det = sc.get<double>((size_t)n);
-      uint32_t *unconv = sc.get<uint32_t>(1);
-      ExplicitLocals el;
-      if (P) el = explicit_locals(*P, gbb, sc, st);
-      NewtonArgs na{n, cand_x, cand_s, sources, yc, dc, c1, c2, tol,
+      const double *fx = cand_x, *fres = nullptr, *fdet = nullptr;  // the final iteration's
+      NewtonArgs na{n, cand_x, cand_s, sources, nullptr, nullptr, c1, c2, tol,
                     4.0 * std::hypot(grid->dx, grid->dy), {gbb[0], gbb[1], gbb[2], gbb[3]},
-                    res, det, unconv, 1};
-      for (int it = 0; it <= max_iter; ++it) {
-        if (P) {
-          fmm_explicit_eval(*P, el, cand_x, n, c1, c2, yc, st, dc);
-        } else {
+                    nullptr, nullptr, nullptr, 1};
+      if (P) {
+        const ExplicitLocals el = explicit_locals(*P, gbb, sc, st);
+        EvalArgs ea{};
+        fill_star_side(*P, el.wl, el.loc, ea);
+        // iterations per launch: a few first (most sources converge in
+        // them), then up to 64, in at most 64 MB of history
+        const int64_t room = std::max<int64_t>(1, (int64_t(1) << 26) / (32 * n));
+        const int64_t most = std::min<int64_t>({room, 64, (int64_t)max_iter + 1});
+        NewtonHistory h{};
+        h.x = sc.get<double>((size_t)(most * n) * 2);
+        h.res = sc.get<double>((size_t)(most * n));
+        h.det = sc.get<double>((size_t)(most * n));
+        h.unconverged = sc.get<uint32_t>((size_t)most);
+        std::vector<uint32_t> left((size_t)most);
+        for (int64_t done = 0; done <= max_iter;) {
+          h.iters = (int32_t)std::min<int64_t>(done == 0 ? std::min<int64_t>(most, 8) : most, max_iter + 1 - done);
+          h.last_steps = done + h.iters <= max_iter;
+          launch_fill_u32(h.unconverged, h.iters, 0u, st);
+          {
+            StageTimer tm("images", st);
+            launch_newton_fmm(na, ea, h, P->precision, st);
+          }
+          LENS_HIP(hipMemcpyAsync(left.data(), h.unconverged, (size_t)h.iters * 4, hipMemcpyDeviceToHost, st));
+          LENS_HIP(hipStreamSynchronize(st));
+          const int64_t at = std::min<int64_t>(std::find(left.begin(), left.begin() + h.iters, 0u) - left.begin(),
+                                               h.iters - 1);
+          fx = h.x + 2 * at * n;
+          fres = h.res + at * n;
+          fdet = h.det + at * n;
+          done += h.iters;
+          if (left[(size_t)at] == 0) break;
+        }
+        P->last_stream = st;
+      } else {
+        double *yc = sc.get<double>((size_t)n * 2), *dc = sc.get<double>((size_t)n * 2);
+        na.y = yc;
+        na.dfdz = dc;
+        fres = na.res = sc.get<double>((size_t)n);
+        fdet = na.det = sc.get<double>((size_t)n);
+        na.unconverged = sc.get<uint32_t>(1);
+        for (int it = 0; it <= max_iter; ++it) {
           DirectArgs d{};
           d.n_stars = fv.f.n_stars;
           d.sxy = fv.f.xy;
@@ -2680,19 +2712,19 @@ lens_status lens_find_images(lens_plan *plan, const lens_field *field, const len
           d.y_out = yc;
           d.dfdz_out = dc;
           launch_direct(d, st);
+          launch_fill_u32(na.unconverged, 1, 0u, st);
+          na.step = it < max_iter;
+          StageTimer tm("images", st);
+          launch_newton(na, st);
+          if (read_scalar(na.unconverged, st) == 0) break;
         }
-        launch_fill_u32(unconv, 1, 0u, st);
-        na.step = it < max_iter;
-        StageTimer tm("images", st);
-        launch_newton(na, st);
-        if (read_scalar(unconv, st) == 0) break;
       }
       // merge the converged candidates of each source (host: images are few)
       std::vector<double> hx((size_t)n * 2), hr((size_t)n), hd((size_t)n);
       std::vector<int32_t> hs((size_t)n);
-      LENS_HIP(hipMemcpyAsync(hx.data(), cand_x, hx.size() * 8, hipMemcpyDeviceToHost, st));
-      LENS_HIP(hipMemcpyAsync(hr.data(), res, hr.size() * 8, hipMemcpyDeviceToHost, st));
-      LENS_HIP(hipMemcpyAsync(hd.data(), det, hd.size() * 8, hipMemcpyDeviceToHost, st));
+      LENS_HIP(hipMemcpyAsync(hx.data(), fx, hx.size() * 8, hipMemcpyDeviceToHost, st));
+      LENS_HIP(hipMemcpyAsync(hr.data(), fres, hr.size() * 8, hipMemcpyDeviceToHost, st));
+      LENS_HIP(hipMemcpyAsync(hd.data(), fdet, hd.size() * 8, hipMemcpyDeviceToHost, st));
       LENS_HIP(hipMemcpyAsync(hs.data(), cand_s, hs.size() * 4, hipMemcpyDeviceToHost, st));
       LENS_HIP(hipStreamSynchronize(st));
       std::vector<int64_t> ord;

@@ -83,24 +83,14 @@ __global__ __launch_bounds__(kThreads) void k_image_cells(ImageCellArgs a) {
   }
 }
 
-// One Newton step per candidate from y(x) and f'(x): x <- x + A^-1 (beta - y),
-// the step's length clamped to max_step and x to the box.  res receives
-// |beta - y| at the x the step started from; *unconverged counts those above
-// tol.
-__global__ __launch_bounds__(kThreads) void k_newton(NewtonArgs a) {
-  const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (k >= a.n) return;
-  const int32_t s = a.cand_s[k];
-  const double r0 = a.src[2 * s] - a.y[2 * k], r1 = a.src[2 * s + 1] - a.y[2 * k + 1];
-  const double res = sqrt(r0 * r0 + r1 * r1);
-  const double fr = a.dfdz[2 * k], fi = a.dfdz[2 * k + 1];
+// One Newton step x <- x + A^-1 (beta - y) from the residual (r0, r1) of
+// length res and f', its length clamped to max_step and x to the box; no step
+// if !move.  Returns det A.
+__device__ __forceinline__ double newton_step(const NewtonArgs &a, double r0, double r1, double res,
+                                              double fr, double fi, bool move, double &x0, double &x1) {
   const double A11 = a.c1 - fr, A22 = a.c2 + fr, A12 = fi;
   const double det = A11 * A22 - A12 * A12;
-  a.res[k] = res;
-  a.det[k] = det;
-  if (!(res <= a.tol)) atomicAdd(a.unconverged, 1u);
-  if (!a.step) return;
-  if (!(res > 0.0) || !(det != 0.0) || !isfinite(det)) return;
+  if (!move || !(res > 0.0) || !(det != 0.0) || !isfinite(det)) return det;
   double d0 = (A22 * r0 - A12 * r1) / det, d1 = (A11 * r1 - A12 * r0) / det;
   const double len = sqrt(d0 * d0 + d1 * d1);
   if (!(len <= a.max_step)) {
@@ -108,8 +98,125 @@ __global__ __launch_bounds__(kThreads) void k_newton(NewtonArgs a) {
     d0 *= f;
     d1 *= f;
   }
-  a.cand_x[2 * k] = fmin(fmax(a.cand_x[2 * k] + d0, a.box[0]), a.box[2]);
-  a.cand_x[2 * k + 1] = fmin(fmax(a.cand_x[2 * k + 1] + d1, a.box[1]), a.box[3]);
+  x0 = fmin(fmax(x0 + d0, a.box[0]), a.box[2]);
+  x1 = fmin(fmax(x1 + d1, a.box[1]), a.box[3]);
+  return det;
+}
+
+// One Newton step per candidate from y(x) and f'(x) (the direct sum's).  res
+// receives |beta - y| at the x the step started from; *unconverged counts
+// those above tol.
+__global__ __launch_bounds__(kThreads) void k_newton(NewtonArgs a) {
+  const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (k >= a.n) return;
+  const int32_t s = a.cand_s[k];
+  const double r0 = a.src[2 * s] - a.y[2 * k], r1 = a.src[2 * s + 1] - a.y[2 * k + 1];
+  const double res = sqrt(r0 * r0 + r1 * r1);
+  a.res[k] = res;
+  if (!(res <= a.tol)) atomicAdd(a.unconverged, 1u);
+  a.det[k] = newton_step(a, r0, r1, res, a.dfdz[2 * k], a.dfdz[2 * k + 1], a.step != 0, a.cand_x[2 * k],
+                         a.cand_x[2 * k + 1]);
+}
+
+// Newton iterations of the candidates on the FMM, a wave per candidate: each
+// iteration evaluates y and f' at x -- the lanes share the stars of the 3x3
+// leaf neighbourhood, their sums added across the wave in FP64, and the local
+// expansion and its derivative come from one Horner recurrence -- and steps as
+// k_newton does.  One launch takes a.iters iterations and keeps every one's
+// (x after the step, residual, det A) and the number of candidates above tol,
+// so the caller can stop at the first iteration that leaves none.  (A launch
+// per stage of each iteration -- sort the candidates by box, evaluate, step,
+// read the count back -- took 110 us an iteration for ~1000 candidates; this
+// kernel takes about 3.)
+template <bool MIXED>
+__global__ __launch_bounds__(64) void k_newton_fmm(NewtonArgs a, EvalArgs e, NewtonHistory h) {
+  const int lane = threadIdx.x;
+  const int64_t k = blockIdx.x;
+  const int32_t sid = a.cand_s[k];
+  const double beta0 = a.src[2 * sid], beta1 = a.src[2 * sid + 1];
+  double x0 = a.cand_x[2 * k], x1 = a.cand_x[2 * k + 1];
+  const int64_t nL = int64_t(1) << e.g.L;
+  const double s = ldexp(e.g.side, -e.g.L), inv_s = 1.0 / s;
+  for (int it = 0; it < h.iters; ++it) {
+    // the candidate's box, clamped to the window (as explicit rays are)
+    int64_t ix = box_coord(x0, e.g.x0, s, nL) - e.win.bx0;
+    int64_t iy = box_coord(x1, e.g.y0, s, nL) - e.win.by0;
+    ix = ix < 0 ? 0 : (ix >= e.win.nbx ? e.win.nbx - 1 : ix);
+    iy = iy < 0 ? 0 : (iy >= e.win.nby ? e.win.nby - 1 : iy);
+    const int64_t gx = e.win.bx0 + ix, gy = e.win.by0 + iy;
+    int32_t rs[3], pre[4];
+    pre[0] = 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int64_t row = gy - 1 + d;
+      rs[d] = 0;
+      int32_t re = 0;
+      if (row >= 0 && row < nL) {
+        rs[d] = e.leaf_start[row * nL + (gx > 0 ? gx - 1 : 0)];
+        re = e.leaf_start[row * nL + (gx + 1 < nL ? gx + 1 : nL - 1) + 1];
+      }
+      pre[d + 1] = pre[d] + (re - rs[d]);
+    }
+    double a1 = 0.0, a2 = 0.0, dre = 0.0, dim = 0.0;
+    for (int32_t t = lane; t < pre[3]; t += 64) {
+      const int d = t >= pre[2] ? 2 : (t >= pre[1] ? 1 : 0);
+      const int64_t i = (d == 2 ? rs[2] - pre[2] : (d == 1 ? rs[1] - pre[1] : rs[0])) + (int64_t)t;
+      const double ex = x0 - e.sxy[2 * i], ey = x1 - e.sxy[2 * i + 1];
+      if (MIXED) {
+        constexpr float tiny = 0x1p-100f;
+        const float dx = (float)ex, dy = (float)ey;
+        const float r2 = fmaf(dx, dx, fmaf(dy, dy, tiny)), inv = rcp_f32(r2), w = e.sm32[i] * inv;
+        const float u = r2 > tiny ? w * inv : 0.0f;
+        a1 += (double)(w * dx);
+        a2 += (double)(w * dy);
+        dre += (double)(-u * ((dx - dy) * (dx + dy)));
+        dim += (double)((u + u) * (dx * dy));
+      } else {
+        constexpr double tiny = 0x1p-664;
+        const double r2 = fma(ex, ex, fma(ey, ey, tiny)), inv = rcp_f64(r2), w = e.sm[i] * inv;
+        const double u = r2 > tiny ? w * inv : 0.0;
+        a1 = fma(w, ex, a1);
+        a2 = fma(w, ey, a2);
+        dre = fma(-u, (ex - ey) * (ex + ey), dre);
+        dim = fma(u + u, ex * ey, dim);
+      }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      a1 += __shfl_xor(a1, d);
+      a2 += __shfl_xor(a2, d);
+      dre += __shfl_xor(dre, d);
+      dim += __shfl_xor(dim, d);
+    }
+    // far field: f = sum b_l w^l and its derivative
+    const double2 *lb = reinterpret_cast<const double2 *>(e.loc) + (iy * e.win.nbx + ix) * e.p;
+    const cplx w = {(x0 - (e.g.x0 + ((double)gx + 0.5) * s)) * inv_s,
+                    (x1 - (e.g.y0 + ((double)gy + 0.5) * s)) * inv_s};
+    cplx f = {0.0, 0.0}, df = {0.0, 0.0};
+#pragma unroll 4
+    for (int l = e.p - 1; l >= 0; --l) {
+      const double2 b = lb[l];
+      df = cmad(df, w, f);
+      f = cmad(f, w, cplx{b.x, b.y});
+    }
+    const double y0 = a.c1 * x0 - (f.re + a1), y1 = a.c2 * x1 - (a2 - f.im);
+    const double fr = fma(df.re, inv_s, dre), fi = fma(df.im, inv_s, dim);
+    const double r0 = beta0 - y0, r1 = beta1 - y1;
+    const double res = sqrt(r0 * r0 + r1 * r1);
+    const double det = newton_step(a, r0, r1, res, fr, fi, h.last_steps || it + 1 < h.iters, x0, x1);
+    if (lane == 0) {
+      const int64_t o = (int64_t)it * a.n + k;
+      h.x[2 * o] = x0;
+      h.x[2 * o + 1] = x1;
+      h.res[o] = res;
+      h.det[o] = det;
+      if (!(res <= a.tol)) atomicAdd(&h.unconverged[it], 1u);
+    }
+  }
+  if (lane == 0) {
+    a.cand_x[2 * k] = x0;
+    a.cand_x[2 * k + 1] = x1;
+  }
 }
 
 // det A at the four corners of a cell: zero crossings on its edges.
@@ -221,6 +328,17 @@ void launch_image_cells(const ImageCellArgs &a, hipStream_t stream) {
 void launch_newton(const NewtonArgs &a, hipStream_t stream) {
   if (a.n <= 0) return;
   hipLaunchKernelGGL(k_newton, dim3(blocks_for(a.n)), dim3(kThreads), 0, stream, a);
+  LENS_HIP(hipGetLastError());
+}
+
+void launch_newton_fmm(const NewtonArgs &a, const EvalArgs &e, const NewtonHistory &h, int precision,
+                       hipStream_t stream) {
+  if (a.n <= 0) return;
+  if (a.n > 0x7fffffff) fail(LENS_EUNSUPPORTED, "too many image candidates");
+  if (precision == LENS_MIXED)
+    hipLaunchKernelGGL(k_newton_fmm<true>, dim3((unsigned)a.n), dim3(64), 0, stream, a, e, h);
+  else
+    hipLaunchKernelGGL(k_newton_fmm<false>, dim3((unsigned)a.n), dim3(64), 0, stream, a, e, h);
   LENS_HIP(hipGetLastError());
 }
 

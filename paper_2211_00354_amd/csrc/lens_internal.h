@@ -356,6 +356,17 @@ struct NewtonArgs {
   int step;               // 0: residual and det only
 };
 void launch_newton(const NewtonArgs &a, hipStream_t stream);
+// Several iterations on the FMM in one launch (e: the star side, window and
+// locals of the rays' box): iteration i leaves its results in the i-th slices.
+struct NewtonHistory {
+  int32_t iters;
+  int32_t last_steps;     // whether the last iteration steps too
+  double *x;              // [iters][n][2] positions after the step
+  double *res, *det;      // [iters][n] at the position before it
+  uint32_t *unconverged;  // [iters], zeroed by the caller
+};
+void launch_newton_fmm(const NewtonArgs &a, const EvalArgs &e, const NewtonHistory &h, int precision,
+                       hipStream_t stream);
 
 struct CritArgs {
   const double *dfdz;

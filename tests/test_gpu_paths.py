@@ -66,3 +66,25 @@ def test_p2m_lanes_and_shift_chains(lf, n, leaf, p):
     ref = lf.deflect(dev(xy), dev(m), method="direct", **kw)
     y = lf.deflect(dev(xy), dev(m), precision="fp64", p=p, leaf_level=leaf, **kw)
     assert float((y - ref).norm() / ref.norm()) < 4 * 0.55 ** p
+
+
+@pytest.mark.parametrize("precision,p,tol", [("fp64", 36, 1e-8), ("mixed", 24, 1e-4)])
+@pytest.mark.parametrize("max_iter", [0, 1, 7, 8, 9, 40, 80])
+def test_newton_iterations_match_direct(lf, max_iter, precision, p, tol):
+    # the iterations run 8, then up to 64 to a launch; the direct sum steps one
+    # at a time.  Both stop at the first iteration that leaves no candidate
+    # above tol, or after max_iter, so they keep the same images; positions
+    # within the evaluations' difference over |det A| (at most 1e3 here).
+    f = wl.random_field(300, 30.0, seed=51, gamma=0.15)
+    g = lf.Grid(-24.0, -24.0, 0.1875, 0.1875, 256, 256)
+    xy, m = dev(f.xy), dev(f.m)
+    src = dev(np.random.default_rng(3).uniform(-5, 5, (4, 2)))
+    kw = dict(grid=g, sources=src, gamma=0.15, tol=tol, max_iter=max_iter)
+    ref, rs = lf.find_images(xy, m, method="direct", **kw)
+    img, s = lf.find_images(xy, m, precision=precision, p=p, **kw)
+    ref, rs, img, s = (t.cpu().numpy() for t in (ref, rs, img, s))
+    ok = np.abs(ref[:, 2]) < 1e3
+    assert abs(len(img) - len(ref)) <= (0 if precision == "fp64" else 1 + len(ref) // 50)
+    for r, k in zip(ref[ok], rs[ok]):
+        d = np.hypot(img[s == k, 0] - r[0], img[s == k, 1] - r[1])
+        assert d.min(initial=np.inf) < 1e3 * (1e-9 if precision == "fp64" else tol)
