@@ -2182,7 +2182,7 @@ lens_status lens_map_ipm(lens_plan *plan, const lens_field *field, const lens_gr
         1, std::min<int64_t>({ny - 1, chunk / nx - 1, kIpmPassCellsMax / (nx - 1)}));
     Scratch sc(st);
     const int64_t npx = (int64_t)map->npix * map->npix;
-    const int64_t ndiff = (int64_t)map->npix * (map->npix + 1);
+    const int64_t ndiff = ipm_diff_len(map->npix);
     auto *acc = sc.get<unsigned long long>((size_t)npx);
     auto *diff = sc.get<unsigned long long>((size_t)ndiff);
     launch_ipm_zero(acc, npx, st);

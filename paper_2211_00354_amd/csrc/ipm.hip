@@ -24,9 +24,9 @@
 //     kPairMax pixels is apportioned pixel by pixel, its (cell, pixel) pairs
 //     shared out evenly over the workgroup; a wider cell (next to a star its
 //     image can stretch over much of the map) is queued;
-//   * k_ipm_wide, a wave per queued cell: its image (the quadrilateral, or a
-//     folded cell's two lobes) is rasterised edge by edge, so the work is
-//     proportional to its perimeter in pixels: an edge adds its Green term to
+//   * k_ipm_wide, a wave per 16 queued cells: their images (the quadrilateral,
+//     or a folded cell's two lobes) are rasterised edge by edge, so the work is
+//     proportional to their perimeters in pixels: an edge adds its Green term to
 //     the few pixels it crosses in each row and a constant to the row's
 //     pixels right of it through a row-difference accumulator that the final
 //     pass prefix-sums along the row.
@@ -38,8 +38,11 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr double kFix = 1099511627776.0;  // 2^40
-// widest bounding box (in pixels) apportioned by the per-cell pair path
-constexpr int32_t kPairMax = 64;
+// widest bounding box (in pixels) apportioned by the per-cell pair path: a pair
+// costs four edge terms, a rasterised cell its perimeter.  16384^2 rays at mu
+// = 50 into 2000^2 pixels, k_ipm + k_ipm_wide: 64 pixels 10.6 + 5.6 ms, 32
+// 9.2 + 6.6, 16 8.3 + 7.2, 4 6.9 + 11.3.
+constexpr int32_t kPairMax = 16;
 
 __device__ __forceinline__ double orient2(double ax, double ay, double bx, double by, double cx,
                                           double cy) {
@@ -248,7 +251,8 @@ struct IpmArgs {
   double cell_px, y1min, y2min, S;
   int32_t npix;
   unsigned long long *acc;   // [npix][npix]
-  unsigned long long *diff;  // [npix][npix + 1] row differences (full pixels)
+  unsigned long long *diff;  // row differences of wide cells, tiled (diff_index)
+  int64_t diff_cols;         // its tiles per row of tiles
   uint32_t *queue;           // wide cells: index (j - j0) (nx - 1) + i
   uint32_t *qcount;
 };
@@ -258,14 +262,15 @@ __device__ __forceinline__ bool load_quad(const IpmArgs &a, int64_t i, int64_t j
                                           double (&q)[4][2]) {
   const int64_t r0 = (j - a.ybase) * a.nx + i, r1 = r0 + a.nx;
   const int64_t id[4] = {r0, r0 + 1, r1 + 1, r1};
-  bool finite = true;
+  double z = 0.0;  // stays 0 unless a value is infinite or NaN
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     q[k][0] = (a.y[2 * id[k]] - a.y1min) * a.S;
     q[k][1] = (a.y[2 * id[k] + 1] - a.y2min) * a.S;
-    finite = finite && isfinite(q[k][0]) && isfinite(q[k][1]);
+    z = fma(q[k][0], 0.0, z);
+    z = fma(q[k][1], 0.0, z);
   }
-  return finite;
+  return z == 0.0;
 }
 
 // Pixel bounding box of q clamped to the map; false if it misses the map
@@ -294,29 +299,36 @@ __device__ __forceinline__ unsigned long long to_fix(double x) {
   return (unsigned long long)llrint(x * kFix);
 }
 
-// Workgroup-local sums of pixel contributions: an LDS hash table of pixels,
-// flushed to the map once per workgroup, so the many cells of a patch that
-// land in the same pixels (all of them, away from stars; those around a
-// star's caustic, near one) cost few global atomics.  Two probes, then the
-// global map: patches near a star touch more pixels than the table holds,
-// and long probe chains there (a wave waits for its slowest lane) cost more
-// than the atomics they save.
-constexpr int kTable = 1024;
+// Workgroup-local sums of pixel contributions: an LDS hash table of 64-byte
+// segments of the map (8 pixels), flushed to the map once per workgroup, so
+// the many cells of a patch that land in the same pixels (all of them, away
+// from stars; those around a star's caustic, near one) cost few global
+// atomics.  The chip takes 23.7e9 atomic requests a second whatever their
+// addresses or scope, but a request carries every lane of an instruction that
+// falls in one 64-byte segment (188e9 lane operations a second with 8 lanes
+// to a segment): a segment's pixels lie side by side in the table, so the
+// flush sends one request for all of them.  Two probes, then the global map:
+// patches near a star touch more pixels than the table holds, and long probe
+// chains there (a wave waits for its slowest lane) cost more than the atomics
+// they save.
+constexpr int kSegBits = 7, kSegs = 1 << kSegBits;
+constexpr int kTable = 8 * kSegs;
 constexpr int kPatch = 32;  // a workgroup takes kPatch x kPatch cells
 
-__device__ __forceinline__ void table_add(int32_t *tkey, unsigned long long *tval,
+__device__ __forceinline__ void table_add(int32_t *tseg, unsigned long long *tval,
                                           unsigned long long *__restrict__ acc, int32_t key,
                                           unsigned long long v) {
-  const uint32_t h = ((uint32_t)key * 2654435761u) >> 22;  // 10 bits
+  const int32_t seg = key >> 3;
+  const uint32_t h = ((uint32_t)seg * 2654435761u) >> (32 - kSegBits);
   for (int probe = 0; probe < 2; ++probe) {
-    const int slot = (int)((h + (uint32_t)probe) & (kTable - 1));
-    int32_t k = tkey[slot];
+    const int slot = (int)((h + (uint32_t)probe) & (kSegs - 1));
+    int32_t k = tseg[slot];
     if (k == -1) {
-      const int32_t old = atomicCAS(&tkey[slot], -1, key);
-      k = old == -1 ? key : old;
+      const int32_t old = atomicCAS(&tseg[slot], -1, seg);
+      k = old == -1 ? seg : old;
     }
-    if (k == key) {
-      atomicAdd(&tval[slot], v);
+    if (k == seg) {
+      atomicAdd(&tval[8 * slot + (key & 7)], v);
       return;
     }
   }
@@ -350,7 +362,7 @@ __device__ __forceinline__ int32_t block_excl_scan(int32_t x, int32_t *wsum, int
 // Four waves per SIMD (at most 128 VGPRs), as many as its LDS allows.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm(
     IpmArgs a) {
-  __shared__ int32_t tkey[kTable];
+  __shared__ int32_t tseg[kSegs];
   __shared__ unsigned long long tval[kTable];
   __shared__ double sq[kThreads][10];       // multi-pixel cells of the batch: corners, X,
   __shared__ double sinv[kThreads];         // 1 / area,
@@ -360,7 +372,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   __shared__ int32_t wsum[kThreads / 64];
   const int t = threadIdx.x;
   for (int e = t; e < kTable; e += kThreads) {
-    tkey[e] = -1;
+    if ((e & 7) == 0) tseg[e >> 3] = -1;
     tval[e] = 0ull;
   }
   __syncthreads();
@@ -375,52 +387,53 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const int64_t i = pi * kPatch + (k % kPatch), j = a.j0 + pj * kPatch + (k / kPatch);
     int32_t npairs = 0;
     Cell c;
-    if (i < ncx && j < a.j1 && load_quad(a, i, j, c.q)) {
+    int32_t u0, v0, u1, v1;
+    bool inside;
+    // up to two pixels take their shares at once (a cell in one pixel, or
+    // across one pixel edge)
+    unsigned long long s0 = 0ull, s1 = 0ull;
+    if (i < ncx && j < a.j1 && load_quad(a, i, j, c.q) &&
+        quad_bbox(c.q, npix, u0, v0, u1, v1, inside)) {
       classify(c);
-      int32_t u0, v0, u1, v1;
-      bool inside;
-      const bool hits = quad_bbox(c.q, npix, u0, v0, u1, v1, inside);
       const int64_t npx = (int64_t)(u1 - u0 + 1) * (v1 - v0 + 1);
       if (!(c.area > 0.0)) {
         // no shape: a quarter of the cell to each corner's pixel
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) {
           const int64_t pk = pixel_of(c.q[cc], npix);
-          if (pk >= 0) table_add(tkey, tval, a.acc, (int32_t)pk, q_quarter);
+          if (pk >= 0) table_add(tseg, tval, a.acc, (int32_t)pk, q_quarter);
         }
-      } else if (hits) {
-        if (u0 == u1 && v0 == v1 && inside) {
-          table_add(tkey, tval, a.acc, v0 * npix + u0, q_cell);  // wholly inside
-        } else if (npx == 2 && inside && c.kind == 0) {
-          // across one pixel edge: the first pixel's overlap by Green's
-          // theorem, the second takes the rest of the cell (in fixed point,
-          // so the cell's total is exact)
-          const double ov = split_area(c.q, u1 != u0, (double)(u0 + 1), (double)(v0 + 1));
-          const double f = fmin(fmax(ov / c.area, 0.0), 1.0);
-          const unsigned long long q0 = to_fix(a.cell_px * f);
-          const unsigned long long q1 = q_cell >= q0 ? q_cell - q0 : 0ull;
-          if (q0) table_add(tkey, tval, a.acc, v0 * npix + u0, q0);
-          if (q1) table_add(tkey, tval, a.acc, v1 * npix + u1, q1);
-        } else if (npx > kPairMax) {
-          const uint32_t slot = atomicAdd(a.qcount, 1u);
-          a.queue[slot] = (uint32_t)((j - a.j0) * ncx + i);
-        } else {
-          npairs = (int32_t)npx;
+      } else if (npx == 1 && inside) {
+        s0 = q_cell;  // wholly inside
+      } else if (npx == 2 && inside && c.kind == 0) {
+        // across one pixel edge: the first pixel's overlap by Green's
+        // theorem, the second takes the rest of the cell (in fixed point,
+        // so the cell's total is exact)
+        const double ov = split_area(c.q, u1 != u0, (double)(u0 + 1), (double)(v0 + 1));
+        const double f = fmin(fmax(ov / c.area, 0.0), 1.0);
+        s0 = to_fix(a.cell_px * f);
+        s1 = q_cell >= s0 ? q_cell - s0 : 0ull;
+      } else if (npx > kPairMax) {
+        const uint32_t slot = atomicAdd(a.qcount, 1u);
+        a.queue[slot] = (uint32_t)((j - a.j0) * ncx + i);
+      } else {
+        npairs = (int32_t)npx;
 #pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            sq[t][2 * cc] = c.q[cc][0];
-            sq[t][2 * cc + 1] = c.q[cc][1];
-          }
-          sq[t][8] = c.X[0];
-          sq[t][9] = c.X[1];
-          sinv[t] = 1.0 / c.area;
-          sshape[t] = c.kind | ((c.kind == 0 ? convex_orientation(c.q) + 1 : 1) << 2);
-          sbox[t][0] = u0;
-          sbox[t][1] = v0;
-          sbox[t][2] = u1 - u0 + 1;
+        for (int cc = 0; cc < 4; ++cc) {
+          sq[t][2 * cc] = c.q[cc][0];
+          sq[t][2 * cc + 1] = c.q[cc][1];
         }
+        sq[t][8] = c.X[0];
+        sq[t][9] = c.X[1];
+        sinv[t] = 1.0 / c.area;
+        sshape[t] = c.kind | ((c.kind == 0 ? convex_orientation(c.q) + 1 : 1) << 2);
+        sbox[t][0] = u0;
+        sbox[t][1] = v0;
+        sbox[t][2] = u1 - u0 + 1;
       }
     }
+    if (s0) table_add(tseg, tval, a.acc, v0 * npix + u0, s0);
+    if (s1) table_add(tseg, tval, a.acc, v1 * npix + u1, s1);
     int32_t total;
     const int32_t first = block_excl_scan(npairs, wsum, &total);
     sfirst[t] = first;
@@ -467,13 +480,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         const int32_t u = bu + local % bw, v = bv + local / bw;
         if (kind == 0 && o != 0 && convex_misses(cq, o, (double)u, (double)v)) continue;
         const double ov = cell_pixel_overlap(cq, X, kind, k, kinv, (double)u, (double)v);
-        if (ov > 0.0) table_add(tkey, tval, a.acc, v * npix + u, to_fix(a.cell_px * (ov * inv)));
+        if (ov > 0.0) table_add(tseg, tval, a.acc, v * npix + u, to_fix(a.cell_px * (ov * inv)));
       }
     }
     __syncthreads();  // the batch's shared cells are consumed
   }
-  for (int e = t; e < kTable; e += kThreads)
-    if (tkey[e] >= 0) atomicAdd(&a.acc[tkey[e]], tval[e]);
+  for (int e = t; e < kTable; e += kThreads) {
+    const unsigned long long v = tval[e];
+    if (v != 0ull) atomicAdd(&a.acc[(int64_t)tseg[e >> 3] * 8 + (e & 7)], v);
+  }
 }
 
 // Wide cells are apportioned edge by edge.  By Green's theorem the overlap
@@ -485,13 +500,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 // for the pixels the edge passes through.  Since the C_e of a closed polygon
 // sum to zero in every strip,
 //     sum_e T_e(u) = sum_e ( -C_e [u >= ulo_e] + P_e(u) [ulo_e <= u <= uhi_e] ),
-// with [ulo_e, uhi_e] the pixels the edge crosses in that row: each (edge,
-// row) adds -C_e to the row-difference accumulator at ulo_e (prefix-summed
-// along the row by the final pass) and P_e(u) = T_e(u) to the few pixels it
-// crosses.  C_e is formed in fixed point as G(y_end) - G(y_start) with
-// G(y) = fix((y - v) w), so the constants of a closed polygon cancel exactly
-// in integers and pixels outside it receive exactly nothing.  Work is
-// proportional to the image's perimeter in pixels, not its area.
+// with [ulo_e, uhi_e] the pixels the edge crosses in that row and P_e = T_e
+// there: each (edge, row) adds -C_e + P_e(ulo) at ulo_e, P_e(u) - P_e(u-1) at
+// the next pixels and -P_e(uhi) after the last to the row-difference
+// accumulator, which the final pass prefix-sums along the row.  C_e is formed
+// in fixed point as G(y_end) - G(y_start) with G(y) = fix((y - v) w), so the
+// constants of a closed polygon cancel exactly in integers and pixels outside
+// it receive exactly nothing.  Work is proportional to the image's perimeter
+// in pixels, not its area.
+//
+// The edge between two wide cells, neither of them folded, belongs to both:
+// it is rasterised once with both weights (each in its own fixed point), by
+// the cell left of it or below it.
 
 // An edge's part in the strip [v, v+1]: heights yb < yt, the x extent
 // [xl, xh] there and (signed) start/end heights in the edge's direction.
@@ -511,40 +531,72 @@ __device__ __forceinline__ bool edge_strip(double ax, double ay, double bx, doub
   return true;
 }
 
-// One polygon edge of a queued cell, with the items the wave's lanes take:
-// a steep edge (at least as many rows as columns in the map) one item per
-// row (its crossed pixels and its difference entry); a flat one an item per
-// column (the pixels it crosses there) plus an item per row (the difference
-// entry only).
+// One polygon edge a -> b: signed weight w0 of the cell it was taken from, w1
+// of the cell on its other side (0: none), whose polygon runs along it the
+// other way.
 struct EdgeJob {
-  double ax, ay, bx, by, k, kinv, w;
-  int32_t steep, r0, nr, c0, nc, first;
+  double ax, ay, bx, by, k, kinv, w0, w1;
+  int32_t r0, c0;
 };
-constexpr int kMaxEdges = 8;  // two triangles, or one quadrilateral
+constexpr int kBatch = 16;              // cells per wave and batch
+constexpr int kMaxJobs = 6 * kBatch;    // two triangles per folded cell
 
-__device__ __forceinline__ void row_item(const EdgeJob &e, int32_t v, bool pixels,
-                                         const IpmArgs &a) {
+// Both cells' fixed-point shares of a signed term t of the edge.
+__device__ __forceinline__ unsigned long long edge_fix(const EdgeJob &e, double t) {
+  return to_fix(t * e.w0) - to_fix(t * e.w1);
+}
+// ... and of the edge's height in row v, from ys to ye.
+__device__ __forceinline__ unsigned long long edge_const(const EdgeJob &e, double ys, double ye,
+                                                         double v) {
+  return edge_fix(e, ye - v) - edge_fix(e, ys - v);
+}
+
+// The row differences lie in 64-byte tiles of 4 rows by 2 columns: one atomic
+// request carries every lane of an instruction in one tile, in whatever lanes
+// they are, and a steep edge's rows lie above each other (a request per ~2
+// rows, where rows of 8 columns take one or two per row).
+__device__ __forceinline__ int64_t diff_index(int32_t v, int32_t u, int64_t cols) {
+  return (((int64_t)(v >> 2) * cols + (u >> 1)) << 3) + ((v & 3) << 1) + (u & 1);
+}
+
+// Row v of a steep edge (at least as many rows as columns in the map), by
+// four neighbouring lanes (sub = 0..3), an entry of the difference row each.
+__device__ __forceinline__ void row_item(const EdgeJob &e, int32_t v, int sub, const IpmArgs &a) {
   const int32_t npix = a.npix;
-  double xl, xh, ys, ye;
+  double xl = 0, xh = 0, ys = 0, ye = 0;
   if (!edge_strip(e.ax, e.ay, e.bx, e.by, e.k, (double)v, xl, xh, ys, ye)) return;
-  const double ulo = floor(xl), uhi = ceil(xh) - 1.0;
-  if (pixels) {
-    const double ua = fmax(ulo, 0.0), ub = fmin(uhi, (double)(npix - 1));
-    for (int32_t u = (int32_t)ua; (double)u <= ub; ++u) {
-      const double t = edge_term(e.ax - u, e.ay - v, e.bx - u, e.by - v, e.k, e.kinv);
-      if (t != 0.0) atomicAdd(&a.acc[(int64_t)v * npix + u], to_fix(t * e.w));
-    }
-  }
-  if (ulo < (double)npix) {
-    const unsigned long long c = to_fix((ye - v) * e.w) - to_fix((ys - v) * e.w);
-    if (c != 0ull) {
-      const int32_t d = ulo < 0.0 ? 0 : (int32_t)ulo;
-      atomicAdd(&a.diff[(int64_t)v * (npix + 1) + d], 0ull - c);
-    }
+  const double ulo = floor(xl);
+  if (!(ulo < (double)npix)) return;
+  const int32_t ua = ulo < 0.0 ? 0 : (int32_t)ulo;
+  const double uhi = fmin(ceil(xh) - 1.0, (double)(npix - 1));
+  const int32_t ub = uhi < (double)ua ? ua - 1 : (int32_t)uhi;
+  unsigned long long carry = 0ull;
+  for (int32_t u0 = ua; u0 <= ub + 1; u0 += 4) {  // the same for the four lanes
+    const int32_t u = u0 + sub;
+    unsigned long long P = 0ull;
+    if (u <= ub) P = edge_fix(e, edge_term(e.ax - u, e.ay - v, e.bx - u, e.by - v, e.k, e.kinv));
+    const unsigned long long left = __shfl_up(P, 1, 4);
+    unsigned long long d = P - (sub == 0 ? carry : left);
+    carry = __shfl(P, 3, 4);
+    if (u == ua) d -= edge_const(e, ys, ye, (double)v);
+    if (u <= ub + 1 && d != 0ull) atomicAdd(&a.diff[diff_index(v, u, a.diff_cols)], d);
   }
 }
 
-__device__ __forceinline__ void column_item(const EdgeJob &e, int32_t u, const IpmArgs &a) {
+// Row v of a flat edge: its constant only (its pixels are column_item's).
+__device__ __forceinline__ void flat_row_item(const EdgeJob &e, int32_t v, const IpmArgs &a) {
+  double xl, xh, ys, ye;
+  if (!edge_strip(e.ax, e.ay, e.bx, e.by, e.k, (double)v, xl, xh, ys, ye)) return;
+  const double ulo = floor(xl);
+  if (!(ulo < (double)a.npix)) return;
+  const unsigned long long c = edge_const(e, ys, ye, (double)v);
+  const int32_t d = ulo < 0.0 ? 0 : (int32_t)ulo;
+  if (c != 0ull) atomicAdd(&a.diff[diff_index(v, d, a.diff_cols)], 0ull - c);
+}
+
+// Column u of a flat edge (rows [r0, r0 + nr) of the map): the pixels it
+// crosses there.
+__device__ __forceinline__ void column_item(const EdgeJob &e, int32_t nr, int32_t u, const IpmArgs &a) {
   const int32_t npix = a.npix;
   const double ex0 = fmin(e.ax, e.bx), ex1 = fmax(e.ax, e.bx);
   const double x0 = fmax(ex0, (double)u), x1 = fmin(ex1, (double)u + 1.0);
@@ -554,46 +606,42 @@ __device__ __forceinline__ void column_item(const EdgeJob &e, int32_t u, const I
   // rows this column's part may touch, one row of margin either way; a row
   // takes the pixel only if its own strip test puts u among the crossed ones
   const double vlo = fmax(floor(fmin(y0, y1)) - 1.0, (double)e.r0);
-  const double vhi = fmin(ceil(fmax(y0, y1)), (double)(e.r0 + e.nr - 1));
+  const double vhi = fmin(ceil(fmax(y0, y1)), (double)(e.r0 + nr - 1));
   for (int32_t v = (int32_t)vlo; (double)v <= vhi; ++v) {
     double xl, xh, ys, ye;
     if (!edge_strip(e.ax, e.ay, e.bx, e.by, e.k, (double)v, xl, xh, ys, ye)) continue;
     if ((double)u < floor(xl) || (double)u > ceil(xh) - 1.0) continue;
-    const double t = edge_term(e.ax - u, e.ay - v, e.bx - u, e.by - v, e.k, e.kinv);
-    if (t != 0.0) atomicAdd(&a.acc[(int64_t)v * npix + u], to_fix(t * e.w));
+    const unsigned long long P = edge_fix(e, edge_term(e.ax - u, e.ay - v, e.bx - u, e.by - v, e.k, e.kinv));
+    if (P != 0ull) atomicAdd(&a.acc[(int64_t)v * npix + u], P);
   }
 }
 
-// Adds the edges of polygon P (n vertices) to the wave's job table.
-__device__ __forceinline__ void add_edges(const double (*P)[2], int n, double w, int32_t npix,
-                                          EdgeJob *jobs, int &ne, int32_t &items) {
-  // orientation: every edge term is signed by it, so the weight carries it
+// Twice the signed area of polygon P (n vertices): its edge terms carry the
+// orientation, so the weight does.
+template <int N>
+__device__ __forceinline__ double signed_weight(const double (&P)[N][2], double w) {
   double s = 0.0;
-  for (int e = 0; e < n; ++e) {
-    const int e1 = e + 1 == n ? 0 : e + 1;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const int e1 = e + 1 == N ? 0 : e + 1;
     s += (P[e][0] - P[0][0]) * (P[e1][1] - P[0][1]) - (P[e1][0] - P[0][0]) * (P[e][1] - P[0][1]);
   }
-  const double ws = s < 0.0 ? -w : w;
-  for (int e = 0; e < n; ++e) {
-    const int e1 = e + 1 == n ? 0 : e + 1;
-    const double ax = P[e][0], ay = P[e][1], bx = P[e1][0], by = P[e1][1];
-    if (ay == by) continue;  // horizontal: no term
-    const double ey0 = fmin(ay, by), ey1 = fmax(ay, by), ex0 = fmin(ax, bx), ex1 = fmax(ax, bx);
-    if (!(ey1 >= 0.0) || !(ey0 < (double)npix) || !(ex0 < (double)npix)) continue;
-    // an edge wholly left of the map (ex1 < 0) still shifts its rows
-    const double r0 = fmax(floor(ey0), 0.0), r1 = fmin(floor(ey1), (double)(npix - 1));
-    const double c0 = fmax(floor(ex0), 0.0), c1 = fmin(floor(ex1), (double)(npix - 1));
-    EdgeJob &j = jobs[ne++];
-    j.ax = ax, j.ay = ay, j.bx = bx, j.by = by, j.w = ws;
-    edge_slope(P[e], P[e1], j.k, j.kinv);
-    j.r0 = (int32_t)r0;
-    j.nr = (int32_t)(r1 - r0) + 1;
-    j.c0 = (int32_t)c0;
-    j.nc = c1 >= c0 ? (int32_t)(c1 - c0) + 1 : 0;
-    j.steep = j.nr >= j.nc;
-    j.first = items;
-    items += j.steep ? j.nr : j.nc + j.nr;
-  }
+  return s < 0.0 ? -w : w;
+}
+
+// The weight of an unfolded wide cell (as k_ipm queues them) of the pass, or
+// 0 for any other.
+__device__ __forceinline__ double wide_weight(const IpmArgs &a, int64_t i, int64_t j) {
+  if (i < 0 || i >= a.nx - 1 || j < a.j0 || j >= a.j1) return 0.0;
+  Cell c;
+  if (!load_quad(a, i, j, c.q)) return 0.0;
+  classify(c);
+  if (c.kind != 0 || !(c.area > 0.0)) return 0.0;
+  int32_t u0, v0, u1, v1;
+  bool inside;
+  if (!quad_bbox(c.q, a.npix, u0, v0, u1, v1, inside)) return 0.0;
+  if ((int64_t)(u1 - u0 + 1) * (v1 - v0 + 1) <= kPairMax) return 0.0;
+  return signed_weight(c.q, a.cell_px / c.area);
 }
 
 // Orders the LDS accesses of a converged wave (its lanes exchange data
@@ -604,99 +652,175 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// A wave per queued cell: its image (the quadrilateral, or a folded cell's
-// two lobes) becomes a table of edge jobs in LDS, and the wave's lanes take
-// the jobs' items in turn, so even a cell of a few rows keeps most lanes busy.
-// Waves pull cells in a fixed stride and exit past the queue's end.
-__global__ __launch_bounds__(kThreads) void k_ipm_wide(IpmArgs a) {
-  __shared__ EdgeJob jobs_all[kThreads / 64][kMaxEdges];
-  __shared__ int32_t counts_all[kThreads / 64][2];
+__device__ __forceinline__ int32_t wave_excl_scan(int32_t x, int lane, int32_t &total) {
+  int32_t inc = x;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int32_t y = __shfl_up(inc, d);
+    if (lane >= d) inc += y;
+  }
+  total = __shfl(inc, 63);
+  return inc - x;
+}
+
+// (The high-magnification map above: 5.6 ms for the cells beyond 64 pixels,
+// 18.1 with a wave per cell, an atomic per pixel and difference, and every
+// edge twice: it ran at the chip's 23.7e9 atomic requests a second.)
+//
+// Sixteen queued cells per wave and batch: four lanes of each classify it,
+// one edge to a lane (with the neighbour across it), and write the edges to be
+// rasterised -- the quadrilateral's, or a folded cell's two lobes' -- to a
+// table in LDS; the wave's lanes then take the table's items in turn: the rows
+// of steep edges, four lanes each, the columns of flat ones, and their rows.
+// Waves pull batches in a fixed stride and exit past the queue's end.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_wide(
+    IpmArgs a) {
+  __shared__ EdgeJob jobs_all[kThreads / 64][kMaxJobs];
+  // first item of each job, by kind: steep rows, flat columns, flat rows
+  __shared__ int32_t first_all[kThreads / 64][3][kMaxJobs + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   EdgeJob *jobs = jobs_all[wv];
+  int32_t(*first)[kMaxJobs + 1] = first_all[wv];
   const uint32_t nq = *a.qcount;
   const int64_t ncx = a.nx - 1;
   const uint32_t waves = gridDim.x * (kThreads / 64);
-  for (uint32_t q = blockIdx.x * (kThreads / 64) + wv; q < nq; q += waves) {
-    const uint32_t id = a.queue[q];
+  const int e = lane & 3, sub = lane & 3;
+  const uint64_t step = (uint64_t)waves * kBatch;
+  uint64_t base = (uint64_t)(blockIdx.x * (kThreads / 64) + wv) * kBatch;
+  for (; base < nq; base += step) {
+    const bool on = base + (lane >> 2) < nq;
+    const uint32_t id = a.queue[on ? base + (lane >> 2) : base];
     const int64_t i = (int64_t)(id % (uint64_t)ncx), j = a.j0 + (int64_t)(id / (uint64_t)ncx);
     Cell c;
     load_quad(a, i, j, c.q);  // finite: it was queued
     classify(c);
     const double w = a.cell_px / c.area;
-    wave_sync();  // the previous cell's items have read the table
-    if (lane == 0) {
-      // lane 0 writes the table to LDS; the others read it after the sync
-      int ne = 0;
-      int32_t items = 0;
-      if (c.kind == 0) {
-        add_edges(c.q, 4, w, a.npix, jobs, ne, items);
-      } else {
-        const int ia = c.kind == 1 ? 0 : 1;
-        double T[3][2];
-        T[0][0] = c.X[0], T[0][1] = c.X[1];
-        T[1][0] = c.q[ia + 1][0], T[1][1] = c.q[ia + 1][1];
-        T[2][0] = c.q[ia + 2][0], T[2][1] = c.q[ia + 2][1];
-        add_edges(T, 3, w, a.npix, jobs, ne, items);
-        T[0][0] = c.q[ia][0], T[0][1] = c.q[ia][1];
-        T[1][0] = c.X[0], T[1][1] = c.X[1];
-        T[2][0] = c.q[(ia + 3) & 3][0], T[2][1] = c.q[(ia + 3) & 3][1];
-        add_edges(T, 3, w, a.npix, jobs, ne, items);
+    // up to two edges of this lane: A (edge e of the quadrilateral, or of the
+    // first lobe), B (edge e of the second lobe)
+    double A[4], B[4], wa = 0.0, wa1 = 0.0, wb = 0.0;
+    auto pick = [](int k, const double (&p0)[2], const double (&p1)[2], const double (&p2)[2],
+                   const double (&p3)[2], double &x, double &y) {
+      x = k == 0 ? p0[0] : (k == 1 ? p1[0] : (k == 2 ? p2[0] : p3[0]));
+      y = k == 0 ? p0[1] : (k == 1 ? p1[1] : (k == 2 ? p2[1] : p3[1]));
+    };
+    B[0] = B[1] = B[2] = B[3] = 0.0;
+    bool has_a = on, has_b = false;
+    if (c.kind == 0) {
+      pick(e, c.q[0], c.q[1], c.q[2], c.q[3], A[0], A[1]);
+      pick((e + 1) & 3, c.q[0], c.q[1], c.q[2], c.q[3], A[2], A[3]);
+      wa = signed_weight(c.q, w);
+      // the cell across: below, right, above, left
+      wa1 = wide_weight(a, i + (e == 1) - (e == 3), j + (e == 2) - (e == 0));
+      if (wa1 != 0.0 && (e == 0 || e == 3)) has_a = false;  // the neighbour's
+    } else {
+      const bool k1 = c.kind == 1;
+      double T[3][2], U[3][2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        T[0][x] = c.X[x], T[1][x] = k1 ? c.q[1][x] : c.q[2][x], T[2][x] = k1 ? c.q[2][x] : c.q[3][x];
+        U[0][x] = k1 ? c.q[0][x] : c.q[1][x], U[1][x] = c.X[x], U[2][x] = k1 ? c.q[3][x] : c.q[0][x];
       }
-      counts_all[wv][0] = ne;
-      counts_all[wv][1] = items;
+      const int e1 = e == 2 ? 0 : e + 1;
+      pick(e, T[0], T[1], T[2], T[2], A[0], A[1]);
+      pick(e1, T[0], T[1], T[2], T[2], A[2], A[3]);
+      pick(e, U[0], U[1], U[2], U[2], B[0], B[1]);
+      pick(e1, U[0], U[1], U[2], U[2], B[2], B[3]);
+      wa = signed_weight(T, w);
+      wb = signed_weight(U, w);
+      has_a = has_b = on && e < 3;
     }
-    wave_sync();
-    const int ne = counts_all[wv][0];
-    const int32_t items = counts_all[wv][1];
-    for (int32_t t = lane; t < items; t += 64) {
-      int e = 0;
-      while (e + 1 < ne && jobs[e + 1].first <= t) ++e;
-      const EdgeJob &jb = jobs[e];
-      const int32_t r = t - jb.first;
-      if (jb.steep) {
-        row_item(jb, jb.r0 + r, true, a);
-      } else if (r < jb.nc) {
-        column_item(jb, jb.c0 + r, a);
-      } else {
-        row_item(jb, jb.r0 + (r - jb.nc), false, a);
+    wave_sync();  // the previous batch's items have read the table
+    int njobs = 0;
+    int32_t totals[3] = {0, 0, 0};
+    auto emit = [&](bool has, const double (&E)[4], double w0, double w1) {
+      const double ax = E[0], ay = E[1], bx = E[2], by = E[3], top = (double)a.npix;
+      const double ey0 = fmin(ay, by), ey1 = fmax(ay, by), ex0 = fmin(ax, bx), ex1 = fmax(ax, bx);
+      // horizontal edges have no term; an edge wholly left of the map
+      // (ex1 < 0) still shifts its rows
+      has = has && ay != by && ey1 >= 0.0 && ey0 < top && ex0 < top;
+      const int32_t r0 = (int32_t)fmin(fmax(floor(ey0), 0.0), top - 1.0);
+      const int32_t r1 = (int32_t)fmax(fmin(floor(ey1), top - 1.0), 0.0);
+      const int32_t c0 = (int32_t)fmin(fmax(floor(ex0), 0.0), top - 1.0);
+      const int32_t c1 = (int32_t)fmax(fmin(floor(ex1), top - 1.0), -1.0);
+      const int32_t nr = r1 - r0 + 1, nc = c1 >= c0 ? c1 - c0 + 1 : 0;
+      const bool steep = nr >= nc;
+      const uint64_t m = __ballot(has);
+      const int slot = njobs + __popcll(m & ((1ull << lane) - 1));
+      const int32_t n[3] = {has && steep ? nr : 0, has && !steep ? nc : 0, has && !steep ? nr : 0};
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        int32_t tot;
+        const int32_t f = totals[q] + wave_excl_scan(n[q], lane, tot);
+        if (has) first[q][slot] = f;
+        totals[q] += tot;
       }
+      if (has) {
+        EdgeJob &jb = jobs[slot];
+        jb.ax = ax, jb.ay = ay, jb.bx = bx, jb.by = by, jb.w0 = w0, jb.w1 = w1;
+        const double pa[2] = {ax, ay}, pb[2] = {bx, by};
+        edge_slope(pa, pb, jb.k, jb.kinv);
+        jb.r0 = r0;
+        jb.c0 = c0;
+      }
+      njobs += __popcll(m);
+    };
+    emit(has_a, A, wa, wa1);
+    if (__any(has_b)) emit(has_b, B, wb, 0.0);
+    if (lane < 3) first[lane][njobs] = lane == 0 ? totals[0] : (lane == 1 ? totals[1] : totals[2]);
+    wave_sync();
+    // a lane's items grow, so its job is found by walking on
+    int jb = 0;
+    for (int32_t t = lane >> 2; t < totals[0]; t += 16) {
+      while (first[0][jb + 1] <= t) ++jb;
+      row_item(jobs[jb], jobs[jb].r0 + (t - first[0][jb]), sub, a);
+    }
+    jb = 0;
+    for (int32_t t = lane; t < totals[1]; t += 64) {
+      while (first[1][jb + 1] <= t) ++jb;
+      column_item(jobs[jb], first[2][jb + 1] - first[2][jb], jobs[jb].c0 + (t - first[1][jb]), a);
+    }
+    jb = 0;
+    for (int32_t t = lane; t < totals[2]; t += 64) {
+      while (first[2][jb + 1] <= t) ++jb;
+      flat_row_item(jobs[jb], jobs[jb].r0 + (t - first[2][jb]), a);
     }
   }
 }
 
-// mu[v][u] += (acc[v][u] + sum_{u' <= u} diff[v][u']) 2^-40: a workgroup per
-// map row, the row's differences prefix-summed 256 at a time (integers, so
-// the result does not depend on the order).
+// mu[v][u] += (acc[v][u] + sum_{u' <= u} diff[v][u']) 2^-40: a wave per map
+// row, four to a workgroup (a row of tiles), the row's differences
+// prefix-summed 256 at a time, four to a lane (integers, so the result does
+// not depend on the order).
 __global__ __launch_bounds__(kThreads) void k_ipm_finish(const unsigned long long *__restrict__ acc,
                                                          const unsigned long long *__restrict__ diff,
-                                                         int32_t npix, double *__restrict__ mu) {
-  __shared__ unsigned long long wsum[kThreads / 64];
-  const int64_t v = blockIdx.x;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const unsigned long long *drow = diff + v * (int64_t)(npix + 1);
+                                                         int64_t cols, int32_t npix,
+                                                         double *__restrict__ mu) {
+  const int32_t v = (int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (v >= npix) return;
   unsigned long long carry = 0;
-  for (int32_t base = 0; base < npix; base += kThreads) {
-    const int32_t u = base + (int32_t)threadIdx.x;
-    unsigned long long x = u < npix ? drow[u] : 0ull;
+  for (int64_t base = 0; base < npix; base += 256) {
+    const int64_t u0 = base + 4 * lane;
+    unsigned long long x[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      sum += u0 + q < npix ? diff[diff_index(v, (int32_t)(u0 + q), cols)] : 0ull;
+      x[q] = sum;
+    }
+    unsigned long long inc = sum;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-      const unsigned long long y = __shfl_up(x, d);
-      if (lane >= d) x += y;
+      const unsigned long long y = __shfl_up(inc, d);
+      if (lane >= d) inc += y;
     }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    unsigned long long off = carry, tot = carry;
+    const unsigned long long off = carry + inc - sum;
 #pragma unroll
-    for (int q = 0; q < kThreads / 64; ++q) {
-      if (q < w) off += wsum[q];
-      tot += wsum[q];
-    }
-    if (u < npix) {
-      const int64_t idx = v * npix + u;
-      mu[idx] += (double)(long long)(acc[idx] + off + x) * (1.0 / kFix);
-    }
-    carry = tot;
-    __syncthreads();
+    for (int q = 0; q < 4; ++q)
+      if (u0 + q < npix) {
+        const int64_t idx = (int64_t)v * npix + u0 + q;
+        mu[idx] += (double)(long long)(acc[idx] + off + x[q]) * (1.0 / kFix);
+      }
+    carry += __shfl(inc, 63);
   }
 }
 
@@ -711,10 +835,15 @@ unsigned grid_for(int64_t n) {
   return (unsigned)(b < 1 ? 1 : (b > 65536 ? 65536 : b));
 }
 
+// columns of 4 x 2 tiles of the difference rows (npix + 1 entries each)
+int64_t diff_tile_cols(int32_t npix) { return ((int64_t)npix + 2) / 2; }
+
 // workgroups of the wide-cell kernel
-constexpr unsigned kWideBlocks = 1536;  // six waves per SIMD (its register limit)
+constexpr unsigned kWideBlocks = 1024;  // four waves per SIMD (its register limit)
 
 }  // namespace
+
+int64_t ipm_diff_len(int32_t npix) { return ((int64_t)npix + 3) / 4 * diff_tile_cols(npix) * 8; }
 
 void launch_ipm_zero(unsigned long long *acc, int64_t n, hipStream_t stream) {
   hipLaunchKernelGGL(k_zero_u64, dim3(grid_for(n)), dim3(kThreads), 0, stream, acc, n);
@@ -728,7 +857,7 @@ void launch_ipm_cells(const IpmPass &p, hipStream_t stream) {
   if (patches > 0x7fffffff) fail(LENS_EUNSUPPORTED, "IPM pass too large");
   if (ncx * nrows > (int64_t)0xffffffffu) fail(LENS_EUNSUPPORTED, "IPM pass too large");
   IpmArgs a{p.y, p.nx, p.ybase, p.j0, p.j1, p.cell_px, p.y1min, p.y2min, p.S, p.npix,
-            p.acc, p.diff, p.queue, p.qcount};
+            p.acc, p.diff, diff_tile_cols(p.npix), p.queue, p.qcount};
   launch_fill_u32(p.qcount, 1, 0u, stream);
   hipLaunchKernelGGL(k_ipm, dim3((unsigned)patches), dim3(kThreads), 0, stream, a);
   LENS_HIP(hipGetLastError());
@@ -738,8 +867,8 @@ void launch_ipm_cells(const IpmPass &p, hipStream_t stream) {
 
 void launch_ipm_finish(const unsigned long long *acc, const unsigned long long *diff, int32_t npix,
                        double *mu, hipStream_t stream) {
-  hipLaunchKernelGGL(k_ipm_finish, dim3((unsigned)npix), dim3(kThreads), 0, stream, acc, diff, npix,
-                     mu);
+  hipLaunchKernelGGL(k_ipm_finish, dim3((unsigned)((npix + 3) / 4)), dim3(kThreads), 0, stream, acc,
+                     diff, diff_tile_cols(npix), npix, mu);
   LENS_HIP(hipGetLastError());
 }
 

@@ -316,9 +316,8 @@ struct DirectArgs {
 void launch_direct(const DirectArgs &a, hipStream_t stream);
 
 // Inverse polygon mapping (ipm.hip).  acc is an npix^2 fixed-point
-// accumulator (units of 2^-40 of a pixel's magnification) and diff an
-// npix x (npix + 1) one of row differences (pixels a wide cell covers
-// completely); launch_ipm_finish adds acc plus the row prefix sums of diff to
+// accumulator (units of 2^-40 of a pixel's magnification) and diff one of
+// row differences (wide cells), ipm_diff_len(npix) long; launch_ipm_finish adds acc plus the row prefix sums of diff to
 // the FP64 map mu.  y holds grid rows [ybase, ...) with nx rays per row;
 // cells of rows [j0, j1) are mapped.  queue needs (nx - 1) (j1 - j0) entries.
 struct IpmPass {
@@ -392,6 +391,7 @@ struct MultiPlaneArgs {
 };
 void launch_mp_positions(const MultiPlaneArgs &a, hipStream_t stream);
 void launch_mp_alpha(const double *x, const double *y, double *alpha, int64_t n, hipStream_t stream);
+int64_t ipm_diff_len(int32_t npix);
 void launch_ipm_zero(unsigned long long *acc, int64_t n, hipStream_t stream);
 void launch_ipm_cells(const IpmPass &p, hipStream_t stream);
 void launch_ipm_finish(const unsigned long long *acc, const unsigned long long *diff, int32_t npix,

@@ -88,3 +88,24 @@ def test_newton_iterations_match_direct(lf, max_iter, precision, p, tol):
     for r, k in zip(ref[ok], rs[ok]):
         d = np.hypot(img[s == k, 0] - r[0], img[s == k, 1] - r[1])
         assert d.min(initial=np.inf) < 1e3 * (1e-9 if precision == "fp64" else tol)
+
+
+@pytest.mark.parametrize("npix", [1, 2, 3, 5, 8, 101, 258])
+def test_ipm_map_edges_of_tiles(lf, npix):
+    # the row differences of wide cells lie in 4 x 2 tiles and k_ipm's sums in
+    # segments of 8 pixels: maps that end inside them.  Same corners as the
+    # oracle's; contributions round to 2^-40 of a pixel's magnification, a
+    # pixel takes at most a few thousand of them.
+    import oracle
+    f, g, _ = wl.small_disk()
+    side = 0.02 * npix if npix > 8 else 0.4  # cells of 1 to ~1000 pixels' images
+    md = lf.MapDesc(-0.5 * side, -0.4 * side, side, npix)
+    grid = lf.Grid(g.x0, g.y0, g.dx, g.dy, g.nx, g.ny)
+    kw = dict(grid=grid, kappa_s=f.kappa_s, gamma=f.gamma, method="direct")
+    xy, m = dev(f.xy), dev(f.m)
+    mu = lf.ipm_map(xy, m, map=md, **kw).cpu().numpy()
+    y = lf.deflect(xy, m, **kw).cpu().numpy()
+    ref = oracle.ipm(y.reshape(g.ny, g.nx, 2), g.dx * g.dy, md.y1min, md.y2min, md.side, npix)
+    assert np.abs(mu - ref).max() <= 1e-9 * max(1.0, ref.max())
+    again = lf.ipm_map(xy, m, map=md, max_rays_per_chunk=41 * g.nx, **kw).cpu().numpy()
+    np.testing.assert_array_equal(mu, again)
