@@ -109,3 +109,30 @@ def test_ipm_map_edges_of_tiles(lf, npix):
     assert np.abs(mu - ref).max() <= 1e-9 * max(1.0, ref.max())
     again = lf.ipm_map(xy, m, map=md, max_rays_per_chunk=41 * g.nx, **kw).cpu().numpy()
     np.testing.assert_array_equal(mu, again)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 17, 1001])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (63, 1), (65, 3), (725, 724), (1024, 513)])
+def test_direct_sum_forms(lf, n, nx, ny):
+    # the stars shared out over a workgroup's waves (up to 524288 rays) and
+    # whole (725 * 724 = 524900, 1024 * 513), counts that leave slices empty;
+    # against the oracle on a sample.  Each pair carries a few FP64 roundings
+    # of its own size, so the error is bounded by the sum of the pairs' sizes.
+    import oracle
+    f = wl.random_field(n, 10.0, seed=60 + n, masses="powerlaw", kappa_s=0.1, gamma=0.2)
+    g = lf.Grid(-6.0, -6.0, 12.0 / nx, 12.0 / ny, nx, ny)
+    y, d = lf.deflect(dev(f.xy), dev(f.m), grid=g, kappa_s=0.1, gamma=0.2, method="direct", want_dfdz=True)
+    y1 = lf.deflect(dev(f.xy), dev(f.m), grid=g, kappa_s=0.1, gamma=0.2, method="direct")
+    assert torch.equal(y, y1)
+    w = wl.Grid(g.x0, g.y0, g.dx, g.dy, nx, ny)
+    idx = np.unique(np.linspace(0, nx * ny - 1, 64).astype(np.int64))
+    rays = w.rays(idx)
+    yo, _, _ = oracle.deflect(f.xy, f.m, rays, 0.1, 0.2)
+    z = rays[:, :1] + 1j * rays[:, 1:] - (f.xy[:, 0] + 1j * f.xy[:, 1])[None, :]
+    size = (f.m / np.abs(z)).sum(1) + 12.0
+    got = y.cpu().numpy()[idx]
+    assert (np.abs(got - yo).max(1) <= 16 * np.finfo(float).eps * size).all()
+    fp = -(f.m / z ** 2).sum(1)
+    size2 = (f.m / np.abs(z) ** 2).sum(1)
+    dz = d.cpu().numpy()[idx]
+    assert (np.abs(dz[:, 0] + 1j * dz[:, 1] - fp) <= 32 * np.finfo(float).eps * size2).all()
