@@ -52,7 +52,7 @@ struct lens_plan {
   DevBuf sm32;               // FP32 copies of real masses (mixed-precision near field)
   std::vector<DevBuf> mp;    // index = level, FP64 multipoles
   std::vector<DevBuf> mp32;  // index = level, FP32 copies (fine levels, mixed)
-  DevBuf keys, vals, keys_tmp, vals_tmp, cnt, scan_tmp, box_coarse;  // tree-build scratch
+  DevBuf keys, vals, keys_tmp, vals_tmp, cnt, box_coarse, rec;  // tree-build scratch
   hipStream_t last_stream = nullptr;
 
   const double *mp_at(int l) const { return static_cast<const double *>(mp[l].ptr); }
@@ -62,7 +62,7 @@ struct lens_plan {
   // return every buffer to the pool, ordered after the work on `st`
   void put_all(hipStream_t st) {
     std::vector<DevBuf *> ps = {&sxy, &sm, &sm32, &leaf_start, &keys, &vals, &keys_tmp, &vals_tmp,
-                                &cnt, &scan_tmp, &box_coarse};
+                                &cnt, &box_coarse, &rec};
     for (auto &b : mp) ps.push_back(&b);
     for (auto &b : mp32) ps.push_back(&b);
     pool_put_batch(ps.data(), ps.size(), st);
@@ -449,9 +449,8 @@ void plan_alloc(lens_plan *P, hipStream_t st) {
   if (P->qdim == 1) P->sm32 = pool_get((size_t)N * 4, st);
   for (DevBuf *b : {&P->keys, &P->vals, &P->keys_tmp, &P->vals_tmp})
     *b = pool_get((size_t)N * sizeof(uint32_t), st);
-  const size_t ncnt = radix_counts_len(N);
-  P->cnt = pool_get(ncnt * sizeof(uint32_t), st);
-  P->scan_tmp = pool_get(scan_tmp_len(ncnt) * sizeof(uint32_t), st);
+  P->cnt = pool_get(radix_counts_len(N) * sizeof(uint32_t), st);
+  if (tree_rec_len(N)) P->rec = pool_get(tree_rec_len(N) * sizeof(double), st);
   P->box_coarse = pool_get((size_t)box_starts_coarse_len(nbox) * sizeof(int32_t), st);
   for (int l = 2; l <= L; ++l) {
     const size_t n = (size_t)P->swin[l].count() * P->p * 2;
@@ -467,22 +466,27 @@ void plan_alloc(lens_plan *P, hipStream_t st) {
 void plan_upward(lens_plan *P, hipStream_t st);
 
 void plan_tree(lens_plan *P, const double *xy, const double *q, hipStream_t st) {
-  const int L = P->g.L;
-  const int64_t nbox = int64_t(1) << (2 * L);
-  const int64_t N = P->n_stars;
   StageTimer tm("tree", st);
-  auto *k = static_cast<uint32_t *>(P->keys.ptr), *v = static_cast<uint32_t *>(P->vals.ptr);
-  auto *kt = static_cast<uint32_t *>(P->keys_tmp.ptr), *vt = static_cast<uint32_t *>(P->vals_tmp.ptr);
-  launch_leaf_keys(xy, N, P->g, k, v, nullptr, st);
-  const bool in_tmp = radix_sort_pairs(k, v, kt, vt, N, 2 * L, static_cast<uint32_t *>(P->cnt.ptr),
-                                       static_cast<uint32_t *>(P->scan_tmp.ptr), st);
-  const uint32_t *ks = in_tmp ? kt : k, *vs = in_tmp ? vt : v;
-  P->perm = vs;
-  launch_gather_stars(vs, xy, q, P->qdim, N, static_cast<double *>(P->sxy.ptr),
-                      static_cast<double *>(P->sm.ptr), static_cast<float *>(P->sm32.ptr), st);
-  // all zero when N = 0
-  launch_box_starts(ks, N, nbox, static_cast<int32_t *>(P->leaf_start.ptr),
-                    static_cast<int32_t *>(P->box_coarse.ptr), st);
+  auto u32 = [](const DevBuf &b) { return static_cast<uint32_t *>(b.ptr); };
+  TreeSort t{};
+  t.xy = xy;
+  t.n = P->n_stars;
+  t.g = P->g;
+  t.nbox = int64_t(1) << (2 * P->g.L);
+  t.q = q;
+  t.qdim = P->qdim;
+  t.sxy = static_cast<double *>(P->sxy.ptr);
+  t.sq = static_cast<double *>(P->sm.ptr);
+  t.sq32 = static_cast<float *>(P->sm32.ptr);
+  t.start = static_cast<int32_t *>(P->leaf_start.ptr);
+  t.coarse = static_cast<int32_t *>(P->box_coarse.ptr);
+  t.k = u32(P->keys);
+  t.v = u32(P->vals);
+  t.k_tmp = u32(P->keys_tmp);
+  t.v_tmp = u32(P->vals_tmp);
+  t.cnt = u32(P->cnt);
+  t.rec = static_cast<double *>(P->rec.ptr);
+  P->perm = launch_tree_sort(t, st);
 }
 
 void plan_enqueue(lens_plan *P, const double *xy, const double *q, hipStream_t st) {
@@ -875,30 +879,39 @@ ExplicitLocals explicit_locals(lens_plan &P, const double bb[4], Scratch &sc, hi
   return e;
 }
 
+// The sort of n points by their boxes of the window wl, its buffers from sc
+// (charges to be added by the caller).
+TreeSort window_sort(const double *xy, int64_t n, const Geometry &g, const Window &wl, Scratch &sc) {
+  TreeSort t{};
+  t.xy = xy;
+  t.n = n;
+  t.g = g;
+  t.win = wl;
+  t.windowed = true;
+  t.nbox = wl.count();
+  t.k = sc.get<uint32_t>(n);
+  t.v = sc.get<uint32_t>(n);
+  t.k_tmp = sc.get<uint32_t>(n);
+  t.v_tmp = sc.get<uint32_t>(n);
+  t.cnt = sc.get<uint32_t>(radix_counts_len(n));
+  t.sxy = sc.get<double>((size_t)n * 2);
+  t.start = sc.get<int32_t>(wl.count() + 1);
+  t.coarse = sc.get<int32_t>(box_starts_coarse_len(wl.count()));
+  return t;
+}
+
 void fmm_explicit_eval(lens_plan &P, const ExplicitLocals &e, const double *rays, int64_t n,
                        double c1, double c2, double *y_out, hipStream_t st, double *dfdz = nullptr) {
   Scratch sc(st);
   const Window wl = e.wl;
-  uint32_t *k = sc.get<uint32_t>(n), *v = sc.get<uint32_t>(n);
-  uint32_t *kt = sc.get<uint32_t>(n), *vt = sc.get<uint32_t>(n);
-  const size_t ncnt = radix_counts_len(n);
-  uint32_t *cnt = sc.get<uint32_t>(ncnt);
-  uint32_t *stmp = sc.get<uint32_t>(scan_tmp_len(ncnt));
-  launch_ray_keys(rays, n, P.g, wl, k, v, st);
-  int bits = 1;
-  while ((int64_t(1) << bits) < wl.count()) ++bits;
-  const bool in_tmp = radix_sort_pairs(k, v, kt, vt, n, bits, cnt, stmp, st);
-  const uint32_t *ks = in_tmp ? kt : k, *vs = in_tmp ? vt : v;
-  double *srays = sc.get<double>((size_t)n * 2);
-  launch_gather_rays(vs, rays, n, srays, st);
-  int32_t *rstart = sc.get<int32_t>(wl.count() + 1);
-  launch_box_starts(ks, n, wl.count(), rstart, sc.get<int32_t>(box_starts_coarse_len(wl.count())), st);
+  TreeSort t = window_sort(rays, n, P.g, wl, sc);
+  const uint32_t *vs = launch_tree_sort(t, st);
   EvalArgs ea{};
   fill_star_side(P, wl, e.loc, ea);
   ea.grid_mode = 0;
-  ea.rxy = srays;
+  ea.rxy = t.sxy;
   ea.rperm = vs;
-  ea.ray_start = rstart;
+  ea.ray_start = t.start;
   ea.c1 = c1;
   ea.c2 = c2;
   ea.y_out = y_out;
@@ -1514,7 +1527,7 @@ std::unique_ptr<BatchExec> batch_build(int n, const lens_field *f, const lens_gr
   while ((size_t(1) << fbits) < jobs.size()) ++fbits;
   const bool multi = jobs.size() >= 2 && shift + fbits <= 32 &&
                      total < (int64_t)std::numeric_limits<int32_t>::max();
-  uint32_t *mk = nullptr, *mv = nullptr, *mkt = nullptr, *mvt = nullptr, *mcnt = nullptr, *mscan = nullptr;
+  uint32_t *mk = nullptr, *mv = nullptr, *mkt = nullptr, *mvt = nullptr, *mcnt = nullptr;
   TreeJob *jobs_dev = nullptr;
   if (multi) {
     auto grab = [&](size_t bytes) {
@@ -1526,9 +1539,7 @@ std::unique_ptr<BatchExec> batch_build(int n, const lens_field *f, const lens_gr
     mv = static_cast<uint32_t *>(grab((size_t)total * 4));
     mkt = static_cast<uint32_t *>(grab((size_t)total * 4));
     mvt = static_cast<uint32_t *>(grab((size_t)total * 4));
-    const size_t ncnt = radix_counts_len(total);
-    mcnt = static_cast<uint32_t *>(grab(ncnt * 4));
-    mscan = static_cast<uint32_t *>(grab(scan_tmp_len(ncnt) * 4));
+    mcnt = static_cast<uint32_t *>(grab(radix_counts_len(total) * 4));
     LENS_HIP(hipMemcpyAsync(jobs_dev, jobs.data(), jobs.size() * sizeof(TreeJob), hipMemcpyHostToDevice, st));
   }
   LENS_HIP(hipStreamCreateWithFlags(&B->origin, hipStreamNonBlocking));
@@ -1548,8 +1559,8 @@ std::unique_ptr<BatchExec> batch_build(int n, const lens_field *f, const lens_gr
   try {
     const uint32_t *msk = nullptr, *msv = nullptr;
     if (multi) {
-      launch_leaf_keys_multi(jobs_dev, (int)jobs.size(), total, shift, mk, mv, B->origin);
-      const bool in_tmp = radix_sort_pairs(mk, mv, mkt, mvt, total, shift + fbits, mcnt, mscan, B->origin);
+      const bool in_tmp = launch_sort_multi(jobs_dev, (int)jobs.size(), total, shift, shift + fbits, mk, mv,
+                                            mkt, mvt, mcnt, B->origin);
       uint32_t *ks = in_tmp ? mkt : mk;
       msv = in_tmp ? mvt : mv;
       launch_gather_multi(jobs_dev, (int)jobs.size(), total, (uint32_t)((uint64_t(1) << shift) - 1), ks,
@@ -1585,7 +1596,6 @@ std::unique_ptr<BatchExec> batch_build(int n, const lens_field *f, const lens_gr
       if (multi) {
         // the field's segment of the combined sort: its leaf starts, then P2M / M2M
         const TreeJob &t = jobs[job++];
-        P->perm = msv + t.off;
         launch_box_starts(msk + t.off, t.n, int64_t(1) << (2 * P->g.L),
                           static_cast<int32_t *>(P->leaf_start.ptr),
                           static_cast<int32_t *>(P->box_coarse.ptr), s);
@@ -2427,24 +2437,14 @@ lens_status lens_deflect_backward(lens_plan *plan, const lens_field *field, cons
     try {
       double *loc = nullptr;
       const Window wl = downward(*P, tb, sc, st, &loc);
-      uint32_t *k = sc.get<uint32_t>(N), *v = sc.get<uint32_t>(N);
-      uint32_t *kt = sc.get<uint32_t>(N), *vt = sc.get<uint32_t>(N);
-      const size_t ncnt = radix_counts_len(N);
-      uint32_t *cnt = sc.get<uint32_t>(ncnt);
-      uint32_t *stmp = sc.get<uint32_t>(scan_tmp_len(ncnt));
-      double *txy = sc.get<double>((size_t)N * 2), *tm = sc.get<double>((size_t)N);
-      int32_t *tstart = sc.get<int32_t>(wl.count() + 1);
+      TreeSort t = window_sort(field->xy, N, P->g, wl, sc);
+      t.q = field->m;
+      t.qdim = 1;
+      t.sq = sc.get<double>((size_t)N);
+      const uint32_t *v;
       {
         StageTimer tmr("adjoint_targets", st);
-        launch_ray_keys(field->xy, N, P->g, wl, k, v, st);
-        int bits = 1;
-        while ((int64_t(1) << bits) < wl.count()) ++bits;
-        const bool in_tmp = radix_sort_pairs(k, v, kt, vt, N, bits, cnt, stmp, st);
-        const uint32_t *ks = in_tmp ? kt : k;
-        v = in_tmp ? vt : v;
-        launch_gather_stars(v, field->xy, field->m, 1, N, txy, tm, nullptr, st);
-        launch_box_starts(ks, N, wl.count(), tstart,
-                          sc.get<int32_t>(box_starts_coarse_len(wl.count())), st);
+        v = launch_tree_sort(t, st);
       }
       EvalArgs ea{};
       fill_star_side(*P, wl, loc, ea);
@@ -2453,7 +2453,7 @@ lens_status lens_deflect_backward(lens_plan *plan, const lens_field *field, cons
           std::max<int64_t>(1, (per + adj_targets_per_unit() - 1) / adj_targets_per_unit());
       while (wl.count() * ea.chunks_per_box > (int64_t)0x7fffffff && ea.chunks_per_box > 1)
         ea.chunks_per_box = (ea.chunks_per_box + 1) / 2;
-      AdjArgs d{static_cast<const double *>(P->sm.ptr), txy, tm, v, tstart, grad_xy, grad_m};
+      AdjArgs d{static_cast<const double *>(P->sm.ptr), t.sxy, t.sq, v, t.start, grad_xy, grad_m};
       StageTimer tme("eval_adjoint", st);
       launch_eval_adj(ea, d, P->precision, st);
     } catch (...) {

@@ -440,22 +440,6 @@ __global__ __launch_bounds__(kThreads) void k_grid_ranges(GridAxis ax, GridAxis 
   a.out[c] = (int32_t)lo;
 }
 
-__global__ __launch_bounds__(kThreads) void k_ray_keys(const double *__restrict__ rxy, int64_t n,
-                                                       Geometry g, Window win,
-                                                       uint32_t *__restrict__ keys,
-                                                       uint32_t *__restrict__ vals) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  const int64_t nL = int64_t(1) << g.L;
-  const double s = ldexp(g.side, -g.L);
-  int64_t ix = box_coord(rxy[2 * i], g.x0, s, nL) - win.bx0;
-  int64_t iy = box_coord(rxy[2 * i + 1], g.y0, s, nL) - win.by0;
-  ix = ix < 0 ? 0 : (ix >= win.nbx ? win.nbx - 1 : ix);
-  iy = iy < 0 ? 0 : (iy >= win.nby ? win.nby - 1 : iy);
-  keys[i] = (uint32_t)(iy * win.nbx + ix);
-  vals[i] = (uint32_t)i;
-}
-
 constexpr int64_t kMaxEvalBlocks = 256 * 32 * 4;  // CUs x waves per CU x sweeps in flight
 
 template <int PM, bool MIXED, bool MAP, bool GRID, int R, bool DERIV = false>
@@ -567,14 +551,6 @@ void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j
   const int64_t nmax = std::max(win.nbx, win.nby) + 1;
   hipLaunchKernelGGL(k_grid_ranges, dim3((unsigned)((nmax + kThreads - 1) / kThreads), 2),
                      dim3(kThreads), 0, stream, ax, ay, s, nL);
-  LENS_HIP(hipGetLastError());
-}
-
-void launch_ray_keys(const double *rxy, int64_t n, Geometry g, Window win, uint32_t *keys,
-                     uint32_t *vals, hipStream_t stream) {
-  if (n == 0) return;
-  hipLaunchKernelGGL(k_ray_keys, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     stream, rxy, n, g, win, keys, vals);
   LENS_HIP(hipGetLastError());
 }
 

@@ -96,26 +96,34 @@ struct BBoxSet {
 // out[s][4] = bounding box of set s (sets_dev: device array of nsets sets)
 void launch_bbox_multi(const BBoxSet *sets_dev, int nsets, int nparts, double *partial,
                        double *out, hipStream_t stream);
-void launch_leaf_keys(const double *xy, int64_t n, Geometry g, uint32_t *keys, uint32_t *vals,
-                      uint32_t *box_count, hipStream_t stream);
 // p[0..n) = v (a kernel, so it may be captured in a graph)
 void launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream);
-// Stable LSD radix sort of (key, value) pairs on the low `bits` bits of key.
-// Uses (k_tmp, v_tmp) as ping-pong storage; returns true if the sorted result
-// ended up in the tmp buffers.
-bool radix_sort_pairs(uint32_t *k, uint32_t *v, uint32_t *k_tmp, uint32_t *v_tmp, int64_t n,
-                      int bits, uint32_t *counts, uint32_t *scan_tmp, hipStream_t stream);
+// Points sorted by box (a stable sort, so equal keys keep their order): keys
+// are the leaf boxes of the whole level, or with `windowed` the boxes of win,
+// points outside clamped to it.  Writes the sorted positions sxy [n][2], with
+// q the charges sq [n][qdim] (qdim 1: real masses, and with sq32 their FP32
+// copies; 2: complex), and start[b] = first sorted point of box b, b in
+// [0, nbox].  Returns the permutation (sorted position -> point), in v or
+// v_tmp.  k, v, k_tmp, v_tmp: n entries; cnt: radix_counts_len(n); coarse:
+// box_starts_coarse_len(nbox); rec: tree_rec_len(n) (with q; may be nullptr).
+struct TreeSort {
+  const double *xy;
+  int64_t n;
+  Geometry g;
+  Window win;
+  bool windowed;
+  int64_t nbox;
+  const double *q;
+  int qdim;
+  double *sxy, *sq;
+  float *sq32;
+  int32_t *start, *coarse;
+  uint32_t *k, *v, *k_tmp, *v_tmp, *cnt;
+  double *rec;
+};
+size_t tree_rec_len(int64_t n);
+const uint32_t *launch_tree_sort(const TreeSort &a, hipStream_t stream);
 size_t radix_counts_len(int64_t n);
-size_t scan_tmp_len(size_t n);
-void exclusive_scan_u32(const uint32_t *in, uint32_t *out, size_t n, uint32_t *tmp,
-                        hipStream_t stream);
-// sources (stars, or rays with complex charges) sorted by leaf box:
-// positions [n][2] and charges [n][qdim] (qdim 1: real masses; 2: complex);
-// with sq32 (qdim 1), also the masses rounded to FP32
-void launch_gather_stars(const uint32_t *perm, const double *xy, const double *q, int qdim,
-                         int64_t n, double *sxy, double *sq, float *sq32, hipStream_t stream);
-void launch_gather_rays(const uint32_t *perm, const double *xy, int64_t n, double *sxy,
-                        hipStream_t stream);
 // start[b] = first sorted index with key >= b, for b in [0, nbox]
 void launch_box_starts(const uint32_t *sorted_keys, int64_t n, int64_t nbox, int32_t *start,
                        int32_t *coarse, hipStream_t stream);
@@ -161,9 +169,12 @@ struct TreeJob {
   Geometry g;
   int64_t off, n;
 };
-// keys (j << shift) | leaf key, values the field-local index
-void launch_leaf_keys_multi(const TreeJob *jobs, int njobs, int64_t total, int shift, uint32_t *keys,
-                            uint32_t *vals, hipStream_t stream);
+// stable sort of every field's sources by (j << shift) | leaf key (bits bits),
+// values their indices in the combined arrays; true: the result is in the tmp
+// buffers
+bool launch_sort_multi(const TreeJob *jobs, int njobs, int64_t total, int shift, int bits, uint32_t *k,
+                       uint32_t *v, uint32_t *k_tmp, uint32_t *v_tmp, uint32_t *counts,
+                       hipStream_t stream);
 // after the sort: gather each field's sources, keys &= mask (leaf keys)
 void launch_gather_multi(const TreeJob *jobs, int njobs, int64_t total, uint32_t mask, uint32_t *keys,
                          const uint32_t *perm, hipStream_t stream);
@@ -276,8 +287,6 @@ void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j
                         int64_t j_end, int32_t *col_start, int32_t *row_start, hipStream_t stream);
 void eval_shape(int64_t max_rays, int *R, int64_t *CH);
 void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles);
-void launch_ray_keys(const double *rxy, int64_t n, Geometry g, Window win, uint32_t *keys,
-                     uint32_t *vals, hipStream_t stream);
 
 // Adjoint (adjoint.hip): gradients at stars from rays with complex charges
 struct AdjArgs {

@@ -136,3 +136,30 @@ def test_direct_sum_forms(lf, n, nx, ny):
     size2 = (f.m / np.abs(z) ** 2).sum(1)
     dz = d.cpu().numpy()[idx]
     assert (np.abs(dz[:, 0] + 1j * dz[:, 1] - fp) <= 32 * np.finfo(float).eps * size2).all()
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 1023, 1025, 8192, 8193, 20000, 524287, 524288, 2200000])
+@pytest.mark.parametrize("leaf", [2, 7, 8])
+def test_tree_sort_forms(lf, n, leaf):
+    # one workgroup (up to 8192 points in 16384 boxes), radix passes over 2048-
+    # and 4096-point tiles, packed records from 2^19 points: the sorted stars
+    # give each box its multipole, so rays far outside every box's near field
+    # see the field of all of them, and a plan's backward pass returns gradients
+    # in the caller's order.
+    rng = np.random.default_rng(n + leaf)
+    xy = rng.uniform(-8, 8, (n, 2))
+    m = rng.uniform(0.5, 1.5, n)
+    xy[: min(n, 3)] = xy[0]  # equal keys
+    rays = dev(np.array([[9.0, 0.25], [-0.75, 10.0], [0.3, 0.2], [-7.9, 7.7]]))
+    box = (-10.0, -10.0, 10.0, 10.0)
+    X, M = dev(xy), dev(m)
+    plan = lf.Plan(X, M, ray_box=box, precision="fp64", p=40, leaf_level=leaf)
+    y = lf.deflect(rays=rays, plan=plan)
+    ref = lf.deflect(X, M, rays=rays, method="direct")
+    assert float((y - ref).norm() / (ref - rays).norm()) < 1e-9
+    g = dev(rng.standard_normal((4, 2)))
+    gx, gm = lf.deflect_backward(None, None, g, rays=rays, plan=plan)
+    rx, rm = lf.deflect_backward(X, M, g, rays=rays, method="direct")
+    plan.close()
+    assert float((gx - rx).norm() / rx.norm()) < 1e-8
+    assert float((gm - rm).norm() / rm.norm()) < 1e-8
