@@ -16,6 +16,8 @@
 // complex charges, then at the stars the local expansion and its derivative
 // (Horner) plus the near field over the rays of the 3x3 leaf neighbourhood.
 // A ray exactly on a star is skipped, as in the forward map.
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace lensfmm {
@@ -25,6 +27,7 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kThreads = 256;
 constexpr int32_t kFlushSources = 128;  // LENS_MIXED near-field partials per FP64 flush
+constexpr int64_t kHeldLanes = 1 << 19;  // lanes of k_eval_adj the chip holds at once, about
 
 // One source (position, complex charge) against the R targets of a lane:
 // h += q/d, hp -= q/d^2 with d = z_target - z_source.  A coincident pair has
@@ -53,114 +56,114 @@ __device__ __forceinline__ void adj_pair(const double (&tx)[R], const double (&t
   }
 }
 
-template <int PMAX, bool MIXED, int R>
-__global__ __launch_bounds__(kWave) void k_eval_adj(
-    EvalArgs a, const double *__restrict__ loc, const double *__restrict__ sxy,
+// h and h' at the targets, SPLIT lanes to a target and neighbouring targets
+// (sorted by leaf box) in neighbouring lanes, each lane with its own box's
+// sources: clustered lenses leave most boxes a few targets, so a wave to a box
+// had most of its lanes idle (2e5 clustered stars, 1e6 rays: 318 us, now 80).
+// What is left is the loads' latency, so a lane keeps four sources in flight
+// behind the four that it works on (one instead: 94 us).  A lane
+// walks the three contiguous source ranges of its 3x3 neighbourhood, in groups
+// of kFlushSources sources; with SPLIT > 1 the lanes of a target take its groups
+// in turn.  LENS_MIXED sums a group in FP32 and the groups in FP64, so a
+// neighbourhood of thousands of rays does not accumulate thousands of FP32
+// roundings.
+template <bool MIXED, int SPLIT>
+__global__ __launch_bounds__(kThreads) void k_eval_adj(
+    EvalArgs a, int64_t nt, const double *__restrict__ loc, const double *__restrict__ sxy,
     const double *__restrict__ sq, const int32_t *__restrict__ leaf_start,
     const double *__restrict__ txy, const double *__restrict__ tm, const uint32_t *__restrict__ tperm,
-    const int32_t *__restrict__ tstart, int32_t tglobal, double *__restrict__ grad_xy,
-    double *__restrict__ grad_m) {
-  const int lane = threadIdx.x;
-  const uint32_t CH = (uint32_t)a.chunks_per_box;
-  const uint32_t nbx = (uint32_t)a.win.nbx;
-  const uint32_t nunits = (uint32_t)(a.win.count() * CH);
+    double *__restrict__ grad_xy, double *__restrict__ grad_m) {
+  using acc_t = typename std::conditional<MIXED, float, double>::type;
+  const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int part = (int)(gid % SPLIT);
+  const bool act = gid / SPLIT < nt;
+  const int64_t t = act ? gid / SPLIT : nt - 1;
   const int64_t nL = int64_t(1) << a.g.L;
   const double s = ldexp(a.g.side, -a.g.L);
   const double inv_s = 1.0 / s;
   const int p = a.p;
-  constexpr int RPC = kWave * R;
-  using acc_t = typename std::conditional<MIXED, float, double>::type;
-
-  for (uint32_t u = blockIdx.x; u < nunits; u += gridDim.x) {
-    const uint32_t b = u / CH, c0 = u - b * CH;
-    const uint32_t byw = b / nbx, bxw = b - byw * nbx;
-    const int64_t gx = a.win.bx0 + bxw, gy = a.win.by0 + byw;
-    // target starts per window box, or (tglobal) per box of the whole leaf
-    // level, row-major (a forward plan's leaf starts)
-    const int64_t tb = tglobal ? gy * nL + gx : (int64_t)b;
-    const int32_t t0 = tstart[tb], nt = tstart[tb + 1] - t0;
-    if (nt == 0 || (int64_t)c0 * RPC >= nt) continue;  // uniform
-
-    int32_t rs[3], re[3];
+  const double tx[1] = {txy[2 * t]}, ty[1] = {txy[2 * t + 1]};
+  // the target's box, in the window (as the targets' sort places them)
+  int64_t ix = box_coord(tx[0], a.g.x0, s, nL) - a.win.bx0;
+  int64_t iy = box_coord(ty[0], a.g.y0, s, nL) - a.win.by0;
+  ix = ix < 0 ? 0 : (ix >= a.win.nbx ? a.win.nbx - 1 : ix);
+  iy = iy < 0 ? 0 : (iy >= a.win.nby ? a.win.nby - 1 : iy);
+  const int64_t gx = a.win.bx0 + ix, gy = a.win.by0 + iy;
+  // source ranges of the three rows, and their running totals
+  int32_t rs[3], pre[4];
+  pre[0] = 0;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int64_t row = gy - 1 + d;
-      rs[d] = 0;
-      re[d] = 0;
-      if (row >= 0 && row < nL) {
-        const int64_t cx0 = gx > 0 ? gx - 1 : 0;
-        const int64_t cx1 = gx + 1 < nL ? gx + 1 : nL - 1;
-        rs[d] = leaf_start[row * nL + cx0];
-        re[d] = leaf_start[row * nL + cx1 + 1];
-      }
+  for (int d = 0; d < 3; ++d) {
+    const int64_t row = gy - 1 + d;
+    rs[d] = 0;
+    int32_t re = 0;
+    if (act && row >= 0 && row < nL) {
+      rs[d] = leaf_start[row * nL + (gx > 0 ? gx - 1 : 0)];
+      re = leaf_start[row * nL + (gx + 1 < nL ? gx + 1 : nL - 1) + 1];
     }
-    const double cx = a.g.x0 + ((double)gx + 0.5) * s;
-    const double cy = a.g.y0 + ((double)gy + 0.5) * s;
-
-    for (int32_t base = (int32_t)c0 * RPC; base < nt; base += (int32_t)CH * RPC) {
-      double tx[R], ty[R];
-      acc_t hr[R], hi[R], pr[R], pi[R];
-      bool act[R];
-      int32_t id[R];
+    pre[d + 1] = pre[d] + (re - rs[d]);
+  }
+  const int32_t n = pre[3];
+  const double2 *sz = reinterpret_cast<const double2 *>(sxy), *sg = reinterpret_cast<const double2 *>(sq);
+  double Sr = 0.0, Si = 0.0, Tr = 0.0, Ti = 0.0;
+  acc_t hr[1] = {0}, hi[1] = {0}, pr[1] = {0}, pi[1] = {0};
+  for (int32_t g = part; (int64_t)g * kFlushSources < n; g += SPLIT) {
+    int32_t k = g * kFlushSources;
+    const int32_t end = min(n, k + kFlushSources);
+    // the next four sources' loads are issued before the current four pairs
+    double2 nz[4], nq[4];
+    auto fetch = [&](int32_t q0) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int32_t idx = base + r * kWave + lane;
-        act[r] = idx < nt;
-        id[r] = t0 + (act[r] ? idx : 0);
-        tx[r] = txy[2 * (int64_t)id[r]];
-        ty[r] = txy[2 * (int64_t)id[r] + 1];
-        hr[r] = hi[r] = pr[r] = pi[r] = 0;
+      for (int j = 0; j < 4; ++j) {
+        const int32_t q = min(q0 + j, end - 1);
+        const int32_t i = q >= pre[2] ? rs[2] + (q - pre[2]) : (q >= pre[1] ? rs[1] + (q - pre[1]) : rs[0] + q);
+        nz[j] = sz[i];
+        nq[j] = sg[i];
       }
-      // LENS_MIXED: the FP32 partial sums move into FP64 ones every
-      // kFlushSources sources, so a neighbourhood of thousands of rays does
-      // not accumulate thousands of FP32 roundings
-      double Sr[R], Si[R], Tr[R], Ti[R];
+    };
+    fetch(k);
+    for (; k < end; k += 4) {
+      double2 z[4], q[4];
 #pragma unroll
-      for (int r = 0; r < R; ++r) Sr[r] = Si[r] = Tr[r] = Ti[r] = 0.0;
-      int32_t since = 0;
+      for (int j = 0; j < 4; ++j) z[j] = nz[j], q[j] = nq[j];
+      fetch(k + 4);
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        for (int32_t i = rs[d]; i < re[d]; ++i) {
-          adj_pair<MIXED, R>(tx, ty, sxy[2 * (int64_t)i], sxy[2 * (int64_t)i + 1],
-                             sq[2 * (int64_t)i], sq[2 * (int64_t)i + 1], hr, hi, pr, pi);
-          if (MIXED && ++since == kFlushSources) {
-            since = 0;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-              Sr[r] += (double)hr[r];
-              Si[r] += (double)hi[r];
-              Tr[r] += (double)pr[r];
-              Ti[r] += (double)pi[r];
-              hr[r] = hi[r] = pr[r] = pi[r] = 0;
-            }
-          }
-        }
-
-      const double *lb = loc + 2 * (int64_t)b * p;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        // far field: h = sum b_l w^l and dh/dw by one Horner recurrence
-        const cplx w = {(tx[r] - cx) * inv_s, (ty[r] - cy) * inv_s};
-        cplx f = {0.0, 0.0}, df = {0.0, 0.0};
-#pragma unroll
-        for (int l = PMAX - 1; l >= 0; --l)
-          if (l < p) {
-            df = cmad(df, w, f);
-            f = cmad(f, w, cplx{lb[2 * l], lb[2 * l + 1]});
-          }
-        const double Hr = f.re + (Sr[r] + (double)hr[r]), Hi = f.im + (Si[r] + (double)hi[r]);
-        const double Pr = df.re * inv_s + (Tr[r] + (double)pr[r]);
-        const double Pi = df.im * inv_s + (Ti[r] + (double)pi[r]);
-        (void)Hi;
-        if (!act[r]) continue;
-        const uint32_t o = tperm[id[r]];
-        const double m = tm[id[r]];
-        grad_m[o] = Hr;
-        grad_xy[2 * (int64_t)o] = m * Pr;
-        grad_xy[2 * (int64_t)o + 1] = -(m * Pi);
-      }
+      for (int j = 0; j < 4; ++j)
+        if (k + j < end) adj_pair<MIXED, 1>(tx, ty, z[j].x, z[j].y, q[j].x, q[j].y, hr, hi, pr, pi);
+    }
+    if (MIXED) {
+      Sr += (double)hr[0];
+      Si += (double)hi[0];
+      Tr += (double)pr[0];
+      Ti += (double)pi[0];
+      hr[0] = hi[0] = pr[0] = pi[0] = 0;
     }
   }
+  if (!MIXED) Sr = hr[0], Si = hi[0], Tr = pr[0], Ti = pi[0];
+#pragma unroll
+  for (int d = SPLIT / 2; d >= 1; d >>= 1) {
+    Sr += __shfl_xor(Sr, d);
+    Tr += __shfl_xor(Tr, d);
+    Ti += __shfl_xor(Ti, d);
+  }
+  (void)Si;  // Im h enters no gradient
+  // far field: h = sum b_l w^l and dh/dw by one Horner recurrence
+  const double2 *lb = reinterpret_cast<const double2 *>(loc) + (iy * a.win.nbx + ix) * p;
+  const cplx w = {(tx[0] - (a.g.x0 + ((double)gx + 0.5) * s)) * inv_s,
+                  (ty[0] - (a.g.y0 + ((double)gy + 0.5) * s)) * inv_s};
+  cplx f = {0.0, 0.0}, df = {0.0, 0.0};
+#pragma unroll 4
+  for (int l = p - 1; l >= 0; --l) {
+    const double2 b = lb[l];
+    df = cmad(df, w, f);
+    f = cmad(f, w, cplx{b.x, b.y});
+  }
+  if (!act || part != 0) return;
+  const uint32_t o = tperm[t];
+  const double m = tm[t];
+  grad_m[o] = f.re + Sr;
+  grad_xy[2 * (int64_t)o] = m * (df.re * inv_s + Tr);
+  grad_xy[2 * (int64_t)o + 1] = -(m * (df.im * inv_s + Ti));
 }
 
 // Direct FP64 gradient: every star against every ray, rays streamed through
@@ -218,26 +221,38 @@ __global__ __launch_bounds__(kThreads) void k_grid_rays(lens_grid g, double *__r
   out[2 * k + 1] = grid_coord(g.y0, g.dy, k / g.nx);
 }
 
-template <int PM, bool MIXED>
+template <bool MIXED, int SPLIT>
 void adj_launch(const EvalArgs &a, const AdjArgs &d, hipStream_t stream) {
-  constexpr int R = 1;
-  const int64_t units = a.win.count() * a.chunks_per_box;
-  const int64_t nblk = units < 65536 ? units : 65536;
-  hipLaunchKernelGGL((k_eval_adj<PM, MIXED, R>), dim3((unsigned)nblk), dim3(kWave), 0, stream, a,
-                     a.loc, a.sxy, d.sq, a.leaf_start, d.txy, d.tm, d.tperm, d.tstart,
-                     (int32_t)d.tglobal, d.grad_xy, d.grad_m);
+  const int64_t blocks = (d.nt * SPLIT + kThreads - 1) / kThreads;
+  hipLaunchKernelGGL((k_eval_adj<MIXED, SPLIT>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a,
+                     d.nt, a.loc, a.sxy, d.sq, a.leaf_start, d.txy, d.tm, d.tperm, d.grad_xy, d.grad_m);
+}
+
+template <bool MIXED>
+void adj_dispatch(const EvalArgs &a, const AdjArgs &d, hipStream_t stream) {
+  // Lanes to a target: more where each still finds whole groups of the mean
+  // neighbourhood's sources, or where the chip holds all lanes at once and an
+  // uneven distribution's longest chain is all that counts.  Whole backward
+  // pass, mixed: 1e5 stars on 1e6 rays within a tenth of their radius 6.7 ms
+  // with one lane, 1.1 with sixteen (a wave to a box: 4.3); half of the rays
+  // within 1/60 of it 47 and 14 ms with four; even rays pay 259 against 286 us.
+  const double groups = 9.0 * d.per_box / kFlushSources;
+  if (groups >= 16.0 || d.nt <= kHeldLanes / 16)
+    adj_launch<MIXED, 16>(a, d, stream);
+  else if (groups >= 4.0 || d.nt <= kHeldLanes / 4)
+    adj_launch<MIXED, 4>(a, d, stream);
+  else
+    adj_launch<MIXED, 1>(a, d, stream);
 }
 
 }  // namespace
 
-int64_t adj_targets_per_unit() { return kWave; }
-
 void launch_eval_adj(const EvalArgs &a, const AdjArgs &d, int precision, hipStream_t stream) {
-  if (a.win.count() == 0) return;
+  if (a.win.count() == 0 || d.nt == 0) return;
   if (precision == LENS_MIXED)
-    LENS_PMAX_DISPATCH(a.p, (adj_launch<PM, true>(a, d, stream)));
+    adj_dispatch<true>(a, d, stream);
   else
-    LENS_PMAX_DISPATCH(a.p, (adj_launch<PM, false>(a, d, stream)));
+    adj_dispatch<false>(a, d, stream);
   LENS_HIP(hipGetLastError());
 }
 

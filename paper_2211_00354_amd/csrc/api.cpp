@@ -803,7 +803,6 @@ void gridexec_alloc(const lens_plan &P, const lens_grid &grid, int64_t j0, int64
                         : pool_get((size_t)(wl.nby + 1) * sizeof(int32_t), st);
   EvalArgs &ea = ge.ea;
   fill_star_side(P, wl, ge.ls.at(P.g.L), ea);
-  ea.grid_mode = 1;
   ea.grid = grid;
   ea.col_start = static_cast<int32_t *>(ge.col_start.ptr);
   ea.row_start = static_cast<int32_t *>(ge.row_start.ptr);
@@ -895,8 +894,6 @@ TreeSort window_sort(const double *xy, int64_t n, const Geometry &g, const Windo
   t.v_tmp = sc.get<uint32_t>(n);
   t.cnt = sc.get<uint32_t>(radix_counts_len(n));
   t.sxy = sc.get<double>((size_t)n * 2);
-  t.start = sc.get<int32_t>(wl.count() + 1);
-  t.coarse = sc.get<int32_t>(box_starts_coarse_len(wl.count()));
   return t;
 }
 
@@ -908,18 +905,15 @@ void fmm_explicit_eval(lens_plan &P, const ExplicitLocals &e, const double *rays
   const uint32_t *vs = launch_tree_sort(t, st);
   EvalArgs ea{};
   fill_star_side(P, wl, e.loc, ea);
-  ea.grid_mode = 0;
   ea.rxy = t.sxy;
   ea.rperm = vs;
-  ea.ray_start = t.start;
   ea.c1 = c1;
   ea.c2 = c2;
   ea.y_out = y_out;
   ea.dfdz_out = dfdz;
-  // explicit rays: shape for the mean box occupancy; fuller boxes loop
-  const int64_t per = (n + wl.count() - 1) / std::max<int64_t>(wl.count(), 1);
-  eval_shape(std::max<int64_t>(per, 1), &ea.rays_per_lane, &ea.chunks_per_box);
-  launch_eval_checked(ea, P.precision, st);
+  if (wl.count() > (int64_t)0x7fffffff) fail(LENS_EUNSUPPORTED, "leaf window too large");
+  StageTimer tm("eval", st);
+  launch_eval_rays(ea, n, P.precision, st);
   P.last_stream = st;
 }
 
@@ -2252,6 +2246,13 @@ lens_status lens_map_ipm(lens_plan *plan, const lens_field *field, const lens_gr
 
 namespace {
 
+// Rays per leaf box over the rays' bounding box rb.
+double rays_per_box(const lens_plan &P, const double rb[4], int64_t n_rays) {
+  const double s = std::ldexp(P.g.side, -P.g.L);
+  const double boxes = std::max((rb[2] - rb[0]) / s, 1.0) * std::max((rb[3] - rb[1]) / s, 1.0);
+  return (double)n_rays / boxes;
+}
+
 // Adjoint FMM with a forward plan: the rays (charges g_k) are sources in a
 // tree of the plan's geometry, the plan's sorted stars are the targets (its
 // leaf starts locate each box's stars, its permutation the caller's order).
@@ -2280,14 +2281,9 @@ void backward_with_plan(lens_plan &F, const double *rays, int64_t n_rays, const 
     const Window wl = downward(*A, F.star_bb, sc, st, &loc);
     EvalArgs ea{};
     fill_star_side(*A, wl, loc, ea);
-    const int64_t per = (F.n_stars + wl.count() - 1) / std::max<int64_t>(wl.count(), 1);
-    ea.chunks_per_box =
-        std::max<int64_t>(1, (per + adj_targets_per_unit() - 1) / adj_targets_per_unit());
-    while (wl.count() * ea.chunks_per_box > (int64_t)0x7fffffff && ea.chunks_per_box > 1)
-      ea.chunks_per_box = (ea.chunks_per_box + 1) / 2;
-    AdjArgs d{static_cast<const double *>(A->sm.ptr), static_cast<const double *>(F.sxy.ptr),
-              static_cast<const double *>(F.sm.ptr), F.perm,
-              static_cast<const int32_t *>(F.leaf_start.ptr), grad_xy, grad_m, true};
+    const AdjArgs d{static_cast<const double *>(A->sm.ptr), F.n_stars,
+                    static_cast<const double *>(F.sxy.ptr), static_cast<const double *>(F.sm.ptr), F.perm,
+                    rays_per_box(*A, rb, n_rays), grad_xy, grad_m};
     StageTimer tme("eval_adjoint", st);
     launch_eval_adj(ea, d, A->precision, st);
   } catch (...) {
@@ -2448,12 +2444,8 @@ lens_status lens_deflect_backward(lens_plan *plan, const lens_field *field, cons
       }
       EvalArgs ea{};
       fill_star_side(*P, wl, loc, ea);
-      const int64_t per = (N + wl.count() - 1) / std::max<int64_t>(wl.count(), 1);
-      ea.chunks_per_box =
-          std::max<int64_t>(1, (per + adj_targets_per_unit() - 1) / adj_targets_per_unit());
-      while (wl.count() * ea.chunks_per_box > (int64_t)0x7fffffff && ea.chunks_per_box > 1)
-        ea.chunks_per_box = (ea.chunks_per_box + 1) / 2;
-      AdjArgs d{static_cast<const double *>(P->sm.ptr), t.sxy, t.sq, v, t.start, grad_xy, grad_m};
+      const AdjArgs d{static_cast<const double *>(P->sm.ptr), N, t.sxy, t.sq, v,
+                      rays_per_box(*P, P->star_bb, n_rays), grad_xy, grad_m};
       StageTimer tme("eval_adjoint", st);
       launch_eval_adj(ea, d, P->precision, st);
     } catch (...) {

@@ -2,7 +2,7 @@
 // field (Section 2.4, step 3) and, for maps, inverse-ray-shooting binning
 // (Section 2.3).
 //
-// Work unit = one chunk of up to 64*R rays of one leaf box of the target
+// Grid rays: work unit = one chunk of up to 64*R rays of one leaf box of the target
 // window, handled by one wave (a 64-thread workgroup):
 //   * the stars of the box's 3x3 neighbourhood (three contiguous row ranges
 //     of the sorted star array) and the box's local expansion are the same
@@ -128,7 +128,7 @@ __device__ __forceinline__ void map_table_flush(int32_t *hkey, uint32_t *hval,
 // The mixed kernels are compiled for five waves per SIMD (at most 96 VGPRs;
 // the R = 4 instances spill a few bytes of per-lane scratch outside the pair
 // loop), which measured faster than four waves without spills.
-template <int PMAX, bool MIXED, bool MAP, bool GRID, int R, bool DERIV>
+template <int PMAX, bool MIXED, bool MAP, int R, bool DERIV>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && !DERIV ? 5 : 1))) void k_eval(EvalArgs a, const double *__restrict__ loc,
                                                 const double *__restrict__ sxy,
                                                 const double *__restrict__ sm,
@@ -136,9 +136,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
                                                 const int32_t *__restrict__ leaf_start,
                                                 const int32_t *__restrict__ col_start,
                                                 const int32_t *__restrict__ row_start,
-                                                const double *__restrict__ rxy,
-                                                const uint32_t *__restrict__ rperm,
-                                                const int32_t *__restrict__ ray_start,
                                                 double *__restrict__ y_out,
                                                 int32_t *__restrict__ counts) {
   // the box's local expansion, read by every lane (LDS broadcast)
@@ -168,8 +165,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
   const double s = ldexp(a.g.side, -a.g.L);
   const double inv_s = 1.0 / s;
   const int p = a.p;
-  constexpr int RPC = kWave * R;
-  // grid rays: a wave's R slots are R tiles of TX x TY rays (TX * TY = 64)
+  // a wave's R slots are R tiles of TX x TY rays (TX * TY = 64)
   const int tsh = a.tile_shift;
   const int TX = 1 << tsh, TY = kWave >> tsh;
   const int lx = lane & (TX - 1), ly = lane >> tsh;
@@ -180,24 +176,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
     const uint32_t byw = b / nbx, bxw = b - byw * nbx;
     const int64_t gx = a.win.bx0 + bxw, gy = a.win.by0 + byw;
 
-    // grid: the box's rays are columns [i0, i0+W) x rows [j0, j0+H), cut into
-    // nt = TW x TH tiles, tpc consecutive tiles per unit; explicit: rays
-    // [r0, r0+nr) of the sorted array in chunks of RPC
-    int32_t nr = 0, r0 = 0, i0 = 0, j0 = 0, W = 0, H = 0, TW = 1, nt = 0, tpc = 0;
-    if (GRID) {
-      i0 = col_start[bxw];
-      W = col_start[bxw + 1] - i0;
-      j0 = row_start[byw];
-      H = row_start[byw + 1] - j0;
-      TW = (W + TX - 1) >> tsh;
-      nt = TW * ((H + TY - 1) / TY);
-      tpc = (nt + (int32_t)CH - 1) / (int32_t)CH;
-      if (nt == 0 || (int64_t)c0 * tpc >= nt) continue;  // uniform
-    } else {
-      r0 = ray_start[b];
-      nr = ray_start[b + 1] - r0;
-      if (nr == 0 || (int64_t)c0 * RPC >= nr) continue;  // uniform
-    }
+    // the box's rays are columns [i0, i0+W) x rows [j0, j0+H), cut into
+    // nt = TW x TH tiles, tpc consecutive tiles per unit
+    const int32_t i0 = col_start[bxw], W = col_start[bxw + 1] - i0;
+    const int32_t j0 = row_start[byw], H = row_start[byw + 1] - j0;
+    const int32_t TW = (W + TX - 1) >> tsh;
+    const int32_t nt = TW * ((H + TY - 1) / TY);
+    const int32_t tpc = (nt + (int32_t)CH - 1) / (int32_t)CH;
+    if (nt == 0 || (int64_t)c0 * tpc >= nt) continue;  // uniform
 
     int32_t rs[3], re[3];
 #pragma unroll
@@ -218,19 +204,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
     if (lane < p) lds_loc[lane] = reinterpret_cast<const double2 *>(loc + 2 * (int64_t)b * p)[lane];
     __syncthreads();
 
-    // passes of R tiles (grid) or RPC rays (explicit); explicit rays beyond
-    // CH chunks are looped over by the box's units
-    int32_t pos, pend, pstep;
-    if (GRID) {
-      pos = (int32_t)c0 * tpc;
-      pend = min(nt, pos + tpc);
-      pstep = R;
-    } else {
-      pos = (int32_t)c0 * RPC;
-      pend = nr;
-      pstep = (int32_t)CH * RPC;
-    }
-    for (; pos < pend; pos += pstep) {
+    // passes of R tiles
+    const int32_t pend = min(nt, (int32_t)c0 * tpc + tpc);
+    for (int32_t pos = (int32_t)c0 * tpc; pos < pend; pos += R) {
       double rx[R], ry[R];
       using acc_t = typename std::conditional<MIXED, float, double>::type;
       acc_t ax[R], ay[R], dre[R], dim[R];
@@ -238,23 +214,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
       bool act[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if (GRID) {
-          // slot r's ray (an inactive slot takes the box's first ray); its
-          // output index is formed after the pair loop
-          const int32_t t = pos + r;  // wave-uniform tile index
-          const int32_t ty = t / TW, tx = t - ty * TW;
-          const int32_t ci = tx * TX + lx, cj = ty * TY + ly;
-          const bool on = t < pend && ci < W && cj < H;
-          rx[r] = grid_coord(a.grid.x0, a.grid.dx, i0 + (on ? ci : 0));
-          ry[r] = grid_coord(a.grid.y0, a.grid.dy, j0 + (on ? cj : 0));
-        } else {
-          const int32_t idx = pos + r * kWave + lane;
-          act[r] = idx < min(nr, pos + RPC);
-          const int32_t id = act[r] ? idx : 0;
-          rx[r] = rxy[2 * ((int64_t)r0 + id)];
-          ry[r] = rxy[2 * ((int64_t)r0 + id) + 1];
-          oidx[r] = rperm ? (int64_t)rperm[r0 + id] : (int64_t)r0 + id;
-        }
+        // slot r's ray (an inactive slot takes the box's first ray); its
+        // output index is formed after the pair loop
+        const int32_t t = pos + r;  // wave-uniform tile index
+        const int32_t ty = t / TW, tx = t - ty * TW;
+        const int32_t ci = tx * TX + lx, cj = ty * TY + ly;
+        const bool on = t < pend && ci < W && cj < H;
+        rx[r] = grid_coord(a.grid.x0, a.grid.dx, i0 + (on ? ci : 0));
+        ry[r] = grid_coord(a.grid.y0, a.grid.dy, j0 + (on ? cj : 0));
         ax[r] = 0;
         ay[r] = 0;
         dre[r] = 0;
@@ -328,16 +295,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
         dxr[r] = rx[r] - cx;
         dyr[r] = ry[r] - cy;
       }
-      if (GRID) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int32_t t = pos + r;
-          const int32_t ty = t / TW, tx = t - ty * TW;
-          const int32_t ci = tx * TX + lx, cj = ty * TY + ly;
-          act[r] = t < pend && ci < W && cj < H;
-          const int32_t cc = act[r] ? ci : 0, rr = act[r] ? cj : 0;
-          oidx[r] = (int64_t)(j0 + rr) * a.grid.nx + (i0 + cc);
-        }
+      for (int r = 0; r < R; ++r) {
+        const int32_t t = pos + r;
+        const int32_t ty = t / TW, tx = t - ty * TW;
+        const int32_t ci = tx * TX + lx, cj = ty * TY + ly;
+        act[r] = t < pend && ci < W && cj < H;
+        const int32_t cc = act[r] ? ci : 0, rr = act[r] ? cj : 0;
+        oidx[r] = (int64_t)(j0 + rr) * a.grid.nx + (i0 + cc);
       }
       // far field: Horner over the R rays from the top coefficient down, one
       // LDS read per coefficient
@@ -413,6 +378,121 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
   }
 }
 
+// Explicit rays, a lane to a ray: neighbouring rays (sorted by leaf box) in
+// neighbouring lanes, each with its own box's locals and stars, so that no lane
+// is idle where boxes hold few rays, and none waits where some hold many.  Bound
+// by the stars' loads, of which a lane keeps four in flight behind the four that
+// it works on.  Whole calls, mixed, a wave to a box before, now: 1e3 stars and
+// 1e6 rays 1249, 165 us; 1e4 and 1e5 119, 119; 1e5 and 1e6 225, 219; 1e6 and 1e5
+// 406, 306; 1e3 stars and 1e3 rays, one chain's latency, 72, 77 (as much as the
+// sort's box starts, which only the other form needed, took).  Each ray meets the
+// stars in the order of k_eval and moves its FP32 sums at the same stars (those
+// of whole steps of four count, per row of the neighbourhood): the same bits.
+template <bool MIXED, bool DERIV>
+__global__ __launch_bounds__(kThreads) void k_eval_rays(EvalArgs a, int64_t n, const double2 *__restrict__ loc,
+                                                        const double2 *__restrict__ sz,
+                                                        const double *__restrict__ sm,
+                                                        const float *__restrict__ sm32,
+                                                        const int32_t *__restrict__ leaf_start,
+                                                        const double2 *__restrict__ rxy,
+                                                        const uint32_t *__restrict__ rperm,
+                                                        double2 *__restrict__ y_out) {
+  using acc_t = typename std::conditional<MIXED, float, double>::type;
+  const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const bool act = gid < n;
+  const int64_t t = act ? gid : n - 1;
+  const int64_t nL = int64_t(1) << a.g.L;
+  const double s = ldexp(a.g.side, -a.g.L);
+  const double inv_s = 1.0 / s;
+  const double2 z = rxy[t];
+  // the ray's box, in the window (as the rays' sort places them)
+  int64_t ix = box_coord(z.x, a.g.x0, s, nL) - a.win.bx0;
+  int64_t iy = box_coord(z.y, a.g.y0, s, nL) - a.win.by0;
+  ix = ix < 0 ? 0 : (ix >= a.win.nbx ? a.win.nbx - 1 : ix);
+  iy = iy < 0 ? 0 : (iy >= a.win.nby ? a.win.nby - 1 : iy);
+  const int64_t gx = a.win.bx0 + ix, gy = a.win.by0 + iy;
+  // star ranges of the three rows, and their running totals
+  int32_t rs[3], pre[4];
+  pre[0] = 0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int64_t row = gy - 1 + d;
+    rs[d] = 0;
+    int32_t re = 0;
+    if (act && row >= 0 && row < nL) {
+      rs[d] = leaf_start[row * nL + (gx > 0 ? gx - 1 : 0)];
+      re = leaf_start[row * nL + (gx + 1 < nL ? gx + 1 : nL - 1) + 1];
+    }
+    pre[d + 1] = pre[d] + (re - rs[d]);
+  }
+  const int32_t ns = pre[3];
+  const double rx[1] = {z.x}, ry[1] = {z.y};
+  acc_t ax[1] = {0}, ay[1] = {0}, dre[1] = {0}, dim[1] = {0};
+  double Sx = 0.0, Sy = 0.0, Tr = 0.0, Ti = 0.0;
+  int32_t since = 0;
+  double2 nz[4];
+  acc_t nm[4];
+  int32_t nk[4];  // place in its row, or -1 beyond the last star
+  auto fetch = [&](int32_t q0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int32_t q = min(q0 + j, ns - 1);
+      const int d = q >= pre[2] ? 2 : (q >= pre[1] ? 1 : 0);
+      const int32_t k = q - (d == 2 ? pre[2] : (d == 1 ? pre[1] : 0));
+      const int32_t i = k + (d == 2 ? rs[2] : (d == 1 ? rs[1] : rs[0]));
+      nk[j] = q0 + j < ns ? k : -1;
+      nz[j] = sz[i];
+      if constexpr (MIXED) nm[j] = sm32[i]; else nm[j] = sm[i];
+    }
+  };
+  if (ns > 0) fetch(0);
+  for (int32_t q0 = 0; q0 < ns; q0 += 4) {
+    double2 cz[4];
+    acc_t cm[4];
+    int32_t ck[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cz[j] = nz[j], cm[j] = nm[j], ck[j] = nk[j];
+    fetch(q0 + 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (ck[j] < 0) continue;
+      pair_update<MIXED, DERIV, 1>(rx, ry, cz[j].x, cz[j].y, cm[j], ax, ay, dre, dim);
+      if (MIXED && (ck[j] & 3) == 3) {
+        since += 4;
+        if (since >= kFlushStars) {
+          since = 0;
+          Sx += (double)ax[0];
+          Sy += (double)ay[0];
+          ax[0] = ay[0] = 0;
+          if (DERIV) {
+            Tr += (double)dre[0];
+            Ti += (double)dim[0];
+            dre[0] = dim[0] = 0;
+          }
+        }
+      }
+    }
+  }
+  // far field: Horner, with the derivative's sum in the same sweep
+  const double2 *lb = loc + (iy * a.win.nbx + ix) * a.p;
+  const cplx w = {(z.x - (a.g.x0 + ((double)gx + 0.5) * s)) * inv_s,
+                  (z.y - (a.g.y0 + ((double)gy + 0.5) * s)) * inv_s};
+  cplx f = {lb[a.p - 1].x, lb[a.p - 1].y}, gd = {0.0, 0.0};
+#pragma unroll 4
+  for (int l = a.p - 2; l >= 0; --l) {
+    const double2 c = lb[l];
+    if (DERIV) gd = cmad(gd, w, f);
+    f = cmad(f, w, cplx{c.x, c.y});
+  }
+  if (!act) return;
+  const int64_t o = rperm[t];
+  y_out[o] = make_double2(a.c1 * z.x - (f.re + ((double)ax[0] + Sx)),
+                          a.c2 * z.y - (((double)ay[0] + Sy) - f.im));
+  if (DERIV)
+    reinterpret_cast<double2 *>(a.dfdz_out)[o] =
+        make_double2(fma(gd.re, inv_s, (double)dre[0] + Tr), fma(gd.im, inv_s, (double)dim[0] + Ti));
+}
+
 // first ray column (row) of every box column (row) of the window: columns in
 // blockIdx.y = 0, rows in blockIdx.y = 1 (one launch)
 struct GridAxis {
@@ -442,48 +522,43 @@ __global__ __launch_bounds__(kThreads) void k_grid_ranges(GridAxis ax, GridAxis 
 
 constexpr int64_t kMaxEvalBlocks = 256 * 32 * 4;  // CUs x waves per CU x sweeps in flight
 
-template <int PM, bool MIXED, bool MAP, bool GRID, int R, bool DERIV = false>
+template <int PM, bool MIXED, bool MAP, int R, bool DERIV = false>
 void eval_launch_r(const EvalArgs &a, hipStream_t stream) {
   const int64_t units = a.win.count() * a.chunks_per_box;
   int64_t nblk = units < kMaxEvalBlocks ? units : kMaxEvalBlocks;
   if (nblk > kXcd) nblk = nblk / kXcd * kXcd;
-  hipLaunchKernelGGL((k_eval<PM, MIXED, MAP, GRID, R, DERIV>), dim3((unsigned)nblk), dim3(kWave), 0, stream,
-                     a, a.loc, a.sxy, a.sm, a.sm32, a.leaf_start, a.col_start, a.row_start, a.rxy, a.rperm,
-                     a.ray_start, a.y_out, a.counts);
+  hipLaunchKernelGGL((k_eval<PM, MIXED, MAP, R, DERIV>), dim3((unsigned)nblk), dim3(kWave), 0, stream,
+                     a, a.loc, a.sxy, a.sm, a.sm32, a.leaf_start, a.col_start, a.row_start, a.y_out,
+                     a.counts);
 }
 
-template <int PM, bool MIXED, bool MAP, bool GRID>
+template <int PM, bool MIXED, bool MAP>
 void eval_launch(const EvalArgs &a, hipStream_t stream) {
   if constexpr (!MAP) {
     // f' wanted: one instance per order bucket, two rays per lane (the
     // launch shape is chosen for R = 2 in that case)
     if (a.dfdz_out) {
-      eval_launch_r<PM, MIXED, MAP, GRID, 2, true>(a, stream);
+      eval_launch_r<PM, MIXED, MAP, 2, true>(a, stream);
       return;
     }
   }
   switch (a.rays_per_lane) {
-    case 1: eval_launch_r<PM, MIXED, MAP, GRID, 1>(a, stream); break;
-    case 2: eval_launch_r<PM, MIXED, MAP, GRID, 2>(a, stream); break;
-    case 3: eval_launch_r<PM, MIXED, MAP, GRID, 3>(a, stream); break;
-    default: eval_launch_r<PM, MIXED, MAP, GRID, 4>(a, stream); break;
+    case 1: eval_launch_r<PM, MIXED, MAP, 1>(a, stream); break;
+    case 2: eval_launch_r<PM, MIXED, MAP, 2>(a, stream); break;
+    case 3: eval_launch_r<PM, MIXED, MAP, 3>(a, stream); break;
+    default: eval_launch_r<PM, MIXED, MAP, 4>(a, stream); break;
   }
 }
 
 template <int PM>
 void eval_dispatch(const EvalArgs &a, int precision, hipStream_t stream) {
   const bool mixed = precision == LENS_MIXED, map = a.counts != nullptr;
-  if (a.grid_mode) {
-    if (mixed) {
-      if (map) eval_launch<PM, true, true, true>(a, stream);
-      else eval_launch<PM, true, false, true>(a, stream);
-    } else {
-      if (map) eval_launch<PM, false, true, true>(a, stream);
-      else eval_launch<PM, false, false, true>(a, stream);
-    }
+  if (mixed) {
+    if (map) eval_launch<PM, true, true>(a, stream);
+    else eval_launch<PM, true, false>(a, stream);
   } else {
-    if (mixed) eval_launch<PM, true, false, false>(a, stream);
-    else eval_launch<PM, false, false, false>(a, stream);
+    if (map) eval_launch<PM, false, true>(a, stream);
+    else eval_launch<PM, false, false>(a, stream);
   }
 }
 
@@ -538,6 +613,26 @@ void launch_eval(const EvalArgs &a, int precision, hipStream_t stream) {
   if (precision == LENS_MIXED && !a.sm32)
     fail(LENS_EINVAL, "mixed-precision evaluation needs the plan's FP32 masses");
   LENS_PMAX_DISPATCH(a.p, eval_dispatch<PM>(a, precision, stream));
+  LENS_HIP(hipGetLastError());
+}
+
+template <bool MIXED>
+void eval_rays(const EvalArgs &a, int64_t n, hipStream_t stream) {
+  auto *kernel = a.dfdz_out ? k_eval_rays<MIXED, true> : k_eval_rays<MIXED, false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a, n,
+                     reinterpret_cast<const double2 *>(a.loc), reinterpret_cast<const double2 *>(a.sxy), a.sm,
+                     a.sm32, a.leaf_start, reinterpret_cast<const double2 *>(a.rxy), a.rperm,
+                     reinterpret_cast<double2 *>(a.y_out));
+}
+
+void launch_eval_rays(const EvalArgs &a, int64_t n, int precision, hipStream_t stream) {
+  if (n == 0) return;
+  if (precision == LENS_MIXED && !a.sm32)
+    fail(LENS_EINVAL, "mixed-precision evaluation needs the plan's FP32 masses");
+  if (precision == LENS_MIXED)
+    eval_rays<true>(a, n, stream);
+  else
+    eval_rays<false>(a, n, stream);
   LENS_HIP(hipGetLastError());
 }
 

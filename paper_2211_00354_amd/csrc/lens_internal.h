@@ -117,7 +117,7 @@ struct TreeSort {
   int qdim;
   double *sxy, *sq;
   float *sq32;
-  int32_t *start, *coarse;
+  int32_t *start, *coarse;  // nullptr: no starts wanted
   uint32_t *k, *v, *k_tmp, *v_tmp, *cnt;
   double *rec;
 };
@@ -261,16 +261,14 @@ struct EvalArgs {
   const double *sm;
   const float *sm32;     // their masses in FP32 (LENS_MIXED near field)
   const int32_t *leaf_start;  // [4^L + 1]
-  // rays: grid or sorted explicit
-  int grid_mode;
+  // rays: a grid (launch_eval) or sorted explicit ones (launch_eval_rays)
   lens_grid grid;
   const int32_t *col_start;   // grid: [win.nbx + 1] first ray column per box column
   const int32_t *row_start;   // grid: [win.nby + 1]
   const double *rxy;          // explicit, sorted by leaf box
   const uint32_t *rperm;      // explicit: sorted position -> caller index
-  const int32_t *ray_start;   // explicit: [win.count() + 1]
-  int64_t chunks_per_box;     // units (waves) per leaf box
-  int rays_per_lane;          // R: rays held per lane (1..4), 64*R rays per unit
+  int64_t chunks_per_box;     // grid: units (waves) per leaf box
+  int rays_per_lane;          // grid: R rays held per lane (1..4), 64*R rays per pass
   int tile_shift;             // grid: a wave's 64 rays are a 2^tile_shift-wide tile
   double c1, c2;              // (1 - kappa_s - gamma), (1 - kappa_s + gamma)
   double *y_out;              // [n][2] or nullptr
@@ -281,6 +279,8 @@ struct EvalArgs {
   int32_t npix;
 };
 void launch_eval(const EvalArgs &a, int precision, hipStream_t stream);
+// a.rxy's n explicit rays, sorted by leaf box, all in a.win
+void launch_eval_rays(const EvalArgs &a, int64_t n, int precision, hipStream_t stream);
 // col_start[c] = first grid column whose rays fall in box column win.bx0 + c
 // (c = 0..nbx); row_start likewise over the rows [j_begin, j_end).
 void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j_begin,
@@ -291,20 +291,19 @@ void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles);
 // Adjoint (adjoint.hip): gradients at stars from rays with complex charges
 struct AdjArgs {
   const double *sq;       // sorted source charges [n][2] (complex g_k)
-  const double *txy;      // targets (stars) sorted by window box
-  const double *tm;       // their masses
+  int64_t nt;             // targets (stars), sorted by leaf box
+  const double *txy, *tm;
   const uint32_t *tperm;  // sorted position -> caller's star index
-  const int32_t *tstart;  // [win.count() + 1], or [4^L + 1] if tglobal
+  double per_box;         // sources per leaf box where the targets are, about
   double *grad_xy;        // [N][2]
   double *grad_m;         // [N]
-  bool tglobal = false;   // tstart indexed by global leaf box (a forward plan's)
 };
+// a.win: a window that holds every target's leaf box, a.loc its locals
 void launch_eval_adj(const EvalArgs &a, const AdjArgs &d, int precision, hipStream_t stream);
 void launch_direct_adj(int64_t n_stars, const double *star_xy, const double *star_m, int64_t n_rays,
                        const double *rays_xy, const double *grad_y, double *grad_xy,
                        double *grad_m, hipStream_t stream);
 void launch_grid_rays(const lens_grid &g, double *out, hipStream_t stream);
-int64_t adj_targets_per_unit();
 
 // Direct FP64 sum (direct.hip)
 struct DirectArgs {

@@ -466,6 +466,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_tree_small(PointKey pkey, int
       }
     __syncthreads();
   }
+  if (!start) {
+    for (int j = t; j < n; j += kSmallThreads) {
+      perm[j] = sval[j];
+      move(sval[j], j);
+    }
+    return;
+  }
   // starts: counts per box (two to a word), then their prefix
   uint32_t *cnt32 = reinterpret_cast<uint32_t *>(run);
   for (int e = t; e < (nbox + 1) / 2; e += kSmallThreads) cnt32[e] = 0u;
@@ -727,7 +734,7 @@ size_t radix_counts_len(int64_t n) {
 
 const uint32_t *launch_tree_sort(const TreeSort &a, hipStream_t stream) {
   if (a.n == 0) {
-    launch_box_starts(a.k, 0, a.nbox, a.start, a.coarse, stream);  // all zero
+    if (a.start) launch_box_starts(a.k, 0, a.nbox, a.start, a.coarse, stream);  // all zero
     return a.v;
   }
   int bits = 1;
@@ -750,7 +757,7 @@ const uint32_t *launch_tree_sort(const TreeSort &a, hipStream_t stream) {
   else
     hipLaunchKernelGGL(k_move<false>, dim3(blocks_for(a.n)), dim3(kThreads), 0, stream, move, nullptr, perm,
                        a.n);
-  launch_box_starts(in_tmp ? a.k_tmp : a.k, a.n, a.nbox, a.start, a.coarse, stream);
+  if (a.start) launch_box_starts(in_tmp ? a.k_tmp : a.k, a.n, a.nbox, a.start, a.coarse, stream);
   return perm;
 }
 

@@ -163,3 +163,59 @@ def test_tree_sort_forms(lf, n, leaf):
     plan.close()
     assert float((gx - rx).norm() / rx.norm()) < 1e-8
     assert float((gm - rm).norm() / rm.norm()) < 1e-8
+
+
+@pytest.mark.parametrize("precision,tol", [("mixed", 1e-5), ("fp64", 1e-9)])
+@pytest.mark.parametrize("n,n_rays,radius", [
+    (1, 1, 1.0), (63, 400, 30.0), (300, 70000, 30.0), (16385, 20000, 30.0), (20000, 40000, 2.0),
+    (65537, 30000, 30.0), (65537, 60000, 3.0), (70000, 90000, 2.0)])
+def test_adjoint_lanes_per_target(lf, n, n_rays, radius, precision, tol):
+    # one, four and sixteen lanes to a star, by the number of stars and by how
+    # many rays share a box; every neighbourhood size around the groups of
+    # sources occurs between a dense middle and an empty rim.  Two stars lie on
+    # rays (such pairs add nothing).
+    f = wl.random_field(n, 30.0, seed=n, masses="powerlaw")
+    rng = np.random.default_rng(n_rays)
+    rays = (rng.random((n_rays, 2)) - 0.5) * 2 * radius
+    xy = f.xy.copy()
+    k = min(2, n, n_rays)
+    xy[:k] = rays[:k]
+    X, M, r = dev(xy), dev(f.m), dev(rays)
+    g = dev(rng.standard_normal((n_rays, 2)))
+    rx, rm = lf.deflect_backward(X, M, g, rays=r, method="direct")
+    p = 12 if precision == "mixed" else 24
+    plan = lf.Plan(X, M, ray_box=(-31.0, -31.0, 31.0, 31.0), precision=precision, p=p)
+    for gx, gm in (lf.deflect_backward(X, M, g, rays=r, precision=precision, p=p),
+                   lf.deflect_backward(None, None, g, rays=r, plan=plan)):
+        for a, b in ((gx, rx), (gm, rm)):
+            # a box without rays near it has locals of every ray at one size:
+            # the norm over all stars is the scale
+            assert float((a - b).norm()) <= tol * max(float(b.norm()), 1e-300)
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("n,leaf_level,side", [(5, 3, 16), (3000, 3, 96), (3000, 5, 33), (20000, 4, 130)])
+def test_explicit_rays_match_grid(lf, n, leaf_level, side, precision):
+    # a lane to a ray against a wave to a box: the same rays as a grid and as
+    # points, shuffled.  A core of stars gives some neighbourhoods thousands of
+    # them (many moves of the FP32 sums), others a few or none.  Both add the
+    # same pairs in the same order; the FP64 sums behind them may round a few
+    # times otherwise (1e-14 of the largest value).
+    f = wl.random_field(n, 30.0, seed=n + side, masses="powerlaw")
+    xy = f.xy.copy()
+    xy[: n // 2] *= 0.1
+    X, M = dev(xy), dev(f.m)
+    g = lf.Grid(-31.0, -30.5, 61.0 / side, 60.0 / side, side, side)
+    plan = lf.Plan(X, M, ray_box=(-32.0, -32.0, 32.0, 32.0), precision=precision, p=12, leaf_level=leaf_level)
+    i, j = np.meshgrid(np.arange(side), np.arange(side))
+    r = np.stack([g.x0 + (i + 0.5) * g.dx, g.y0 + (j + 0.5) * g.dy], -1).reshape(-1, 2)
+    order = np.random.default_rng(side).permutation(len(r))
+    rays = dev(r[order])
+    d, dg = (torch.empty((len(r), 2), dtype=torch.float64, device="cuda") for _ in range(2))
+    yg, _ = lf.deflect(plan=plan, grid=g, dfdz_out=dg)
+    for deriv in (False, True):
+        y = lf.deflect(plan=plan, rays=rays, dfdz_out=d)[0] if deriv else lf.deflect(plan=plan, rays=rays)
+        ref = yg.reshape(-1, 2)[dev(order)]
+        assert float((y.reshape(-1, 2) - ref).abs().max()) <= 1e-14 * float(ref.abs().max())
+    ref = dg[dev(order)]
+    assert float((d - ref).abs().max()) <= 1e-14 * float(ref.abs().max())
