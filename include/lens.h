@@ -163,6 +163,11 @@ LENS_API lens_status lens_plan_create(const lens_field *field, const double *ray
                                       const lens_grid *grid, const lens_opts *opts, void *stream,
                                       lens_plan **out);
 
+/* The bounding box out[4] = x1min, x2min, x1max, x2max (host) of n >= 1
+ * positions xy[n][2] (FP64, device), as lens_plan_create takes it; waits for
+ * it.  Refuses positions that are not all finite. */
+LENS_API lens_status lens_bounds(const double *xy, int64_t n, double *out, void *stream);
+
 /* Release a plan.  Does not wait: its device buffers return to the library's
  * pool ordered after the work last enqueued with the plan (a later reuse on
  * another stream waits for that work). */

@@ -77,6 +77,8 @@ def load(path: str = LIB_PATH):
     lib.lens_opts_default.restype = None
     lib.lens_plan_create.argtypes = [P(LensField), P(D), P(LensGrid), P(LensOpts), V, P(V)]
     lib.lens_plan_create.restype = ctypes.c_int
+    lib.lens_bounds.argtypes = [V, I64, P(D), V]
+    lib.lens_bounds.restype = ctypes.c_int
     lib.lens_plan_destroy.argtypes = [V]
     lib.lens_plan_destroy.restype = None
     lib.lens_plan_info.argtypes = [V, P(I32), P(I32), P(D), P(D), P(D)]

@@ -1980,6 +1980,17 @@ lens_status lens_plan_create(const lens_field *field, const double *ray_box, con
   });
 }
 
+lens_status lens_bounds(const double *xy, int64_t n, double *out, void *stream) {
+  return guarded([&] {
+    if (n < 1 || !xy || !out) fail(LENS_EINVAL, "lens_bounds needs n >= 1 positions and out");
+    const double big = std::numeric_limits<double>::max();
+    const double all[4] = {-big, -big, big, big};
+    int64_t finite = 0;
+    device_bbox(xy, n, (hipStream_t)stream, out, all, &finite);
+    if (finite != n) fail(LENS_EINVAL, "non-finite coordinates in the input positions");
+  });
+}
+
 void lens_plan_destroy(lens_plan *plan) {
   if (!plan) return;
   // stream-ordered: the buffers go back to the pool behind the plan's last
