@@ -817,8 +817,13 @@ void gridexec_alloc(const lens_plan &P, const lens_grid &grid, int64_t j0, int64
     return std::max<int64_t>(1, std::min(n, cap));
   };
   int64_t tiles = 0;
-  grid_tile_shape(per_box(grid.dx, grid.nx), per_box(grid.dy, j1 - j0), &ea.tile_shift, &tiles);
+  const int64_t bw = per_box(grid.dx, grid.nx), bh = per_box(grid.dy, j1 - j0);
+  grid_tile_shape(bw, bh, &ea.tile_shift, &tiles);
   eval_shape(tiles * 64, &ea.rays_per_lane, &ea.chunks_per_box);
+  const int64_t lanes = 64 * ea.rays_per_lane;
+  if (!quad_shape(bw, bh, (tiles * 64 + lanes - 1) / lanes * lanes, &ea.quad_shift, &ea.quad_chunks) ||
+      wl.count() * ea.quad_chunks > (int64_t)0x7fffffff)
+    ea.quad_chunks = 0;
   while (wl.count() * ea.chunks_per_box > (int64_t)0x7fffffff && ea.chunks_per_box > 1)
     ea.chunks_per_box = (ea.chunks_per_box + 1) / 2;
   if (wl.count() > (int64_t)0x7fffffff) fail(LENS_EUNSUPPORTED, "leaf window too large");

@@ -12,11 +12,12 @@
 //   * near field: alpha_near = sum m (x - x_i)/|x - x_i|^2 over those stars;
 //     LENS_MIXED takes ray and star coordinates relative to the box centre
 //     (FP64, rounded to FP32) and does the pair arithmetic in FP32;
-//   * far field: f(z) = sum_l b~_l w^l, w = (z - c)/s, by Horner in FP64,
+//   * far field: f(z) = sum_l b~_l w^l, w = (z - c)/s, in FP64, by Horner or,
+//     four mirror images to a lane, by sums that the four share;
 //     alpha_far = conj(f);
 //   * y = (1-kappa_s-gamma, 1-kappa_s+gamma) * x - alpha in FP64, written as
-//     [n][2] or binned into the map: counts are summed per unit in an LDS
-//     table and added to the map with one integer atomic per distinct pixel.
+//     [n][2] or binned into the map: counts are summed in an LDS table
+//     and added to the map by segments of pixels.
 // Units are spread over a bounded grid; consecutive units (neighbouring
 // boxes, which share stars) go to the same XCD so that they share its L2.
 #include "device_common.h"
@@ -87,48 +88,202 @@ __device__ __forceinline__ void pair_update(const double (&rx)[R], const double 
   }
 }
 
-// Map counts of a work unit are first summed in a small per-wave table in
-// LDS (pixel key -> count, open addressing with four linear probes; a ray
-// whose pixel finds all probed slots taken by other pixels goes straight to
-// the global map), then added to the map with one atomic per distinct pixel.
-// A unit's rays land on a compact patch of pixels, so 256 entries suffice.
-constexpr int kMapTableBits = 8;
-constexpr int kMapTable = 1 << kMapTableBits;
+// Orders a one-wave workgroup's LDS accesses: the LDS takes a wave's in their
+// order, so nothing is waited for (__syncthreads waits for the wave's stores and
+// atomics to memory as well).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
-__device__ __forceinline__ void map_table_add(int32_t *hkey, uint32_t *hval, int32_t key,
-                                              int32_t *__restrict__ counts) {
-  uint32_t slot = ((uint32_t)key * 2654435761u) >> (32 - kMapTableBits);
+// Map counts are first summed in a small per-wave table in LDS: kMapSegs rows of
+// half a 64-byte segment of the map (8 pixels) each, two 16-bit counts to a word
+// (open addressing by segment with four linear probes; a ray whose segment finds
+// all probed rows taken goes straight to the global map).  At a unit's end, or
+// when a pass leaves the table half full, they are added to the map by rows,
+// eight lanes to one.  The map's atomics bound such calls where a box's image
+// is wide: the memory side takes 23.7 requests per ns, and the lanes of an
+// instruction within one segment make one.
+constexpr int kSegBits = 3, kSegPixels = 1 << kSegBits;
+constexpr int kMapSegBits = 7, kMapSegs = 1 << kMapSegBits;
+constexpr int kMapPasses = 64;  // passes of at most 256 rays whose counts fit in 16 bits
+
+struct MapTable {
+  int32_t seg[kMapSegs];  // key / kSegPixels, or -1
+  uint32_t val[kMapSegs * kSegPixels / 2];
+  uint8_t used[kMapSegs];  // the rows in use, listed for the flush
+};
+
+__device__ __forceinline__ void map_table_clear(MapTable &t, int lane) {
+  for (int e = lane; e < kMapSegs; e += kWave) t.seg[e] = -1;
+  for (int e = lane; e < kMapSegs * kSegPixels / 2; e += kWave) t.val[e] = 0;
+}
+
+__device__ __forceinline__ void map_table_add(MapTable &t, int32_t key, int32_t *__restrict__ counts) {
+  const int32_t seg = key >> kSegBits;
+  uint32_t slot = ((uint32_t)seg * 2654435761u) >> (32 - kMapSegBits);
 #pragma unroll
   for (int probe = 0; probe < 4; ++probe) {
-    const int32_t prev = atomicCAS(&hkey[slot], -1, key);
-    if (prev == -1 || prev == key) {
-      atomicAdd(&hval[slot], 1u);
+    // a read first: the lanes share it, while their exchanges would queue
+    int32_t have = *(volatile int32_t *)&t.seg[slot];
+    if (have == -1) have = atomicCAS(&t.seg[slot], -1, seg);
+    if (have == -1 || have == seg) {
+      const uint32_t px = slot * kSegPixels + (key & (kSegPixels - 1));
+      atomicAdd(&t.val[px >> 1], px & 1 ? 0x10000u : 1u);
       return;
     }
-    slot = (slot + 1) & (kMapTable - 1);
+    slot = (slot + 1) & (kMapSegs - 1);
   }
   atomicAdd(&counts[key], 1);
 }
 
-__device__ __forceinline__ void map_table_flush(int32_t *hkey, uint32_t *hval,
-                                                int32_t *__restrict__ counts, int lane) {
-  __syncthreads();
+// adds the counts to the map and clears them if more than `above` rows are used
+__device__ __forceinline__ bool map_table_flush(MapTable &t, int above, int32_t *__restrict__ counts, int lane) {
+  wave_sync();
+  int n = 0;
+  bool have[kMapSegs / kWave];
+  uint64_t mask[kMapSegs / kWave];
 #pragma unroll
-  for (int e = lane; e < kMapTable; e += 64) {
-    const int32_t k = hkey[e];
-    if (k >= 0) {
-      atomicAdd(&counts[k], (int32_t)hval[e]);
-      hkey[e] = -1;
-      hval[e] = 0;
+  for (int q = 0; q < kMapSegs / kWave; ++q) {
+    have[q] = t.seg[q * kWave + lane] >= 0;
+    mask[q] = __ballot(have[q]);
+    n += __popcll(mask[q]);
+  }
+  if (n <= above) return false;
+  int base = 0;
+#pragma unroll
+  for (int q = 0; q < kMapSegs / kWave; ++q) {
+    if (have[q]) t.used[base + __popcll(mask[q] & ((uint64_t(1) << lane) - 1))] = (uint8_t)(q * kWave + lane);
+    base += __popcll(mask[q]);
+  }
+  wave_sync();
+  for (int i = lane >> kSegBits; i < n; i += kWave >> kSegBits) {
+    const int row = t.used[i], px = lane & (kSegPixels - 1), word = (row * kSegPixels + px) >> 1;
+    const uint32_t two = t.val[word];
+    const int32_t seg = t.seg[row];
+    wave_sync();  // read by all, then cleared
+    if (!(px & 1)) t.val[word] = 0;
+    if (px == 0) t.seg[row] = -1;
+    const uint32_t v = px & 1 ? two >> 16 : two & 0xffffu;
+    if (v) atomicAdd(&counts[(seg << kSegBits) + px], (int32_t)v);
+  }
+  wave_sync();
+  return true;
+}
+
+// QUAD: a lane's four rays are mirror images of each other in the centre lines
+// of the box's rays (any grid: the expansion b is first moved to that centre,
+// unless the two agree but for rounding), at w, -conj w, conj w and -w.  With
+// z = w^2, f(w) = E(z) + w O(z) from the even and the odd coefficients, and
+// P(z) = (c_0 - |z|^2 B_2) + z B_1 with the real recurrence
+// B_k = c_k + 2 Re(z) B_k+1 - |z|^2 B_k+2 serves conj z as well: 4 p FMAs for the
+// four rays where a Horner sum for each takes 16 p.  |z| <= 1/2, so the
+// recurrence damps its roundings.  The pair sums gain too: the four rays have
+// two columns and two rows, so a star costs them four differences, not eight.
+// 1e6 stars, 8192^2 rays, p = 12: 343 to 250 million VALU instructions, 700 to
+// 560 us.
+constexpr double kSameCentre = 0x1p-50;
+
+struct InverseInts {
+  double v[LENS_MAX_ORDER + 1];
+  constexpr InverseInts() : v{} {
+    for (int i = 1; i <= LENS_MAX_ORDER; ++i) v[i] = 1.0 / i;
+  }
+};
+__constant__ const InverseInts kInverse = InverseInts();
+
+// b_k <- sum_m C(k+m, m) d^m b_k+m, a lane to a k; m runs while the largest
+// C(p-1, m) |d|^m counts
+__device__ __forceinline__ void shift_local(double2 *b, int p, cplx d, int lane) {
+  const double size = fabs(d.re) + fabs(d.im);
+  cplx t = {1.0, 0.0};
+  double left = 1.0;
+  double2 sum = lane < p ? b[lane] : make_double2(0.0, 0.0);
+  for (int m = 1; m < p; ++m) {
+    left *= size * (double)(p - m) * kInverse.v[m];
+    if (left < 0x1p-60) break;
+    const double up = (double)(lane + m) * kInverse.v[m];
+    t = cplx{(t.re * d.re - t.im * d.im) * up, (t.re * d.im + t.im * d.re) * up};
+    if (lane + m < p) {
+      const double2 c = b[lane + m];
+      sum.x += t.re * c.x - t.im * c.y;
+      sum.y += t.re * c.y + t.im * c.x;
     }
   }
-  __syncthreads();
+  wave_sync();
+  if (lane < p) b[lane] = sum;
+  wave_sync();
+}
+
+// P at z and conj z from B_1 and B_2 (n1, n2): (c0 + q n2) + z n1, q = -|z|^2
+struct Conj {
+  cplx at, cj;
+};
+__device__ __forceinline__ Conj quad_values(cplx z, double q, double2 c0, cplx n1, cplx n2) {
+  const cplx m = {fma(z.re, n1.re, fma(q, n2.re, c0.x)), fma(z.re, n1.im, fma(q, n2.im, c0.y))};
+  return {{fma(-z.im, n1.im, m.re), fma(z.im, n1.re, m.im)}, {fma(z.im, n1.im, m.re), fma(-z.im, n1.re, m.im)}};
+}
+__device__ __forceinline__ cplx quad_step(double r, double q, double2 c, cplx n1, cplx n2) {
+  return {fma(r, n1.re, fma(q, n2.re, c.x)), fma(r, n1.im, fma(q, n2.im, c.y))};
+}
+
+// f (DERIV: and df/dw) at w, -conj w, conj w, -w; b[p] is 0.  The derivative
+// needs P'(z) = B_1 + 2 i Im(z) Q(z), Q's coefficients being B_2, B_3, ...: the
+// same recurrence once more.
+template <bool DERIV>
+__device__ __forceinline__ void quad_local(const double2 *b, int p, cplx w, cplx (&f)[4], cplx (&g)[4]) {
+  const cplx z = {fma(w.re, w.re, -w.im * w.im), 2.0 * w.re * w.im};
+  const double r = 2.0 * z.re, q = -fma(z.re, z.re, z.im * z.im);
+  cplx e1 = {0.0, 0.0}, e2 = {0.0, 0.0}, o1 = {0.0, 0.0}, o2 = {0.0, 0.0};
+  cplx c1 = {0.0, 0.0}, c2 = {0.0, 0.0}, d1 = {0.0, 0.0}, d2 = {0.0, 0.0};
+#pragma unroll 2
+  for (int k = (p - 1) >> 1; k >= 1; --k) {
+    const cplx e = quad_step(r, q, b[2 * k], e1, e2), o = quad_step(r, q, b[2 * k + 1], o1, o2);
+    if (DERIV && k >= 3) {
+      const cplx c = quad_step(r, q, make_double2(e.re, e.im), c1, c2);
+      const cplx d = quad_step(r, q, make_double2(o.re, o.im), d1, d2);
+      c2 = c1;
+      c1 = c;
+      d2 = d1;
+      d1 = d;
+    }
+    e2 = e1;
+    e1 = e;
+    o2 = o1;
+    o1 = o;
+  }
+  const Conj E = quad_values(z, q, b[0], e1, e2), O = quad_values(z, q, b[1], o1, o2);
+  const cplx wo = {fma(w.re, O.at.re, -w.im * O.at.im), fma(w.re, O.at.im, w.im * O.at.re)};
+  const cplx wc = {fma(w.re, O.cj.re, w.im * O.cj.im), fma(w.re, O.cj.im, -w.im * O.cj.re)};
+  f[0] = cplx{E.at.re + wo.re, E.at.im + wo.im};
+  f[1] = cplx{E.cj.re - wc.re, E.cj.im - wc.im};
+  f[2] = cplx{E.cj.re + wc.re, E.cj.im + wc.im};
+  f[3] = cplx{E.at.re - wo.re, E.at.im - wo.im};
+  if constexpr (DERIV) {
+    // f' = (O + 2 z O') +- 2 w E'
+    const Conj C = quad_values(z, q, make_double2(e2.re, e2.im), c1, c2);
+    const Conj D = quad_values(z, q, make_double2(o2.re, o2.im), d1, d2);
+    const double t = 2.0 * z.im;
+    const cplx ea = {fma(-t, C.at.im, e1.re), fma(t, C.at.re, e1.im)};
+    const cplx ec = {fma(t, C.cj.im, e1.re), fma(-t, C.cj.re, e1.im)};
+    const cplx oa = {fma(-t, D.at.im, o1.re), fma(t, D.at.re, o1.im)};
+    const cplx oc = {fma(t, D.cj.im, o1.re), fma(-t, D.cj.re, o1.im)};
+    const cplx sa = {fma(r, oa.re, fma(-t, oa.im, O.at.re)), fma(r, oa.im, fma(t, oa.re, O.at.im))};
+    const cplx sc = {fma(r, oc.re, fma(t, oc.im, O.cj.re)), fma(r, oc.im, fma(-t, oc.re, O.cj.im))};
+    const double u = 2.0 * w.re, v = 2.0 * w.im;
+    const cplx ua = {fma(u, ea.re, -v * ea.im), fma(u, ea.im, v * ea.re)};
+    const cplx uc = {fma(u, ec.re, v * ec.im), fma(u, ec.im, -v * ec.re)};
+    g[0] = cplx{sa.re + ua.re, sa.im + ua.im};
+    g[1] = cplx{sc.re - uc.re, sc.im - uc.im};
+    g[2] = cplx{sc.re + uc.re, sc.im + uc.im};
+    g[3] = cplx{sa.re - ua.re, sa.im - ua.im};
+  }
 }
 
 // The mixed kernels are compiled for five waves per SIMD (at most 96 VGPRs;
 // the R = 4 instances spill a few bytes of per-lane scratch outside the pair
 // loop), which measured faster than four waves without spills.
-template <int PMAX, bool MIXED, bool MAP, int R, bool DERIV>
+template <int PMAX, bool MIXED, bool MAP, int R, bool DERIV, bool QUAD>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && !DERIV ? 5 : 1))) void k_eval(EvalArgs a, const double *__restrict__ loc,
                                                 const double *__restrict__ sxy,
                                                 const double *__restrict__ sm,
@@ -139,21 +294,15 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
                                                 double *__restrict__ y_out,
                                                 int32_t *__restrict__ counts) {
   // the box's local expansion, read by every lane (LDS broadcast)
-  __shared__ double2 lds_loc[PMAX];
+  __shared__ double2 lds_loc[PMAX + 1];
   // LENS_MIXED: FP64 sums of the lanes' FP32 near-field partials, flushed
   // every kFlushStars stars (alpha; f' with DERIV)
   __shared__ double2 lds_acc[MIXED ? kWave * R * (DERIV ? 2 : 1) : 1];
-  __shared__ int32_t hkey[MAP ? kMapTable : 1];
-  __shared__ uint32_t hval[MAP ? kMapTable : 1];
+  __shared__ typename std::conditional<MAP, MapTable, int>::type table;
   const int lane = threadIdx.x;
-  if (MAP) {
-    for (int e = lane; e < kMapTable; e += 64) {
-      hkey[e] = -1;
-      hval[e] = 0;
-    }
-  }
+  if constexpr (MAP) map_table_clear(table, lane);
   // unit counts fit in 31 bits (checked at launch)
-  const uint32_t CH = (uint32_t)a.chunks_per_box;
+  const uint32_t CH = (uint32_t)(QUAD ? a.quad_chunks : a.chunks_per_box);
   const uint32_t nbx = (uint32_t)a.win.nbx;
   const uint32_t nunits = (uint32_t)(a.win.count() * CH);
   // XCD-aware virtual block id: blocks dispatched to one XCD (blockIdx % 8)
@@ -166,7 +315,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
   const double inv_s = 1.0 / s;
   const int p = a.p;
   // a wave's R slots are R tiles of TX x TY rays (TX * TY = 64)
-  const int tsh = a.tile_shift;
+  const int tsh = QUAD ? a.quad_shift : a.tile_shift;
   const int TX = 1 << tsh, TY = kWave >> tsh;
   const int lx = lane & (TX - 1), ly = lane >> tsh;
 
@@ -176,12 +325,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
     const uint32_t byw = b / nbx, bxw = b - byw * nbx;
     const int64_t gx = a.win.bx0 + bxw, gy = a.win.by0 + byw;
 
-    // the box's rays are columns [i0, i0+W) x rows [j0, j0+H), cut into
-    // nt = TW x TH tiles, tpc consecutive tiles per unit
+    // the box's rays are columns [i0, i0+W) x rows [j0, j0+H); they (QUAD: the
+    // quarter at the low corner) are cut into nt = TW x TH tiles, tpc
+    // consecutive tiles per unit
     const int32_t i0 = col_start[bxw], W = col_start[bxw + 1] - i0;
     const int32_t j0 = row_start[byw], H = row_start[byw + 1] - j0;
-    const int32_t TW = (W + TX - 1) >> tsh;
-    const int32_t nt = TW * ((H + TY - 1) / TY);
+    const int32_t Wt = QUAD ? (W + 1) >> 1 : W, Ht = QUAD ? (H + 1) >> 1 : H;
+    const int32_t TW = (Wt + TX - 1) >> tsh;
+    const int32_t nt = TW * ((Ht + TY - 1) / TY);
     const int32_t tpc = (nt + (int32_t)CH - 1) / (int32_t)CH;
     if (nt == 0 || (int64_t)c0 * tpc >= nt) continue;  // uniform
 
@@ -200,13 +351,43 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
     }
     const double cx = a.g.x0 + ((double)gx + 0.5) * s;
     const double cy = a.g.y0 + ((double)gy + 0.5) * s;
-    __syncthreads();  // the previous unit's reads of lds_loc are done
+    wave_sync();  // the previous unit's reads of lds_loc are done
     if (lane < p) lds_loc[lane] = reinterpret_cast<const double2 *>(loc + 2 * (int64_t)b * p)[lane];
-    __syncthreads();
+    if (QUAD && lane == p) lds_loc[p] = make_double2(0.0, 0.0);
+    wave_sync();
+    if constexpr (QUAD) {
+      // the expansion about the centre of the box's rays
+      const double ccx = 0.5 * (grid_coord(a.grid.x0, a.grid.dx, i0) + grid_coord(a.grid.x0, a.grid.dx, i0 + W - 1));
+      const double ccy = 0.5 * (grid_coord(a.grid.y0, a.grid.dy, j0) + grid_coord(a.grid.y0, a.grid.dy, j0 + H - 1));
+      if (fabs(ccx - cx) > kSameCentre * fabs(cx) || fabs(ccy - cy) > kSameCentre * fabs(cy))
+        shift_local(lds_loc, p, cplx{(ccx - cx) * inv_s, (ccy - cy) * inv_s}, lane);
+    }
 
-    // passes of R tiles
+    // passes of R tiles, or of one tile and its three mirror images
     const int32_t pend = min(nt, (int32_t)c0 * tpc + tpc);
-    for (int32_t pos = (int32_t)c0 * tpc; pos < pend; pos += R) {
+    int held = 0;  // passes whose counts the table holds
+    for (int32_t pos = (int32_t)c0 * tpc; pos < pend; pos += QUAD ? 1 : R) {
+      // slot r's column and row in the box (an inactive slot takes tile place
+      // 0, 0); QUAD: r & 1 mirrors the column, r & 2 the row, and the middle
+      // column or row of an odd box is its own image
+      auto place = [&](int r, int32_t &ci, int32_t &cj) -> bool {
+        const int32_t t = QUAD ? pos : pos + r;  // wave-uniform tile index
+        const int32_t ty = t / TW, tx = t - ty * TW;
+        ci = tx * TX + lx;
+        cj = ty * TY + ly;
+        bool on = t < pend && ci < Wt && cj < Ht;
+        ci = on ? ci : 0;
+        cj = on ? cj : 0;
+        if (QUAD && (r & 1)) {
+          on = on && 2 * ci + 1 != W;
+          ci = W - 1 - ci;
+        }
+        if (QUAD && (r & 2)) {
+          on = on && 2 * cj + 1 != H;
+          cj = H - 1 - cj;
+        }
+        return on;
+      };
       double rx[R], ry[R];
       using acc_t = typename std::conditional<MIXED, float, double>::type;
       acc_t ax[R], ay[R], dre[R], dim[R];
@@ -214,14 +395,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
       bool act[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        // slot r's ray (an inactive slot takes the box's first ray); its
-        // output index is formed after the pair loop
-        const int32_t t = pos + r;  // wave-uniform tile index
-        const int32_t ty = t / TW, tx = t - ty * TW;
-        const int32_t ci = tx * TX + lx, cj = ty * TY + ly;
-        const bool on = t < pend && ci < W && cj < H;
-        rx[r] = grid_coord(a.grid.x0, a.grid.dx, i0 + (on ? ci : 0));
-        ry[r] = grid_coord(a.grid.y0, a.grid.dy, j0 + (on ? cj : 0));
+        // its output index is formed after the pair loop
+        int32_t ci, cj;
+        (void)place(r, ci, cj);
+        rx[r] = grid_coord(a.grid.x0, a.grid.dx, i0 + ci);
+        ry[r] = grid_coord(a.grid.y0, a.grid.dy, j0 + cj);
         ax[r] = 0;
         ay[r] = 0;
         dre[r] = 0;
@@ -297,18 +475,21 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int32_t t = pos + r;
-        const int32_t ty = t / TW, tx = t - ty * TW;
-        const int32_t ci = tx * TX + lx, cj = ty * TY + ly;
-        act[r] = t < pend && ci < W && cj < H;
-        const int32_t cc = act[r] ? ci : 0, rr = act[r] ? cj : 0;
-        oidx[r] = (int64_t)(j0 + rr) * a.grid.nx + (i0 + cc);
+        int32_t ci, cj;
+        act[r] = place(r, ci, cj);
+        oidx[r] = (int64_t)(j0 + cj) * a.grid.nx + (i0 + ci);
       }
+      cplx f[R], gd[R];
+      if constexpr (QUAD) {
+        // half the distances to the images: w of slot 0; slots 1..3 are
+        // -conj(w), conj(w), -w
+        quad_local<DERIV>(lds_loc, p, cplx{0.5 * (rx[0] - rx[1]) * inv_s, 0.5 * (ry[0] - ry[2]) * inv_s}, f, gd);
+      } else {
       // far field: Horner over the R rays from the top coefficient down, one
       // LDS read per coefficient
       // (DERIV: the derivative sum g = sum l b_l w^(l-1) in the same sweep,
       // g <- g w + f before f <- f w + b_l; f' = g / s)
-      cplx w[R], f[R], gd[R];
+      cplx w[R];
       {
         const double2 top = lds_loc[p - 1];
 #pragma unroll
@@ -330,6 +511,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
         }
       }
 
+      }
       int32_t key[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -368,13 +550,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
           }
         }
       }
-      if (MAP) {
+      if constexpr (MAP) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          if (key[r] >= 0) map_table_add(hkey, hval, key[r], counts);
+          if (key[r] >= 0) map_table_add(table, key[r], counts);
+        ++held;
+        if (pos + (QUAD ? 1 : R) < pend && map_table_flush(table, held < kMapPasses ? kMapSegs / 2 : 0, counts, lane))
+          held = 0;
       }
     }
-    if (MAP) map_table_flush(hkey, hval, counts, lane);
+    if constexpr (MAP) (void)map_table_flush(table, 0, counts, lane);
   }
 }
 
@@ -522,12 +707,12 @@ __global__ __launch_bounds__(kThreads) void k_grid_ranges(GridAxis ax, GridAxis 
 
 constexpr int64_t kMaxEvalBlocks = 256 * 32 * 4;  // CUs x waves per CU x sweeps in flight
 
-template <int PM, bool MIXED, bool MAP, int R, bool DERIV = false>
+template <int PM, bool MIXED, bool MAP, int R, bool DERIV = false, bool QUAD = false>
 void eval_launch_r(const EvalArgs &a, hipStream_t stream) {
-  const int64_t units = a.win.count() * a.chunks_per_box;
+  const int64_t units = a.win.count() * (QUAD ? a.quad_chunks : a.chunks_per_box);
   int64_t nblk = units < kMaxEvalBlocks ? units : kMaxEvalBlocks;
   if (nblk > kXcd) nblk = nblk / kXcd * kXcd;
-  hipLaunchKernelGGL((k_eval<PM, MIXED, MAP, R, DERIV>), dim3((unsigned)nblk), dim3(kWave), 0, stream,
+  hipLaunchKernelGGL((k_eval<PM, MIXED, MAP, R, DERIV, QUAD>), dim3((unsigned)nblk), dim3(kWave), 0, stream,
                      a, a.loc, a.sxy, a.sm, a.sm32, a.leaf_start, a.col_start, a.row_start, a.y_out,
                      a.counts);
 }
@@ -535,12 +720,19 @@ void eval_launch_r(const EvalArgs &a, hipStream_t stream) {
 template <int PM, bool MIXED, bool MAP>
 void eval_launch(const EvalArgs &a, hipStream_t stream) {
   if constexpr (!MAP) {
-    // f' wanted: one instance per order bucket, two rays per lane (the
-    // launch shape is chosen for R = 2 in that case)
+    // f' wanted: one instance of either form per order bucket, two rays per
+    // lane where they are not mirror images
     if (a.dfdz_out) {
-      eval_launch_r<PM, MIXED, MAP, 2, true>(a, stream);
+      if (a.quad_chunks)
+        eval_launch_r<PM, MIXED, MAP, 4, true, true>(a, stream);
+      else
+        eval_launch_r<PM, MIXED, MAP, 2, true>(a, stream);
       return;
     }
+  }
+  if (a.quad_chunks) {
+    eval_launch_r<PM, MIXED, MAP, 4, false, true>(a, stream);
+    return;
   }
   switch (a.rays_per_lane) {
     case 1: eval_launch_r<PM, MIXED, MAP, 1>(a, stream); break;
@@ -606,6 +798,17 @@ void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles) {
   }
   *shift = best;
   *tiles = best_t;
+}
+
+// Four mirror images to a lane where the quarter's tiles take at most 1.3 times
+// the ordinary ones' lane slots.  ps per ray, mixed, p = 12, ordinary and mirrored:
+// 1.0 (boxes of 16^2 rays) 12.2, 9.9; 1.14 (25^2) 16.3, 15.5; 1.29 (33^2) 11.2,
+// 10.4; 1.33 (11^2) 46.1, 50.8, (23^2) 15.4, 15.7.
+bool quad_shape(int64_t W, int64_t H, int64_t slots, int *shift, int64_t *CH) {
+  int64_t tiles = 0;
+  grid_tile_shape((W + 1) / 2, (H + 1) / 2, shift, &tiles);
+  *CH = (tiles + kPassesPerUnit - 1) / kPassesPerUnit;
+  return 10 * (4 * kWave * tiles) <= 13 * slots;
 }
 
 void launch_eval(const EvalArgs &a, int precision, hipStream_t stream) {

@@ -270,6 +270,8 @@ struct EvalArgs {
   int64_t chunks_per_box;     // grid: units (waves) per leaf box
   int rays_per_lane;          // grid: R rays held per lane (1..4), 64*R rays per pass
   int tile_shift;             // grid: a wave's 64 rays are a 2^tile_shift-wide tile
+  int64_t quad_chunks;        // grid: units per leaf box where a lane's rays are mirror images
+  int quad_shift;             // (0: not so), and the tile shape in the box's quarter
   double c1, c2;              // (1 - kappa_s - gamma), (1 - kappa_s + gamma)
   double *y_out;              // [n][2] or nullptr
   double *dfdz_out;           // [n][2] f'(z) (deflection only) or nullptr
@@ -287,6 +289,9 @@ void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j
                         int64_t j_end, int32_t *col_start, int32_t *row_start, hipStream_t stream);
 void eval_shape(int64_t max_rays, int *R, int64_t *CH);
 void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles);
+// whether boxes of W x H rays, in `slots` lane slots otherwise, are better
+// evaluated four mirror images to a lane, and that form's shape
+bool quad_shape(int64_t W, int64_t H, int64_t slots, int *shift, int64_t *CH);
 
 // Adjoint (adjoint.hip): gradients at stars from rays with complex charges
 struct AdjArgs {

@@ -237,3 +237,38 @@ def test_bounds_of_rays(lf, bad):
         one = torch.ones((1, 2), dtype=torch.float64, device="cuda")
         with pytest.raises(RuntimeError):
             lf.LensDeflect.apply(one, one[:, 0].contiguous(), r)
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 7, 12, 17, 24, 31, 40])
+@pytest.mark.parametrize("nx,ny,leaf_level", [(64, 64, 2), (65, 63, 2), (126, 251, 3), (521, 333, 4), (37, 1, 2)])
+def test_mirrored_rays_match_points(lf, nx, ny, leaf_level, p, precision):
+    # grids whose boxes hold enough rays for four mirror images to a lane (and,
+    # last, one that is a single row): even and odd boxes, aligned ones and
+    # others, boxes cut off at the grid's end; against the same rays as points.
+    # The pairs are added in the same order; the far fields are two FP64 sums
+    # of at most 40 decreasing terms, the shared one with a recurrence that
+    # damps its roundings eightfold at worst, so 1e-13 of the largest value
+    # covers 40 roundings of either twice.
+    f = wl.random_field(2000, 30.0, seed=nx + p, masses="powerlaw")
+    X, M = dev(f.xy), dev(f.m)
+    g = lf.Grid(-31.0, -30.5, 61.0 / nx, 60.0 / ny, nx, ny)
+    plan = lf.Plan(X, M, grid=g, precision=precision, p=p, leaf_level=leaf_level)
+    i, j = np.meshgrid(np.arange(nx), np.arange(ny))
+    r = np.stack([g.x0 + (i + 0.5) * g.dx, g.y0 + (j + 0.5) * g.dy], -1).reshape(-1, 2)
+    yg = lf.deflect(plan=plan, grid=g).reshape(-1, 2)
+    y = lf.deflect(plan=plan, rays=dev(r)).reshape(-1, 2)
+    assert float((y - yg).abs().max()) <= 1e-13 * float(y.abs().max())
+    # f' too (its terms grow by up to p against f's); y is the same bits with it
+    y2, dg = lf.deflect(plan=plan, grid=g, want_dfdz=True)
+    _, d = lf.deflect(plan=plan, rays=dev(r), want_dfdz=True)
+    assert torch.equal(y2.reshape(-1, 2), yg)
+    scale = max(float(d.abs().max()), float(y.abs().max()))
+    assert float((d.reshape(-1, 2) - dg.reshape(-1, 2)).abs().max()) <= 1e-13 * p * scale
+    # the same sums binned into a map
+    npix = 64
+    counts = lf.irs_map(plan=plan, grid=g, map=lf.MapDesc(-20.0, -20.0, 40.0, npix))
+    t = torch.floor((yg + 20.0) * (npix / 40.0)).long()
+    ok = ((t >= 0) & (t < npix)).all(1)
+    ref = torch.bincount(t[ok, 1] * npix + t[ok, 0], minlength=npix * npix).reshape(npix, npix)
+    assert int((counts.reshape(npix, npix) - ref).abs().sum()) <= 2
