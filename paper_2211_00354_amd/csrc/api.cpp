@@ -817,13 +817,21 @@ void gridexec_alloc(const lens_plan &P, const lens_grid &grid, int64_t j0, int64
     return std::max<int64_t>(1, std::min(n, cap));
   };
   int64_t tiles = 0;
-  const int64_t bw = per_box(grid.dx, grid.nx), bh = per_box(grid.dy, j1 - j0);
-  grid_tile_shape(bw, bh, &ea.tile_shift, &tiles);
+  grid_tile_shape(per_box(grid.dx, grid.nx), per_box(grid.dy, j1 - j0), &ea.tile_shift, &tiles);
   eval_shape(tiles * 64, &ea.rays_per_lane, &ea.chunks_per_box);
-  const int64_t lanes = 64 * ea.rays_per_lane;
-  if (!quad_shape(bw, bh, (tiles * 64 + lanes - 1) / lanes * lanes, &ea.quad_shift, &ea.quad_chunks) ||
-      wl.count() * ea.quad_chunks > (int64_t)0x7fffffff)
-    ea.quad_chunks = 0;
+  // mirror images: by the whole grid's boxes, whichever rows are evaluated
+  {
+    const int64_t bw = per_box(grid.dx, grid.nx), bh = per_box(grid.dy, grid.ny);
+    int sh = 0, R = 0;
+    int64_t all = 0, ch = 0;
+    grid_tile_shape(bw, bh, &sh, &all);
+    eval_shape(all * 64, &R, &ch);
+    if (!quad_shape(bw, bh, (all + R - 1) / R * R * 64, &ea.quad_shift, &ea.quad_chunks) ||
+        wl.count() * ea.quad_chunks > (int64_t)0x7fffffff)
+      ea.quad_chunks = 0;
+    ea.j_begin = j0;
+    ea.j_end = j1;
+  }
   while (wl.count() * ea.chunks_per_box > (int64_t)0x7fffffff && ea.chunks_per_box > 1)
     ea.chunks_per_box = (ea.chunks_per_box + 1) / 2;
   if (wl.count() > (int64_t)0x7fffffff) fail(LENS_EUNSUPPORTED, "leaf window too large");
@@ -845,7 +853,9 @@ void gridexec_enqueue(const lens_plan &P, GridExec &ge, double c1, double c2, do
     ea.S = (double)map->npix / map->side;
     ea.npix = map->npix;
   }
-  launch_grid_ranges(ea.grid, P.g, ea.win, ge.j0, ge.j1, const_cast<int32_t *>(ea.col_start),
+  const bool whole = ea.quad_chunks != 0;
+  launch_grid_ranges(ea.grid, P.g, ea.win, whole ? 0 : ge.j0, whole ? ea.grid.ny : ge.j1,
+                     const_cast<int32_t *>(ea.col_start),
                      const_cast<int32_t *>(ea.row_start), st);
   StageTimer tm(ea.counts ? "eval_map" : "eval", st);
   launch_eval(ea, P.precision, st);

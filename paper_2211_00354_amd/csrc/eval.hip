@@ -327,7 +327,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
 
     // the box's rays are columns [i0, i0+W) x rows [j0, j0+H); they (QUAD: the
     // quarter at the low corner) are cut into nt = TW x TH tiles, tpc
-    // consecutive tiles per unit
+    // consecutive tiles per unit.  QUAD: all rows of the box in the grid, of
+    // which those of the band [j_begin, j_end) are evaluated, so that a ray's
+    // bits don't depend on the bands that a call is cut into.
     const int32_t i0 = col_start[bxw], W = col_start[bxw + 1] - i0;
     const int32_t j0 = row_start[byw], H = row_start[byw + 1] - j0;
     const int32_t Wt = QUAD ? (W + 1) >> 1 : W, Ht = QUAD ? (H + 1) >> 1 : H;
@@ -365,6 +367,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
 
     // passes of R tiles, or of one tile and its three mirror images
     const int32_t pend = min(nt, (int32_t)c0 * tpc + tpc);
+    const bool cut = QUAD && (j0 < a.j_begin || j0 + H > a.j_end);
     int held = 0;  // passes whose counts the table holds
     for (int32_t pos = (int32_t)c0 * tpc; pos < pend; pos += QUAD ? 1 : R) {
       // slot r's column and row in the box (an inactive slot takes tile place
@@ -386,8 +389,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
           on = on && 2 * cj + 1 != H;
           cj = H - 1 - cj;
         }
-        return on;
+        return QUAD ? on && j0 + cj >= a.j_begin && j0 + cj < a.j_end : on;
       };
+      if (QUAD && cut) {  // nothing of this tile in the band (uniform)
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          int32_t ci, cj;
+          any = place(r, ci, cj) || any;
+        }
+        if (!__any(any)) continue;
+      }
       double rx[R], ry[R];
       using acc_t = typename std::conditional<MIXED, float, double>::type;
       acc_t ax[R], ay[R], dre[R], dim[R];

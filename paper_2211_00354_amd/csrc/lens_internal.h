@@ -271,7 +271,8 @@ struct EvalArgs {
   int rays_per_lane;          // grid: R rays held per lane (1..4), 64*R rays per pass
   int tile_shift;             // grid: a wave's 64 rays are a 2^tile_shift-wide tile
   int64_t quad_chunks;        // grid: units per leaf box where a lane's rays are mirror images
-  int quad_shift;             // (0: not so), and the tile shape in the box's quarter
+  int quad_shift;             // (0: not so), and the tile shape in the box's quarter;
+  int64_t j_begin, j_end;     // the rows evaluated (row_start then has the whole grid's)
   double c1, c2;              // (1 - kappa_s - gamma), (1 - kappa_s + gamma)
   double *y_out;              // [n][2] or nullptr
   double *dfdz_out;           // [n][2] f'(z) (deflection only) or nullptr

@@ -272,3 +272,26 @@ def test_mirrored_rays_match_points(lf, nx, ny, leaf_level, p, precision):
     ok = ((t >= 0) & (t < npix)).all(1)
     ref = torch.bincount(t[ok, 1] * npix + t[ok, 0], minlength=npix * npix).reshape(npix, npix)
     assert int((counts.reshape(npix, npix) - ref).abs().sum()) <= 2
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+def test_mirrored_rays_in_bands(lf, precision):
+    # a call cut into bands of rows (a caller's buffer that holds part of the
+    # locals) that end inside boxes of mirrored rays: the bits of the whole call
+    from paper_2211_00354_amd import _lib
+    f = wl.random_field(2000, 30.0, seed=3, masses="powerlaw")
+    g = lf.Grid(-31.0, -30.5, 61.0 / 521, 60.0 / 333, 521, 333)
+    plan = lf.Plan(dev(f.xy), dev(f.m), grid=g, precision=precision, p=12, leaf_level=4)
+    y, d = lf.deflect(plan=plan, grid=g, want_dfdz=True)
+    ran = 0
+    for kib in range(8, 96, 4):
+        ws = torch.empty(kib << 10, dtype=torch.uint8, device="cuda")
+        try:
+            yb, db = lf.deflect(plan=plan, grid=g, want_dfdz=True, workspace=ws)
+        except _lib.LensError as e:
+            assert e.status == _lib.LENS_ENOMEM
+            continue
+        ran += 1
+        assert torch.equal(y, yb) and torch.equal(d, db)
+        assert torch.equal(lf.deflect(plan=plan, grid=g, workspace=ws), y)
+    assert ran >= 4
