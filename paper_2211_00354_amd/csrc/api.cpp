@@ -826,9 +826,10 @@ void gridexec_alloc(const lens_plan &P, const lens_grid &grid, int64_t j0, int64
     int64_t all = 0, ch = 0;
     grid_tile_shape(bw, bh, &sh, &all);
     eval_shape(all * 64, &R, &ch);
-    if (!quad_shape(bw, bh, (all + R - 1) / R * R * 64, &ea.quad_shift, &ea.quad_chunks) ||
-        wl.count() * ea.quad_chunks > (int64_t)0x7fffffff)
+    if (!quad_shape(bw, bh, (all + R - 1) / R * R * 64, j1 - j0, &ea.quad_shift, &ea.quad_chunks))
       ea.quad_chunks = 0;
+    while (wl.count() * ea.quad_chunks > (int64_t)0x7fffffff && ea.quad_chunks > 1)
+      ea.quad_chunks = (ea.quad_chunks + 1) / 2;
     ea.j_begin = j0;
     ea.j_end = j1;
   }

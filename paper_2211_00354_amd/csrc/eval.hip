@@ -20,6 +20,8 @@
 //     and added to the map by segments of pixels.
 // Units are spread over a bounded grid; consecutive units (neighbouring
 // boxes, which share stars) go to the same XCD so that they share its L2.
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace lensfmm {
@@ -332,9 +334,21 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
     // bits don't depend on the bands that a call is cut into.
     const int32_t i0 = col_start[bxw], W = col_start[bxw + 1] - i0;
     const int32_t j0 = row_start[byw], H = row_start[byw + 1] - j0;
-    const int32_t Wt = QUAD ? (W + 1) >> 1 : W, Ht = QUAD ? (H + 1) >> 1 : H;
+    const int32_t Wt = QUAD ? (W + 1) >> 1 : W;
+    int32_t qa = 0, Ht = QUAD ? (H + 1) >> 1 : H;  // the rows [qa, Ht) hold tiles
+    bool cut = false;
+    if (QUAD) {
+      const int32_t ja = (int32_t)max(a.j_begin - j0, (int64_t)0), jb = (int32_t)min(a.j_end - j0, (int64_t)H);
+      cut = ja > 0 || jb < H;
+      if (cut) {  // the band's rows [ja, jb) of the quarter, and their images
+        const int32_t half = Ht;
+        const int32_t lo1 = ja, hi1 = min(jb, half), lo2 = max(H - jb, 0), hi2 = min(H - ja, half);
+        qa = min(lo1 < hi1 ? lo1 : half, lo2 < hi2 ? lo2 : half);
+        Ht = max(lo1 < hi1 ? hi1 : 0, lo2 < hi2 ? hi2 : 0);
+      }
+    }
     const int32_t TW = (Wt + TX - 1) >> tsh;
-    const int32_t nt = TW * ((Ht + TY - 1) / TY);
+    const int32_t nt = Ht > qa ? TW * ((Ht - qa + TY - 1) / TY) : 0;
     const int32_t tpc = (nt + (int32_t)CH - 1) / (int32_t)CH;
     if (nt == 0 || (int64_t)c0 * tpc >= nt) continue;  // uniform
 
@@ -367,7 +381,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
 
     // passes of R tiles, or of one tile and its three mirror images
     const int32_t pend = min(nt, (int32_t)c0 * tpc + tpc);
-    const bool cut = QUAD && (j0 < a.j_begin || j0 + H > a.j_end);
     int held = 0;  // passes whose counts the table holds
     for (int32_t pos = (int32_t)c0 * tpc; pos < pend; pos += QUAD ? 1 : R) {
       // slot r's column and row in the box (an inactive slot takes tile place
@@ -377,7 +390,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
         const int32_t t = QUAD ? pos : pos + r;  // wave-uniform tile index
         const int32_t ty = t / TW, tx = t - ty * TW;
         ci = tx * TX + lx;
-        cj = ty * TY + ly;
+        cj = qa + ty * TY + ly;
         bool on = t < pend && ci < Wt && cj < Ht;
         ci = on ? ci : 0;
         cj = on ? cj : 0;
@@ -816,11 +829,13 @@ void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles) {
 // the ordinary ones' lane slots.  ps per ray, mixed, p = 12, ordinary and mirrored:
 // 1.0 (boxes of 16^2 rays) 12.2, 9.9; 1.14 (25^2) 16.3, 15.5; 1.29 (33^2) 11.2,
 // 10.4; 1.33 (11^2) 46.1, 50.8, (23^2) 15.4, 15.7.
-bool quad_shape(int64_t W, int64_t H, int64_t slots, int *shift, int64_t *CH) {
+bool quad_shape(int64_t W, int64_t H, int64_t slots, int64_t rows, int *shift, int64_t *CH) {
   int64_t tiles = 0;
   grid_tile_shape((W + 1) / 2, (H + 1) / 2, shift, &tiles);
+  const bool use = 10 * (4 * kWave * tiles) <= 13 * slots;
+  grid_tile_shape((W + 1) / 2, std::min((H + 1) / 2, rows), shift, &tiles);
   *CH = (tiles + kPassesPerUnit - 1) / kPassesPerUnit;
-  return 10 * (4 * kWave * tiles) <= 13 * slots;
+  return use;
 }
 
 void launch_eval(const EvalArgs &a, int precision, hipStream_t stream) {

@@ -291,8 +291,9 @@ void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j
 void eval_shape(int64_t max_rays, int *R, int64_t *CH);
 void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles);
 // whether boxes of W x H rays, in `slots` lane slots otherwise, are better
-// evaluated four mirror images to a lane, and that form's shape
-bool quad_shape(int64_t W, int64_t H, int64_t slots, int *shift, int64_t *CH);
+// evaluated four mirror images to a lane, and that form's shape for bands of
+// `rows` rows (which no ray's bits depend on)
+bool quad_shape(int64_t W, int64_t H, int64_t slots, int64_t rows, int *shift, int64_t *CH);
 
 // Adjoint (adjoint.hip): gradients at stars from rays with complex charges
 struct AdjArgs {
