@@ -705,14 +705,6 @@ void fill_star_side(const lens_plan &P, Window wl, double *loc, EvalArgs &ea) {
   ea.leaf_start = static_cast<const int32_t *>(P.leaf_start.ptr);
 }
 
-void launch_eval_checked(EvalArgs &ea, int precision, hipStream_t st) {
-  while (ea.win.count() * ea.chunks_per_box > (int64_t)0x7fffffff && ea.chunks_per_box > 1)
-    ea.chunks_per_box = (ea.chunks_per_box + 1) / 2;
-  if (ea.win.count() > (int64_t)0x7fffffff) fail(LENS_EUNSUPPORTED, "leaf window too large");
-  StageTimer tm(ea.counts ? "eval_map" : "eval", st);
-  launch_eval(ea, precision, st);
-}
-
 template <typename F>
 lens_status guarded(F &&fn) {
   try {
