@@ -4,10 +4,13 @@
 //
 // A thread holds a ray; the stars are the same for every lane of a wave, so
 // they are read with scalar loads and used as scalar operands of the vector
-// instructions, ~14.5 issue slots a pair (0.37 ps; 0.41 with the stars
+// instructions, ~14 issue slots a pair (0.36 ps; 0.41 with the stars
 // broadcast from LDS tiles to two rays a thread).  Where the rays make too few
 // waves to fill the chip, a workgroup's four waves take a quarter of the stars
-// each for the same rays and add their sums in LDS.  Pairs with |x - x_i| = 0
+// each for the same rays and add their sums in LDS.  A wave that has its rays to
+// itself sums the same quarters one after another and adds them in the same
+// order, so that a ray's bits depend neither on the number of rays of a launch
+// nor on the passes that a call is cut into.  Pairs with |x - x_i| = 0
 // contribute exactly zero.
 #include "device_common.h"
 
@@ -17,6 +20,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
+constexpr int32_t kFewStars = 32;  // not shared out: a chain no longer than a launch's own time
 
 // DERIV also sums f'(z) = -sum m / (z - z_i)^2 (see the evaluation kernel).
 // SLICES: the stars are shared out over the workgroup's waves.
@@ -57,25 +61,33 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a, const double 
   };
   // star counts fit 31 bits
   const int32_t n = (int32_t)a.n_stars;
-  int32_t i = 0, end = n;
-  if (SLICES) {
-    i = (int32_t)((int64_t)n * wv / kWaves);
-    end = (int32_t)((int64_t)n * (wv + 1) / kWaves);
-  }
-  // four stars per step: their scalar loads issue together
-  for (; i + 4 <= end; i += 4) {
-    double sx[4], sy[4], m[4];
+  // sums over quarter w of the stars (of a few: all of them, or none); whole
+  // steps of four but for the last one's
+  auto first = [&](int w) -> int32_t {
+    if (w == 0 || w == kWaves) return w == 0 ? 0 : n;
+    return n < kFewStars ? n : (int32_t)((int64_t)n * w / kWaves) & ~3;
+  };
+  auto quarter = [&](int w) {
+    const int32_t i = first(w);
+    const double *xy = sxy + 2 * (int64_t)i, *mass = sm + i;
+    ax = ay = dre = dim = 0.0;
+    int32_t left = first(w + 1) - i;
+    // four stars per step: their scalar loads issue together
+    for (; left >= 4; left -= 4, xy += 8, mass += 4) {
+      double sx[4], sy[4], m[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      sx[q] = sxy[2 * (int64_t)(i + q)];
-      sy[q] = sxy[2 * (int64_t)(i + q) + 1];
-      m[q] = sm[i + q];
+      for (int q = 0; q < 4; ++q) {
+        sx[q] = xy[2 * q];
+        sy[q] = xy[2 * q + 1];
+        m[q] = mass[q];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) star(sx[q], sy[q], m[q]);
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) star(sx[q], sy[q], m[q]);
-  }
-  for (; i < end; ++i) star(sxy[2 * (int64_t)i], sxy[2 * (int64_t)i + 1], sm[i]);
+    for (; left > 0; --left, xy += 2, ++mass) star(xy[0], xy[1], mass[0]);
+  };
   if constexpr (SLICES) {
+    quarter(wv);
     double *o = part + (wv > 0 ? wv - 1 : 0) * V * 64 + lane;
     if (wv > 0) {
       o[0] = ax;
@@ -95,6 +107,23 @@ __global__ __launch_bounds__(kThreads) void k_direct(DirectArgs a, const double 
         dre += o[128];
         dim += o[192];
       }
+    }
+  } else {
+    quarter(0);
+    if (n >= kFewStars) {
+      double sax = ax, say = ay, sre = dre, sim = dim;
+#pragma unroll 1
+      for (int w = 1; w < kWaves; ++w) {
+        quarter(w);
+        sax += ax;
+        say += ay;
+        sre += dre;
+        sim += dim;
+      }
+      ax = sax;
+      ay = say;
+      dre = sre;
+      dim = sim;
     }
   }
   if (!act) return;
@@ -140,8 +169,8 @@ void direct_launch(const DirectArgs &a, hipStream_t stream) {
 
 // Rays that fill the chip (8192 waves: two workgroups a SIMD) with a wave's
 // rays each to itself; fewer share the stars out over four waves (1000 stars,
-// whole call: 512^2 rays 120 us against 124, 256^2 39 against 88, 64^2 20
-// against 85).
+// whole call: 512^2 rays 104 us against 121, 256^2 31 against 56, 64^2 15
+// against 57).
 constexpr int64_t kFewRays = 64 * 8192;
 
 }  // namespace

@@ -295,3 +295,22 @@ def test_mirrored_rays_in_bands(lf, precision):
         assert torch.equal(y, yb) and torch.equal(d, db)
         assert torch.equal(lf.deflect(plan=plan, grid=g, workspace=ws), y)
     assert ran >= 4
+
+
+@pytest.mark.parametrize("n", [3, 31, 32, 35, 1000])
+def test_direct_sum_does_not_depend_on_the_passes(lf, n):
+    # 716800 rays at once (a wave's rays to itself) and in passes on the other
+    # side of 524288 (the stars shared over four waves): equal bits
+    f = wl.random_field(n, 10.0, seed=70 + n, masses="powerlaw", kappa_s=0.1, gamma=0.2)
+    X, M = dev(f.xy), dev(f.m)
+    g = lf.Grid(-6.0, -6.0, 12.0 / 1024, 12.0 / 700, 1024, 700)
+    kw = dict(kappa_s=0.1, gamma=0.2, method="direct")
+    y = lf.deflect(X, M, grid=g, **kw)
+    i, j = np.meshgrid(np.arange(g.nx), np.arange(g.ny))
+    rays = dev(np.stack([g.x0 + (i + 0.5) * g.dx, g.y0 + (j + 0.5) * g.dy], -1).reshape(-1, 2))
+    parts = [lf.deflect(X, M, rays=rays[k:k + 300000], **kw) for k in range(0, len(rays), 300000)]
+    assert torch.equal(torch.cat(parts), y)
+    npix = 257
+    ipm = dict(grid=g, map=lf.MapDesc(-4.0, -4.0, 8.0, npix), **kw)
+    assert torch.equal(lf.ipm_map(X, M, **ipm), lf.ipm_map(X, M, max_rays_per_chunk=200 * 1024, **ipm))
+    assert torch.equal(lf.irs_map(X, M, **ipm), lf.irs_map(X, M, max_rays_per_chunk=200 * 1024, **ipm))
