@@ -172,16 +172,23 @@ void direct_launch(const DirectArgs &a, hipStream_t stream) {
 // whole call: 512^2 rays 104 us against 121, 256^2 31 against 56, 64^2 15
 // against 57).
 constexpr int64_t kFewRays = 64 * 8192;
+// A launch takes fewer than 2^32 threads.
+constexpr int64_t kMaxRays = int64_t(1) << 31;
 
 }  // namespace
 
 void launch_direct(const DirectArgs &a, hipStream_t stream) {
   if (a.n_rays == 0) return;
-  if (a.n_rays <= kFewRays)
-    direct_launch<true>(a, stream);
-  else
-    direct_launch<false>(a, stream);
-  LENS_HIP(hipGetLastError());
+  DirectArgs part = a;
+  for (int64_t at = 0; at < a.n_rays; at += kMaxRays) {
+    part.ray_offset = a.ray_offset + at;
+    part.n_rays = a.n_rays - at < kMaxRays ? a.n_rays - at : kMaxRays;
+    if (part.n_rays <= kFewRays)
+      direct_launch<true>(part, stream);
+    else
+      direct_launch<false>(part, stream);
+    LENS_HIP(hipGetLastError());
+  }
 }
 
 }  // namespace lensfmm

@@ -314,3 +314,23 @@ def test_direct_sum_does_not_depend_on_the_passes(lf, n):
     ipm = dict(grid=g, map=lf.MapDesc(-4.0, -4.0, 8.0, npix), **kw)
     assert torch.equal(lf.ipm_map(X, M, **ipm), lf.ipm_map(X, M, max_rays_per_chunk=200 * 1024, **ipm))
     assert torch.equal(lf.irs_map(X, M, **ipm), lf.irs_map(X, M, max_rays_per_chunk=200 * 1024, **ipm))
+
+
+def test_direct_sum_of_almost_2_32_rays(lf):
+    # a launch takes fewer than 2^32 threads: 2^32 - 4 rays (the most a call
+    # takes are 2^32 - 2) without stars, 64 GiB of y, are more than one
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 64 GiB of device memory")
+    nx, ny = (1 << 30) - 1, 4
+    n = nx * ny
+    g = lf.Grid(-1.0, -2.0, 2.0 / nx, 1.0, nx, ny)
+    none = torch.empty((0, 2), dtype=torch.float64, device="cuda")
+    y = torch.full((n, 2), float("nan"), dtype=torch.float64, device="cuda")
+    lf.deflect(none, none[:, 0].contiguous(), grid=g, gamma=0.25, out=y)
+    for k in (0, nx, (1 << 31) - 1, 1 << 31, (1 << 31) + 256, n - 257, n - 1):
+        i, j = k % nx, k // nx
+        x = ((g.x0 + (i + 0.5) * g.dx) * 0.75, (g.y0 + (j + 0.5) * g.dy) * 1.25)
+        assert tuple(y[k].tolist()) == x
+    assert not bool(torch.isnan(y[:: 1 << 12, 0]).any())
+    del y
+    torch.cuda.empty_cache()
