@@ -236,10 +236,12 @@ void adj_dispatch(const EvalArgs &a, const AdjArgs &d, hipStream_t stream) {
   // pass, mixed: 1e5 stars on 1e6 rays within a tenth of their radius 6.7 ms
   // with one lane, 1.1 with sixteen (a wave to a box: 4.3); half of the rays
   // within 1/60 of it 47 and 14 ms with four; even rays pay 259 against 286 us.
+  // A launch takes fewer than 2^32 threads.
   const double groups = 9.0 * d.per_box / kFlushSources;
-  if (groups >= 16.0 || d.nt <= kHeldLanes / 16)
+  const auto fits = [&](int64_t split) { return d.nt * split <= (int64_t(1) << 32) - kThreads; };
+  if ((groups >= 16.0 || d.nt <= kHeldLanes / 16) && fits(16))
     adj_launch<MIXED, 16>(a, d, stream);
-  else if (groups >= 4.0 || d.nt <= kHeldLanes / 4)
+  else if ((groups >= 4.0 || d.nt <= kHeldLanes / 4) && fits(4))
     adj_launch<MIXED, 4>(a, d, stream);
   else
     adj_launch<MIXED, 1>(a, d, stream);

@@ -334,3 +334,29 @@ def test_direct_sum_of_almost_2_32_rays(lf):
     assert not bool(torch.isnan(y[:: 1 << 12, 0]).any())
     del y
     torch.cuda.empty_cache()
+
+
+def test_adjoint_of_2_28_stars(lf):
+    # sixteen lanes to a star would be 2^32 threads, which no launch takes: 2^28
+    # stars on 8192 rays in 16 boxes, against the backward pass of a few of them
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs about 40 GiB of device memory")
+    n = 1 << 28
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    xy = torch.rand((n, 2), generator=gen, dtype=torch.float64, device="cuda").mul_(64.0).sub_(32.0)
+    m = torch.ones(n, dtype=torch.float64, device="cuda")
+    rays = torch.rand((8192, 2), generator=gen, dtype=torch.float64, device="cuda").mul_(64.0).sub_(32.0)
+    g = torch.randn((8192, 2), generator=gen, dtype=torch.float64, device="cuda")
+    kw = dict(rays=rays, precision="fp64", p=24, leaf_level=2)
+    gx, gm = lf.deflect_backward(xy, m, g, **kw)
+    k = torch.arange(0, n, 65537, device="cuda")
+    few = (xy[k].contiguous(), m[k].contiguous())
+    rx, rm = lf.deflect_backward(*few, g, method="direct", rays=rays)
+    # each star against the size of its own sums; truncation 4 * 0.55^24 of them
+    d2 = torch.cdist(few[0], rays) ** 2
+    size = g.norm(dim=1)
+    tol = 4 * 0.55 ** 24
+    assert bool(((gm[k] - rm).abs() <= tol * (size / d2.sqrt()).sum(1)).all())
+    assert bool(((gx[k] - rx).norm(dim=1) <= 24 * tol * (size / d2).sum(1)).all())
+    del xy, m, gx, gm
+    torch.cuda.empty_cache()
