@@ -24,7 +24,6 @@ namespace lensfmm {
 
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kThreads = 256;
 constexpr int32_t kFlushSources = 128;  // LENS_MIXED near-field partials per FP64 flush
 constexpr int64_t kHeldLanes = 1 << 19;  // lanes of k_eval_adj the chip holds at once, about
@@ -108,14 +107,15 @@ __global__ __launch_bounds__(kThreads) void k_eval_adj(
   double Sr = 0.0, Si = 0.0, Tr = 0.0, Ti = 0.0;
   acc_t hr[1] = {0}, hi[1] = {0}, pr[1] = {0}, pi[1] = {0};
   for (int32_t g = part; (int64_t)g * kFlushSources < n; g += SPLIT) {
-    int32_t k = g * kFlushSources;
-    const int32_t end = min(n, k + kFlushSources);
+    // (unsigned: a place may pass 2^31 by a step)
+    uint32_t k = (uint32_t)g * kFlushSources;
+    const uint32_t end = min((uint32_t)n, k + kFlushSources);
     // the next four sources' loads are issued before the current four pairs
     double2 nz[4], nq[4];
-    auto fetch = [&](int32_t q0) {
+    auto fetch = [&](uint32_t q0) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int32_t q = min(q0 + j, end - 1);
+      for (uint32_t j = 0; j < 4; ++j) {
+        const int32_t q = (int32_t)min(q0 + j, end - 1);
         const int32_t i = q >= pre[2] ? rs[2] + (q - pre[2]) : (q >= pre[1] ? rs[1] + (q - pre[1]) : rs[0] + q);
         nz[j] = sz[i];
         nq[j] = sg[i];
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void k_eval_adj(
       for (int j = 0; j < 4; ++j) z[j] = nz[j], q[j] = nq[j];
       fetch(k + 4);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (uint32_t j = 0; j < 4; ++j)
         if (k + j < end) adj_pair<MIXED, 1>(tx, ty, z[j].x, z[j].y, q[j].x, q[j].y, hr, hi, pr, pi);
     }
     if (MIXED) {
