@@ -31,7 +31,8 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kXcd = 8;
 constexpr int32_t kFlushStars = 128;  // LENS_MIXED near-field partials per FP64 flush
-constexpr int kThreads = 256;  // helper kernels
+constexpr int kThreads = 256;  // explicit rays, helper kernels
+constexpr int64_t kManyLanes = 1 << 18;  // half the lanes of k_eval_rays that the chip holds
 
 
 // One star against the R rays of a lane.  The pair difference x - x_i is
@@ -588,17 +589,19 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
   }
 }
 
-// Explicit rays, a lane to a ray: neighbouring rays (sorted by leaf box) in
-// neighbouring lanes, each with its own box's locals and stars, so that no lane
+// Explicit rays, SPLIT lanes to a ray and neighbouring rays (sorted by leaf box)
+// in neighbouring lanes, each with its own box's locals and stars, so that no lane
 // is idle where boxes hold few rays, and none waits where some hold many.  Bound
 // by the stars' loads, of which a lane keeps four in flight behind the four that
-// it works on.  Whole calls, mixed, a wave to a box before, now: 1e3 stars and
-// 1e6 rays 1249, 165 us; 1e4 and 1e5 119, 119; 1e5 and 1e6 225, 219; 1e6 and 1e5
-// 406, 306; 1e3 stars and 1e3 rays, one chain's latency, 72, 77 (as much as the
-// sort's box starts, which only the other form needed, took).  Each ray meets the
-// stars in the order of k_eval and moves its FP32 sums at the same stars (those
-// of whole steps of four count, per row of the neighbourhood): the same bits.
-template <bool MIXED, bool DERIV>
+// it works on.  The stars of a ray's neighbourhood are summed in groups, each by
+// one lane, and the groups' sums are added in FP64 in their order, so that a ray's
+// bits do not depend on SPLIT.  A group ends where k_eval moves its FP32 sums:
+// with the 32nd whole step of four stars (steps do not reach over a row's end), in
+// FP64 with the 64th.  Whole calls, mixed, a wave to a box before, now: 1e3 stars
+// and 1e6 rays 1249, 153 us; 1e4 and 1e5 119, 119; 1e5 and 1e6 225, 200; 1e6 and
+// 1e5 406, 290; 1e3 stars and 1e3 rays, one chain's latency, 72, 76 (as much as
+// the sort's box starts, which only the other form needed, took).
+template <bool MIXED, bool DERIV, int SPLIT>
 __global__ __launch_bounds__(kThreads) void k_eval_rays(EvalArgs a, int64_t n, const double2 *__restrict__ loc,
                                                         const double2 *__restrict__ sz,
                                                         const double *__restrict__ sm,
@@ -608,9 +611,11 @@ __global__ __launch_bounds__(kThreads) void k_eval_rays(EvalArgs a, int64_t n, c
                                                         const uint32_t *__restrict__ rperm,
                                                         double2 *__restrict__ y_out) {
   using acc_t = typename std::conditional<MIXED, float, double>::type;
+  constexpr int32_t kSteps = (MIXED ? kFlushStars : 2 * kFlushStars) / 4;
   const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const bool act = gid < n;
-  const int64_t t = act ? gid : n - 1;
+  const int part = (int)(gid % SPLIT);
+  const bool act = gid / SPLIT < n;
+  const int64_t t = act ? gid / SPLIT : n - 1;
   const int64_t nL = int64_t(1) << a.g.L;
   const double s = ldexp(a.g.side, -a.g.L);
   const double inv_s = 1.0 / s;
@@ -636,49 +641,59 @@ __global__ __launch_bounds__(kThreads) void k_eval_rays(EvalArgs a, int64_t n, c
     pre[d + 1] = pre[d] + (re - rs[d]);
   }
   const int32_t ns = pre[3];
-  const double rx[1] = {z.x}, ry[1] = {z.y};
-  acc_t ax[1] = {0}, ay[1] = {0}, dre[1] = {0}, dim[1] = {0};
-  double Sx = 0.0, Sy = 0.0, Tr = 0.0, Ti = 0.0;
-  int32_t since = 0;
-  double2 nz[4];
-  acc_t nm[4];
-  int32_t nk[4];  // place in its row, or -1 beyond the last star
-  auto fetch = [&](int32_t q0) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int32_t q = min(q0 + j, ns - 1);
-      const int d = q >= pre[2] ? 2 : (q >= pre[1] ? 1 : 0);
-      const int32_t k = q - (d == 2 ? pre[2] : (d == 1 ? pre[1] : 0));
-      const int32_t i = k + (d == 2 ? rs[2] : (d == 1 ? rs[1] : rs[0]));
-      nk[j] = q0 + j < ns ? k : -1;
-      nz[j] = sz[i];
-      if constexpr (MIXED) nm[j] = sm32[i]; else nm[j] = sm[i];
-    }
+  // whole steps up to the end of each row, and the last group
+  const int32_t w1 = pre[1] >> 2, w2 = w1 + ((pre[2] - pre[1]) >> 2), w3 = w2 + ((ns - pre[2]) >> 2);
+  const int32_t last = w3 / kSteps;
+  // group g's first star (a place in the three rows together)
+  auto first = [&](int32_t g) -> uint32_t {
+    const int32_t w = g * kSteps;  // the whole steps before it
+    if (w == 0) return 0u;
+    return 4u * (uint32_t)w + (w > w2 ? pre[2] - 4 * w2 : (w > w1 ? pre[1] - 4 * w1 : 0));
   };
-  if (ns > 0) fetch(0);
-  for (int32_t q0 = 0; q0 < ns; q0 += 4) {
-    double2 cz[4];
-    acc_t cm[4];
-    int32_t ck[4];
+  const double rx[1] = {z.x}, ry[1] = {z.y};
+  double Sx = 0.0, Sy = 0.0, Tr = 0.0, Ti = 0.0;
+  for (int32_t g0 = 0; g0 <= last; g0 += SPLIT) {
+    const int32_t g = g0 + part;
+    acc_t ax[1] = {0}, ay[1] = {0}, dre[1] = {0}, dim[1] = {0};
+    uint32_t k = g <= last ? first(g) : 0u;
+    const uint32_t end = g < last ? first(g + 1) : (g == last ? (uint32_t)ns : 0u);
+    double2 nz[4];
+    acc_t nm[4];
+    auto fetch = [&](uint32_t q0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cz[j] = nz[j], cm[j] = nm[j], ck[j] = nk[j];
-    fetch(q0 + 4);
+      for (uint32_t j = 0; j < 4; ++j) {
+        const int32_t q = (int32_t)min(q0 + j, end - 1);
+        const int32_t i = q >= pre[2] ? rs[2] + (q - pre[2]) : (q >= pre[1] ? rs[1] + (q - pre[1]) : rs[0] + q);
+        nz[j] = sz[i];
+        if constexpr (MIXED) nm[j] = sm32[i]; else nm[j] = sm[i];
+      }
+    };
+    if (k < end) fetch(k);
+    for (; k < end; k += 4) {
+      double2 cz[4];
+      acc_t cm[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (ck[j] < 0) continue;
-      pair_update<MIXED, DERIV, 1>(rx, ry, cz[j].x, cz[j].y, cm[j], ax, ay, dre, dim);
-      if (MIXED && (ck[j] & 3) == 3) {
-        since += 4;
-        if (since >= kFlushStars) {
-          since = 0;
-          Sx += (double)ax[0];
-          Sy += (double)ay[0];
-          ax[0] = ay[0] = 0;
-          if (DERIV) {
-            Tr += (double)dre[0];
-            Ti += (double)dim[0];
-            dre[0] = dim[0] = 0;
-          }
+      for (int j = 0; j < 4; ++j) cz[j] = nz[j], cm[j] = nm[j];
+      fetch(k + 4);
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j)
+        if (k + j < end) pair_update<MIXED, DERIV, 1>(rx, ry, cz[j].x, cz[j].y, cm[j], ax, ay, dre, dim);
+    }
+    if (SPLIT == 1 || last == 0) {  // (one group: lane 0's)
+      Sx += (double)ax[0];
+      Sy += (double)ay[0];
+      if (DERIV) {
+        Tr += (double)dre[0];
+        Ti += (double)dim[0];
+      }
+    } else {  // the lanes of a ray go round together
+#pragma unroll
+      for (int q = 0; q < SPLIT; ++q) {
+        Sx += (double)__shfl(ax[0], q, SPLIT);
+        Sy += (double)__shfl(ay[0], q, SPLIT);
+        if (DERIV) {
+          Tr += (double)__shfl(dre[0], q, SPLIT);
+          Ti += (double)__shfl(dim[0], q, SPLIT);
         }
       }
     }
@@ -694,13 +709,12 @@ __global__ __launch_bounds__(kThreads) void k_eval_rays(EvalArgs a, int64_t n, c
     if (DERIV) gd = cmad(gd, w, f);
     f = cmad(f, w, cplx{c.x, c.y});
   }
-  if (!act) return;
+  if (!act || part != 0) return;
   const int64_t o = rperm[t];
-  y_out[o] = make_double2(a.c1 * z.x - (f.re + ((double)ax[0] + Sx)),
-                          a.c2 * z.y - (((double)ay[0] + Sy) - f.im));
+  y_out[o] = make_double2(a.c1 * z.x - (f.re + Sx), a.c2 * z.y - (Sy - f.im));
   if (DERIV)
     reinterpret_cast<double2 *>(a.dfdz_out)[o] =
-        make_double2(fma(gd.re, inv_s, (double)dre[0] + Tr), fma(gd.im, inv_s, (double)dim[0] + Ti));
+        make_double2(fma(gd.re, inv_s, Tr), fma(gd.im, inv_s, Ti));
 }
 
 // first ray column (row) of every box column (row) of the window: columns in
@@ -846,13 +860,29 @@ void launch_eval(const EvalArgs &a, int precision, hipStream_t stream) {
   LENS_HIP(hipGetLastError());
 }
 
-template <bool MIXED>
+template <bool MIXED, int SPLIT>
 void eval_rays(const EvalArgs &a, int64_t n, hipStream_t stream) {
-  auto *kernel = a.dfdz_out ? k_eval_rays<MIXED, true> : k_eval_rays<MIXED, false>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a, n,
-                     reinterpret_cast<const double2 *>(a.loc), reinterpret_cast<const double2 *>(a.sxy), a.sm,
-                     a.sm32, a.leaf_start, reinterpret_cast<const double2 *>(a.rxy), a.rperm,
+  auto *kernel = a.dfdz_out ? k_eval_rays<MIXED, true, SPLIT> : k_eval_rays<MIXED, false, SPLIT>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((n * SPLIT + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream,
+                     a, n, reinterpret_cast<const double2 *>(a.loc), reinterpret_cast<const double2 *>(a.sxy),
+                     a.sm, a.sm32, a.leaf_start, reinterpret_cast<const double2 *>(a.rxy), a.rperm,
                      reinterpret_cast<double2 *>(a.y_out));
+}
+
+// Lanes to a ray: as many as fill half of the chip with few rays, whose longest
+// chain of stars is all that counts then (five clusters of 2e5 stars, mixed: 300
+// rays 4.8 ms with one lane, 0.6 with sixteen; 30000 rays 4.8 ms with one, 1.3 with
+// four, 0.9 with sixteen).  More rays would pay for the far field that a ray's lanes
+// all sum: 30000 rays on 1e4 uniform stars in FP64 104 us with four lanes, 119 with
+// sixteen; 1e5 rays on 1e5 stars 132 with one, 155 with four.
+template <bool MIXED>
+void eval_rays_dispatch(const EvalArgs &a, int64_t n, hipStream_t stream) {
+  if (n <= kManyLanes / 32)
+    eval_rays<MIXED, 16>(a, n, stream);
+  else if (n <= kManyLanes / 4)
+    eval_rays<MIXED, 4>(a, n, stream);
+  else
+    eval_rays<MIXED, 1>(a, n, stream);
 }
 
 void launch_eval_rays(const EvalArgs &a, int64_t n, int precision, hipStream_t stream) {
@@ -860,9 +890,9 @@ void launch_eval_rays(const EvalArgs &a, int64_t n, int precision, hipStream_t s
   if (precision == LENS_MIXED && !a.sm32)
     fail(LENS_EINVAL, "mixed-precision evaluation needs the plan's FP32 masses");
   if (precision == LENS_MIXED)
-    eval_rays<true>(a, n, stream);
+    eval_rays_dispatch<true>(a, n, stream);
   else
-    eval_rays<false>(a, n, stream);
+    eval_rays_dispatch<false>(a, n, stream);
   LENS_HIP(hipGetLastError());
 }
 

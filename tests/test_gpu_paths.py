@@ -360,3 +360,28 @@ def test_adjoint_of_2_28_stars(lf):
     assert bool(((gx[k] - rx).norm(dim=1) <= 24 * tol * (size / d2).sum(1)).all())
     del xy, m, gx, gm
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("n,leaf_level", [(1, 2), (130, 2), (1500, 2), (20000, 3), (20000, 6)])
+def test_explicit_rays_do_not_depend_on_their_number(lf, n, leaf_level, precision):
+    # one, four and sixteen lanes to a ray (70000, 65536 and 8192 rays), whose
+    # neighbourhoods hold no star to thousands: groups of stars that end before,
+    # at and after the end of a row, the last one empty or not.  Equal bits.
+    f = wl.random_field(n, 30.0, seed=n + leaf_level, masses="powerlaw")
+    xy = f.xy.copy()
+    xy[: n // 2] *= 0.1
+    X, M = dev(xy), dev(f.m)
+    plan = lf.Plan(X, M, ray_box=(-32.0, -32.0, 32.0, 32.0), precision=precision, p=12, leaf_level=leaf_level)
+    rays = dev(np.random.default_rng(n).uniform(-31, 31, (70000, 2)))
+    ref = lf.deflect(plan=plan, rays=rays, want_dfdz=True)
+    for part in (65536, 8192, 5000):
+        for deriv in (False, True):
+            r = rays[:part].contiguous()
+            got = lf.deflect(plan=plan, rays=r, want_dfdz=True) if deriv else (lf.deflect(plan=plan, rays=r),)
+            for a, b in zip(got, ref):
+                assert torch.equal(a, b[:part])
+    # and the direct sum's values: pairs of 2^-24 (2^-53) of their size each, the
+    # truncation 0.55^12 of the far field's
+    direct = lf.deflect(X, M, rays=rays[:5000].contiguous(), method="direct")
+    assert float((ref[0][:5000] - direct).norm() / direct.norm()) < 4 * 0.55 ** 12
