@@ -873,7 +873,7 @@ void fmm_grid_rows(lens_plan &P, const lens_grid &grid, int64_t j0, int64_t j1, 
 
 // Explicit rays: sorted by leaf box of the window, evaluated box by box,
 // written back in the caller's order.  The downward pass over the window of
-// bb is separate: the image finder's Newton steps share it.
+// bb is separate: the image finder's iterations share it.
 struct ExplicitLocals {
   Window wl;
   double *loc = nullptr;
@@ -2592,6 +2592,14 @@ lens_status lens_autotune(const lens_field *field, const lens_grid *grid, const 
   });
 }
 
+namespace {
+// Candidates up to which a wave each iterates them all in one launch; more are
+// sorted and evaluated as explicit rays, a lane each, at every iteration.  Whole
+// calls, wave, lane: FP64 p = 24, 9.2e3 images 3.9, 5.6 ms, 2.3e4 9.1, 8.6, 9.4e4
+// 38, 26; mixed p = 12, 3.7e3 1.46, 1.64, 9.2e3 2.98, 2.89, 9.4e4 30, 21.
+constexpr int64_t wave_candidates(int precision) { return precision == LENS_MIXED ? 8192 : 16384; }
+}  // namespace
+
 lens_status lens_find_images(lens_plan *plan, const lens_field *field, const lens_grid *grid,
                              const double *sources, int32_t n_sources, double tol, int32_t max_iter,
                              double *images, int32_t *image_src, int64_t cap, int64_t *n_images,
@@ -2671,14 +2679,14 @@ lens_status lens_find_images(lens_plan *plan, const lens_field *field, const len
       NewtonArgs na{n, cand_x, cand_s, sources, nullptr, nullptr, c1, c2, tol,
                     4.0 * std::hypot(grid->dx, grid->dy), {gbb[0], gbb[1], gbb[2], gbb[3]},
                     nullptr, nullptr, nullptr, 1};
-      if (P) {
-        const ExplicitLocals el = explicit_locals(*P, gbb, sc, st);
+      ExplicitLocals el;
+      if (P) el = explicit_locals(*P, gbb, sc, st);
+      if (P && n <= wave_candidates(P->precision)) {
         EvalArgs ea{};
         fill_star_side(*P, el.wl, el.loc, ea);
         // iterations per launch: a few first (most sources converge in
-        // them), then up to 64, in at most 64 MB of history
-        const int64_t room = std::max<int64_t>(1, (int64_t(1) << 26) / (32 * n));
-        const int64_t most = std::min<int64_t>({room, 64, (int64_t)max_iter + 1});
+        // them), then up to 64 (at most 32 MB of history)
+        const int64_t most = std::min<int64_t>(64, (int64_t)max_iter + 1);
         NewtonHistory h{};
         h.x = sc.get<double>((size_t)(most * n) * 2);
         h.res = sc.get<double>((size_t)(most * n));
@@ -2712,17 +2720,21 @@ lens_status lens_find_images(lens_plan *plan, const lens_field *field, const len
         fdet = na.det = sc.get<double>((size_t)n);
         na.unconverged = sc.get<uint32_t>(1);
         for (int it = 0; it <= max_iter; ++it) {
-          DirectArgs d{};
-          d.n_stars = fv.f.n_stars;
-          d.sxy = fv.f.xy;
-          d.sm = fv.f.m;
-          d.rxy = cand_x;
-          d.n_rays = n;
-          d.c1 = c1;
-          d.c2 = c2;
-          d.y_out = yc;
-          d.dfdz_out = dc;
-          launch_direct(d, st);
+          if (P) {
+            fmm_explicit_eval(*P, el, cand_x, n, c1, c2, yc, st, dc);
+          } else {
+            DirectArgs d{};
+            d.n_stars = fv.f.n_stars;
+            d.sxy = fv.f.xy;
+            d.sm = fv.f.m;
+            d.rxy = cand_x;
+            d.n_rays = n;
+            d.c1 = c1;
+            d.c2 = c2;
+            d.y_out = yc;
+            d.dfdz_out = dc;
+            launch_direct(d, st);
+          }
           launch_fill_u32(na.unconverged, 1, 0u, st);
           na.step = it < max_iter;
           StageTimer tm("images", st);

@@ -103,7 +103,8 @@ __device__ __forceinline__ double newton_step(const NewtonArgs &a, double r0, do
   return det;
 }
 
-// One Newton step per candidate from y(x) and f'(x) (the direct sum's).  res
+// One Newton step per candidate from y(x) and f'(x) (the direct sum's, or those
+// of many candidates as explicit rays).  res
 // receives |beta - y| at the x the step started from; *unconverged counts
 // those above tol.
 __global__ __launch_bounds__(kThreads) void k_newton(NewtonArgs a) {
@@ -127,7 +128,8 @@ __global__ __launch_bounds__(kThreads) void k_newton(NewtonArgs a) {
 // so the caller can stop at the first iteration that leaves none.  (A launch
 // per stage of each iteration -- sort the candidates by box, evaluate, step,
 // read the count back -- took 110 us an iteration for ~1000 candidates; this
-// kernel takes about 3.)
+// kernel takes about 3.  Its lanes all sum the same expansion, so many candidates
+// are better off with a lane each: see wave_candidates.)
 template <bool MIXED>
 __global__ __launch_bounds__(64) void k_newton_fmm(NewtonArgs a, EvalArgs e, NewtonHistory h) {
   const int lane = threadIdx.x;

@@ -385,3 +385,27 @@ def test_explicit_rays_do_not_depend_on_their_number(lf, n, leaf_level, precisio
     # truncation 0.55^12 of the far field's
     direct = lf.deflect(X, M, rays=rays[:5000].contiguous(), method="direct")
     assert float((ref[0][:5000] - direct).norm() / direct.norm()) < 4 * 0.55 ** 12
+
+
+@pytest.mark.parametrize("precision,p,tol,n_src", [("fp64", 30, 1e-9, 24), ("mixed", 16, 1e-4, 12)])
+def test_images_of_many_candidates(lf, precision, p, tol, n_src):
+    # ~900 candidates a source: all of them are more than a wave each takes, four
+    # sources' are not.  The same images (but for those that converge only just),
+    # each as far from the other form's as the residuals allow: 2 tol |mu|.
+    f = wl.random_field(1000, 30.0, seed=52, gamma=0.1)
+    g = lf.Grid(-32.0, -32.0, 0.125, 0.125, 512, 512)
+    plan = lf.Plan(dev(f.xy), dev(f.m), grid=g, precision=precision, p=p)
+    src = dev(np.random.default_rng(4).uniform(-3, 3, (n_src, 2)))
+    kw = dict(plan=plan, grid=g, gamma=0.1, precision=precision, p=p, tol=tol)
+    img, s = (t.cpu().numpy() for t in lf.find_images(sources=src, **kw))
+    assert len(img) > (16384 if precision == "fp64" else 8192)
+    odd = 0
+    for k in range(0, n_src, 4):
+        ref, rs = (t.cpu().numpy() for t in lf.find_images(sources=src[k:k + 4].contiguous(), **kw))
+        for j in range(4):
+            a, b = img[s == k + j], ref[rs == j]
+            d = np.hypot(a[:, None, 0] - b[None, :, 0], a[:, None, 1] - b[None, :, 1])
+            ok = np.abs(b[:, 2]) < 1e3
+            near = d.min(0) <= 2 * tol * np.maximum(1.0, np.abs(b[:, 2])) * 4
+            odd += int((~near & ok).sum()) + abs(len(a) - len(b))
+    assert odd <= len(img) // 1000
