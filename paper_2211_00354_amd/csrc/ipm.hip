@@ -667,12 +667,16 @@ __device__ __forceinline__ int32_t wave_excl_scan(int32_t x, int lane, int32_t &
 // 18.1 with a wave per cell, an atomic per pixel and difference, and every
 // edge twice: it ran at the chip's 23.7e9 atomic requests a second.)
 //
-// Sixteen queued cells per wave and batch: four lanes of each classify it,
+// Up to sixteen queued cells per wave and batch: four lanes of each classify it,
 // one edge to a lane (with the neighbour across it), and write the edges to be
 // rasterised -- the quadrilateral's, or a folded cell's two lobes' -- to a
 // table in LDS; the wave's lanes then take the table's items in turn: the rows
 // of steep edges, four lanes each, the columns of flat ones, and their rows.
-// Waves pull batches in a fixed stride and exit past the queue's end.
+// Waves pull batches in a fixed stride and exit past the queue's end.  A cell can
+// be a thousand pixels wide, so a queue of few batches is shared out: up to sixteen
+// waves form the same table and take a share of its items each (256^2 rays into
+// 4000^2 pixels, 50 stars: 1300 us a call with a wave per batch, 380 so; a wave per
+// cell and every edge twice 525).
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_wide(
     IpmArgs a) {
   __shared__ EdgeJob jobs_all[kThreads / 64][kMaxJobs];
@@ -685,10 +689,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const int64_t ncx = a.nx - 1;
   const uint32_t waves = gridDim.x * (kThreads / 64);
   const int e = lane & 3, sub = lane & 3;
-  const uint64_t step = (uint64_t)waves * kBatch;
-  uint64_t base = (uint64_t)(blockIdx.x * (kThreads / 64) + wv) * kBatch;
+  // a short queue: several waves to a batch, an equal share of its items each
+  const uint32_t parts = min(16u, max(1u, waves / max(1u, (nq + kBatch - 1) / kBatch))), teams = waves / parts;
+  const uint32_t batch = min((uint32_t)kBatch, (nq + teams - 1) / teams);
+  const uint32_t wave = blockIdx.x * (kThreads / 64) + wv, team = wave / parts;
+  const int32_t part = (int32_t)(wave % parts);
+  const uint64_t step = (uint64_t)teams * batch;
+  uint64_t base = team < teams ? (uint64_t)team * batch : nq;
   for (; base < nq; base += step) {
-    const bool on = base + (lane >> 2) < nq;
+    const bool on = (uint32_t)(lane >> 2) < batch && base + (lane >> 2) < nq;
     const uint32_t id = a.queue[on ? base + (lane >> 2) : base];
     const int64_t i = (int64_t)(id % (uint64_t)ncx), j = a.j0 + (int64_t)(id / (uint64_t)ncx);
     Cell c;
@@ -770,17 +779,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     wave_sync();
     // a lane's items grow, so its job is found by walking on
     int jb = 0;
-    for (int32_t t = lane >> 2; t < totals[0]; t += 16) {
+    for (int32_t t = (lane >> 2) + 16 * part; t < totals[0]; t += 16 * (int32_t)parts) {
       while (first[0][jb + 1] <= t) ++jb;
       row_item(jobs[jb], jobs[jb].r0 + (t - first[0][jb]), sub, a);
     }
     jb = 0;
-    for (int32_t t = lane; t < totals[1]; t += 64) {
+    for (int32_t t = lane + 64 * part; t < totals[1]; t += 64 * (int32_t)parts) {
       while (first[1][jb + 1] <= t) ++jb;
       column_item(jobs[jb], first[2][jb + 1] - first[2][jb], jobs[jb].c0 + (t - first[1][jb]), a);
     }
     jb = 0;
-    for (int32_t t = lane; t < totals[2]; t += 64) {
+    for (int32_t t = lane + 64 * part; t < totals[2]; t += 64 * (int32_t)parts) {
       while (first[2][jb + 1] <= t) ++jb;
       flat_row_item(jobs[jb], jobs[jb].r0 + (t - first[2][jb]), a);
     }

@@ -409,3 +409,23 @@ def test_images_of_many_candidates(lf, precision, p, tol, n_src):
             near = d.min(0) <= 2 * tol * np.maximum(1.0, np.abs(b[:, 2])) * 4
             odd += int((~near & ok).sum()) + abs(len(a) - len(b))
     assert odd <= len(img) // 1000
+
+
+@pytest.mark.parametrize("rows", [1, 2, 5, 40])
+def test_ipm_short_queues(lf, rows):
+    # wide cells (up to hundreds of pixels) in passes of a few rows of cells, whose
+    # queues of tens to thousands of cells are shared out over 16 waves to one;
+    # sums of integers, so the whole call's bits, and the oracle's values
+    import oracle
+    f, g, _ = wl.small_disk()
+    grid = lf.Grid(g.x0, g.y0, g.dx, g.dy, g.nx, g.ny)
+    npix = 700
+    md = lf.MapDesc(-1.5, -1.4, 3.0, npix)
+    kw = dict(grid=grid, map=md, kappa_s=f.kappa_s, gamma=f.gamma, method="direct")
+    xy, m = dev(f.xy), dev(f.m)
+    mu = lf.ipm_map(xy, m, **kw)
+    assert torch.equal(mu, lf.ipm_map(xy, m, max_rays_per_chunk=(rows + 1) * g.nx, **kw))
+    if rows == 1:
+        y = lf.deflect(xy, m, grid=grid, kappa_s=f.kappa_s, gamma=f.gamma, method="direct").cpu().numpy()
+        ref = oracle.ipm(y.reshape(g.ny, g.nx, 2), g.dx * g.dy, md.y1min, md.y2min, md.side, npix)
+        assert np.abs(mu.cpu().numpy() - ref).max() <= 1e-9 * max(1.0, ref.max())
