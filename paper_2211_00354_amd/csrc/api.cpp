@@ -760,6 +760,32 @@ size_t gridexec_bytes(const lens_plan &P, const lens_grid &grid, int64_t j0, int
   return total;
 }
 
+// The largest power of two that v is a multiple of.
+double binary_unit(double v) {
+  if (v == 0.0) return std::numeric_limits<double>::max();
+  int e = 0;
+  const uint64_t m = (uint64_t)std::ldexp(std::frexp(std::fabs(v), &e), 53);
+  return std::ldexp(1.0, e - 53 + __builtin_ctzll(m));
+}
+
+// Whether the coordinates x0 + (i + 1/2) dx and the sums of two of them are
+// exact: then rays that lie symmetrically in index lie so in position.
+bool exact_coords(double x0, double dx, int64_t n) {
+  const double unit = std::fmin(binary_unit(x0), 0.5 * binary_unit(dx));
+  return std::fmax(std::fabs(x0), std::fabs(x0 + (double)n * dx)) <= 0x1p52 * unit;
+}
+
+// Whether rays may be evaluated as mirror images: an image's place differs
+// from the ray's by the roundings of their coordinates.  FP64 allows none;
+// LENS_MIXED as many as stay far below the 2^-24 of its pairs (2^-36 of a leaf
+// side s).
+bool rays_mirror(const lens_grid &g, double s, int precision) {
+  if (exact_coords(g.x0, g.dx, g.nx) && exact_coords(g.y0, g.dy, g.ny)) return true;
+  const double far = std::fmax(std::fmax(std::fabs(g.x0), std::fabs(g.x0 + (double)g.nx * g.dx)),
+                               std::fmax(std::fabs(g.y0), std::fabs(g.y0 + (double)g.ny * g.dy)));
+  return precision == LENS_MIXED && far * 0x1p-52 <= s * 0x1p-36;
+}
+
 // Windows, buffers and launch shape of grid rows [j0, j1).  Buffers come
 // from the pool, or, if `region` is given, are carved from it in order
 // (gridexec_bytes of them; the GridExec then owns nothing).
@@ -818,7 +844,8 @@ void gridexec_alloc(const lens_plan &P, const lens_grid &grid, int64_t j0, int64
     int64_t all = 0, ch = 0;
     grid_tile_shape(bw, bh, &sh, &all);
     eval_shape(all * 64, &R, &ch);
-    if (!quad_shape(bw, bh, (all + R - 1) / R * R * 64, j1 - j0, &ea.quad_shift, &ea.quad_chunks))
+    if (!quad_shape(bw, bh, (all + R - 1) / R * R * 64, j1 - j0, &ea.quad_shift, &ea.quad_chunks) ||
+        !rays_mirror(grid, s, P.precision))
       ea.quad_chunks = 0;
     while (wl.count() * ea.quad_chunks > (int64_t)0x7fffffff && ea.quad_chunks > 1)
       ea.quad_chunks = (ea.quad_chunks + 1) / 2;

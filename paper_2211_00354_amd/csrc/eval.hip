@@ -175,8 +175,8 @@ __device__ __forceinline__ bool map_table_flush(MapTable &t, int above, int32_t 
 }
 
 // QUAD: a lane's four rays are mirror images of each other in the centre lines
-// of the box's rays (any grid: the expansion b is first moved to that centre,
-// unless the two agree but for rounding), at w, -conj w, conj w and -w.  With
+// of the box's rays (the expansion b is first moved to that centre, unless the two
+// agree, in LENS_MIXED but for rounding), at w, -conj w, conj w and -w.  With
 // z = w^2, f(w) = E(z) + w O(z) from the even and the odd coefficients, and
 // P(z) = (c_0 - |z|^2 B_2) + z B_1 with the real recurrence
 // B_k = c_k + 2 Re(z) B_k+1 - |z|^2 B_k+2 serves conj z as well: 4 p FMAs for the
@@ -185,7 +185,7 @@ __device__ __forceinline__ bool map_table_flush(MapTable &t, int above, int32_t 
 // two columns and two rows, so a star costs them four differences, not eight.
 // 1e6 stars, 8192^2 rays, p = 12: 343 to 250 million VALU instructions, 700 to
 // 560 us.
-constexpr double kSameCentre = 0x1p-50;
+constexpr double kSameCentre = 0x1p-50;  // LENS_MIXED
 
 struct InverseInts {
   double v[LENS_MAX_ORDER + 1];
@@ -376,7 +376,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(MIXED && 
       // the expansion about the centre of the box's rays
       const double ccx = 0.5 * (grid_coord(a.grid.x0, a.grid.dx, i0) + grid_coord(a.grid.x0, a.grid.dx, i0 + W - 1));
       const double ccy = 0.5 * (grid_coord(a.grid.y0, a.grid.dy, j0) + grid_coord(a.grid.y0, a.grid.dy, j0 + H - 1));
-      if (fabs(ccx - cx) > kSameCentre * fabs(cx) || fabs(ccy - cy) > kSameCentre * fabs(cy))
+      constexpr double same = MIXED ? kSameCentre : 0.0;
+      if (fabs(ccx - cx) > same * fabs(cx) || fabs(ccy - cy) > same * fabs(cy))
         shift_local(lds_loc, p, cplx{(ccx - cx) * inv_s, (ccy - cy) * inv_s}, lane);
     }
 

@@ -429,3 +429,27 @@ def test_ipm_short_queues(lf, rows):
         y = lf.deflect(xy, m, grid=grid, kappa_s=f.kappa_s, gamma=f.gamma, method="direct").cpu().numpy()
         ref = oracle.ipm(y.reshape(g.ny, g.nx, 2), g.dx * g.dy, md.y1min, md.y2min, md.side, npix)
         assert np.abs(mu.cpu().numpy() - ref).max() <= 1e-9 * max(1.0, ref.max())
+
+
+@pytest.mark.parametrize("p", [24, 40])
+@pytest.mark.parametrize("off", [0.0, 3.0e5, 1.0e8])
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("nx,ny,leaf_level", [(256, 256, 3), (250, 250, 3), (1001, 777, 4)])
+def test_mirrored_rays_far_from_the_origin(lf, nx, ny, leaf_level, aligned, off, p):
+    # FP64: rays in boxes that the mirrored form fits, with exact coordinates
+    # (256^2) and rounded ones, on boxes aligned with them and on others, against
+    # the same rays as points.  y = -alpha; the pairs agree in all but the order of
+    # their sums and the far fields are two sums of at most 40 terms at the same
+    # place, so the bound of the rays near the origin holds wherever they are.
+    f = wl.random_field(2000, 30.0, seed=nx + p, masses="powerlaw")
+    xy = f.xy + off
+    g = lf.Grid(off - 31.0, off - 30.5, 61.0 / nx, 60.0 / ny, nx, ny)
+    where = {"grid": g} if aligned else {"ray_box": (off - 31.7, off - 31.3, off + 31.1, off + 30.9)}
+    plan = lf.Plan(dev(xy), dev(f.m), precision="fp64", p=p, leaf_level=leaf_level, **where)
+    i, j = np.meshgrid(np.arange(nx), np.arange(ny))
+    r = dev(np.stack([g.x0 + (i + 0.5) * g.dx, g.y0 + (j + 0.5) * g.dy], -1).reshape(-1, 2))
+    yg, dg = lf.deflect(plan=plan, grid=g, kappa_s=1.0, want_dfdz=True)
+    y, d = lf.deflect(plan=plan, rays=r, kappa_s=1.0, want_dfdz=True)
+    assert float((y - yg).abs().max()) <= 1e-13 * float(y.abs().max())
+    scale = max(float(d.abs().max()), float(y.abs().max()))
+    assert float((d - dg).abs().max()) <= 1e-13 * p * scale
