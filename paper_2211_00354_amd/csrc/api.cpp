@@ -839,12 +839,11 @@ void gridexec_alloc(const lens_plan &P, const lens_grid &grid, int64_t j0, int64
   eval_shape(tiles * 64, &ea.rays_per_lane, &ea.chunks_per_box);
   // mirror images: by the whole grid's boxes, whichever rows are evaluated
   {
-    const int64_t bw = per_box(grid.dx, grid.nx), bh = per_box(grid.dy, grid.ny);
-    int sh = 0, R = 0;
-    int64_t all = 0, ch = 0;
-    grid_tile_shape(bw, bh, &sh, &all);
-    eval_shape(all * 64, &R, &ch);
-    if (!quad_shape(bw, bh, (all + R - 1) / R * R * 64, j1 - j0, &ea.quad_shift, &ea.quad_chunks) ||
+    auto mostly = [&](double step, int64_t cap) {  // the rays of most boxes
+      return std::max<int64_t>(1, std::min((int64_t)std::floor(s / step + 0.5), cap));
+    };
+    if (!quad_shape(mostly(grid.dx, grid.nx), mostly(grid.dy, grid.ny), per_box(grid.dx, grid.nx),
+                    per_box(grid.dy, grid.ny), j1 - j0, &ea.quad_shift, &ea.quad_chunks) ||
         !rays_mirror(grid, s, P.precision))
       ea.quad_chunks = 0;
     while (wl.count() * ea.quad_chunks > (int64_t)0x7fffffff && ea.quad_chunks > 1)

@@ -840,16 +840,31 @@ void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles) {
   *tiles = best_t;
 }
 
-// Four mirror images to a lane where the quarter's tiles take at most 1.3 times
-// the ordinary ones' lane slots.  ps per ray, mixed, p = 12, ordinary and mirrored:
-// 1.0 (boxes of 16^2 rays) 12.2, 9.9; 1.14 (25^2) 16.3, 15.5; 1.29 (33^2) 11.2,
-// 10.4; 1.33 (11^2) 46.1, 50.8, (23^2) 15.4, 15.7.
-bool quad_shape(int64_t W, int64_t H, int64_t slots, int64_t rows, int *shift, int64_t *CH) {
-  int64_t tiles = 0;
-  grid_tile_shape((W + 1) / 2, (H + 1) / 2, shift, &tiles);
-  const bool use = 10 * (4 * kWave * tiles) <= 13 * slots;
-  grid_tile_shape((W + 1) / 2, std::min((H + 1) / 2, rows), shift, &tiles);
-  *CH = (tiles + kPassesPerUnit - 1) / kPassesPerUnit;
+// Four mirror images to a lane where the slots of its units, filled or not, in a
+// box of W x H rays are at most 1.15 times the ordinary form's (the units are shaped
+// for at most Wmax x Hmax rays), unless the quarter makes two short units of 9 to 12
+// passes.  Speed of the mirrored form over the ordinary one, p = 4 to 24, 1 to 20
+// stars a box, 1024 to 16384 boxes (y in mixed precision | in FP64 | y and f' in
+// either): ratio 1 (boxes of 16^2, 32^2, 63^2 rays) 1.0 to 1.3 | 1.0 to 1.15 | 0.9 to
+// 1.2; 1.04 to 1.14 (49^2, 56^2, 100^2) 0.95 to 1.6 | 0.9 to 1.5 | 0.8 to 1.4; 1.33
+// (24^2, 65^2) 0.94 to 1.36 | 0.83 to 1.2 | 0.83 to 1.2; 1.43 (33^2 to 36^2) 1.0 to
+// 1.1 | 0.84 to 1.06 | 0.76 to 1.06; two short units (48^2) 0.94 to 1.06 | 0.86 to
+// 0.94 | 0.7 to 0.9.
+bool quad_shape(int64_t W, int64_t H, int64_t Wmax, int64_t Hmax, int64_t rows, int *shift, int64_t *CH) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  auto tiles_of = [&](int64_t w, int64_t h) { return up(w, int64_t(1) << *shift) * up(h, kWave >> *shift); };
+  int64_t most = 0, ch = 0;
+  int R = 0;
+  grid_tile_shape(Wmax, Hmax, shift, &most);
+  eval_shape(most * kWave, &R, &ch);
+  const int64_t ordinary = ch * up(up(tiles_of(W, H), ch), R) * R;
+  grid_tile_shape((Wmax + 1) / 2, (Hmax + 1) / 2, shift, &most);
+  const int64_t quarter = tiles_of((W + 1) / 2, (H + 1) / 2);
+  ch = up(most, kPassesPerUnit);
+  const int64_t mirrored = 4 * ch * up(quarter, ch);
+  const bool use = 100 * mirrored <= 115 * ordinary && !(quarter > 8 && quarter <= 12);
+  grid_tile_shape((Wmax + 1) / 2, std::min((Hmax + 1) / 2, rows), shift, &most);
+  *CH = up(most, kPassesPerUnit);
   return use;
 }
 

@@ -290,10 +290,10 @@ void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j
                         int64_t j_end, int32_t *col_start, int32_t *row_start, hipStream_t stream);
 void eval_shape(int64_t max_rays, int *R, int64_t *CH);
 void grid_tile_shape(int64_t W, int64_t H, int *shift, int64_t *tiles);
-// whether boxes of W x H rays, in `slots` lane slots otherwise, are better
-// evaluated four mirror images to a lane, and that form's shape for bands of
-// `rows` rows (which no ray's bits depend on)
-bool quad_shape(int64_t W, int64_t H, int64_t slots, int64_t rows, int *shift, int64_t *CH);
+// whether boxes of mostly W x H and at most Wmax x Hmax rays are better evaluated
+// four mirror images to a lane, and that form's shape for bands of `rows` rows
+// (which no ray's bits depend on)
+bool quad_shape(int64_t W, int64_t H, int64_t Wmax, int64_t Hmax, int64_t rows, int *shift, int64_t *CH);
 
 // Adjoint (adjoint.hip): gradients at stars from rays with complex charges
 struct AdjArgs {
