@@ -436,7 +436,8 @@ void plan_geometry(lens_plan *P, int64_t n_sources, const double *sb, const doub
   source_windows(P);
 }
 
-// Plan phase 2: every device buffer the tree build and the upward pass use.
+// Plan phase 2: every device buffer the tree build and the upward pass use, but
+// for the sort's records.
 void plan_alloc(lens_plan *P, hipStream_t st) {
   const int L = P->g.L;
   const int64_t nbox = int64_t(1) << (2 * L);
@@ -450,7 +451,6 @@ void plan_alloc(lens_plan *P, hipStream_t st) {
   for (DevBuf *b : {&P->keys, &P->vals, &P->keys_tmp, &P->vals_tmp})
     *b = pool_get((size_t)N * sizeof(uint32_t), st);
   P->cnt = pool_get(radix_counts_len(N) * sizeof(uint32_t), st);
-  if (tree_rec_len(N)) P->rec = pool_get(tree_rec_len(N) * sizeof(double), st);
   P->box_coarse = pool_get((size_t)box_starts_coarse_len(nbox) * sizeof(int32_t), st);
   for (int l = 2; l <= L; ++l) {
     const size_t n = (size_t)P->swin[l].count() * P->p * 2;
@@ -491,6 +491,20 @@ void plan_tree(lens_plan *P, const double *xy, const double *q, hipStream_t st) 
 
 void plan_enqueue(lens_plan *P, const double *xy, const double *q, hipStream_t st) {
   plan_tree(P, xy, q, st);
+  plan_upward(P, st);
+}
+
+// The sort's packed records (32 bytes a source, for many of them).  A captured
+// plan keeps them, as its replays write them.
+void plan_records(lens_plan *P, hipStream_t st) {
+  if (tree_rec_len(P->n_stars)) P->rec = pool_get(tree_rec_len(P->n_stars) * sizeof(double), st);
+}
+
+// Phase 3 eagerly: the records go back to the pool behind the sort.
+void plan_build(lens_plan *P, const double *xy, const double *q, hipStream_t st) {
+  plan_records(P, st);
+  plan_tree(P, xy, q, st);
+  pool_put(P->rec, st);
   plan_upward(P, st);
 }
 
@@ -579,7 +593,7 @@ lens_plan *build_plan(const lens_field &f, const double *ray_box, const lens_gri
     plan_geometry(P, f.n_stars, sbp, ray_box, align, rays_density, o, rho_local);
     (void)op_tables(o.order_p, st);
     plan_alloc(P, st);
-    plan_enqueue(P, f.xy, qc ? qc : f.m, st);
+    plan_build(P, f.xy, qc ? qc : f.m, st);
   } catch (...) {
     P->release();
     delete P;
@@ -1557,6 +1571,9 @@ std::unique_ptr<BatchExec> batch_build(int n, const lens_field *f, const lens_gr
                      total < (int64_t)std::numeric_limits<int32_t>::max();
   uint32_t *mk = nullptr, *mv = nullptr, *mkt = nullptr, *mvt = nullptr, *mcnt = nullptr;
   TreeJob *jobs_dev = nullptr;
+  if (!multi)
+    for (lens_plan *P : B->plans)
+      if (P) plan_records(P, st);
   if (multi) {
     auto grab = [&](size_t bytes) {
       B->tree.push_back(pool_get(bytes, st));
@@ -1856,6 +1873,7 @@ void fmm_grid_call(const lens_field &f, const lens_grid &grid, const lens_opts &
   std::copy(sb, sb + 4, P->star_bb);
   (void)op_tables(o.order_p, st);
   plan_alloc(P, st);
+  plan_records(P, st);
   gridexec_alloc(*P, grid, 0, grid.ny, c->ge, st);
   LENS_HIP(hipStreamCreateWithFlags(&c->origin, hipStreamNonBlocking));
   LENS_HIP(hipStreamSynchronize(st));  // the buffers above were handed out on st
@@ -2321,7 +2339,7 @@ void backward_with_plan(lens_plan &F, const double *rays, int64_t n_rays, const 
     std::copy(rb, rb + 4, A->star_bb);
     source_windows(A);
     plan_alloc(A, st);
-    plan_enqueue(A, rays, grad_y, st);
+    plan_build(A, rays, grad_y, st);
     double *loc = nullptr;
     const Window wl = downward(*A, F.star_bb, sc, st, &loc);
     EvalArgs ea{};

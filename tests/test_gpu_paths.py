@@ -453,3 +453,25 @@ def test_mirrored_rays_far_from_the_origin(lf, nx, ny, leaf_level, aligned, off,
     assert float((y - yg).abs().max()) <= 1e-13 * float(y.abs().max())
     scale = max(float(d.abs().max()), float(y.abs().max()))
     assert float((d - dg).abs().max()) <= 1e-13 * p * scale
+
+
+def test_plans_keep_no_sort_records(lf):
+    # of the packed records of a sort (32 bytes a star from 2^19 stars on) a plan
+    # keeps none: the second of two plans takes its stars (28 bytes), the sort's
+    # keys and values (16) and its boxes, and less where the pool has blocks
+    n = 1 << 22
+    xy = torch.rand((n, 2), dtype=torch.float64, device="cuda")
+    m = torch.ones(n, dtype=torch.float64, device="cuda")
+    plans = [lf.Plan(xy, m, ray_box=(0.0, 0.0, 1.0, 1.0), p=2, leaf_level=7)]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        free = torch.cuda.mem_get_info()[0]
+        plans.append(lf.Plan(xy, m, ray_box=(0.0, 0.0, 1.0, 1.0), p=2, leaf_level=7))
+        torch.cuda.synchronize()
+        assert free - torch.cuda.mem_get_info()[0] <= 48 * n
+    # the sorts shared the records; each has its own stars
+    g = lf.Grid(0.25, 0.25, 0.01, 0.01, 8, 8)
+    y = [lf.deflect(plan=p, grid=g) for p in plans]
+    assert all(torch.equal(y[0], other) for other in y[1:])
+    for p in plans:
+        p.close()
