@@ -475,3 +475,34 @@ def test_plans_keep_no_sort_records(lf):
     assert all(torch.equal(y[0], other) for other in y[1:])
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("precision,p,eps", [("mixed", 20, 2.0 ** -24), ("fp64", 28, 2.0 ** -53)])
+@pytest.mark.parametrize("n,n_rays,radius", [
+    (300, 30000, 30.0), (16385, 20000, 30.0), (40000, 30000, 4.0), (65537, 20000, 3.0), (140000, 30000, 30.0)])
+def test_adjoint_star_by_star(lf, n, n_rays, radius, precision, p, eps):
+    # one, four and sixteen lanes to a star, each star against the size of its own
+    # sums, sum |g| / |d| and m sum |g| / |d|^2 (a norm over all stars is that of a
+    # few close pairs).  A pair carries a few roundings of its size; the far field
+    # is truncated at 0.55^p of it, its derivative's terms grow by p.
+    f = wl.random_field(n, 30.0, seed=n + 1, masses="powerlaw")
+    rng = np.random.default_rng(n_rays + n)
+    rays = (rng.random((n_rays, 2)) - 0.5) * 2 * radius
+    X, M, r = dev(f.xy), dev(f.m), dev(rays)
+    g = dev(rng.standard_normal((n_rays, 2)))
+    rx, rm = lf.deflect_backward(X, M, g, rays=r, method="direct")
+    plan = lf.Plan(X, M, ray_box=(-31.0, -31.0, 31.0, 31.0), precision=precision, p=p)
+    got = (lf.deflect_backward(X, M, g, rays=r, precision=precision, p=p),
+           lf.deflect_backward(None, None, g, rays=r, plan=plan))
+    tol = 4 * 0.55 ** p + 64 * eps
+    size = g.norm(dim=1)
+    for a in range(0, n, 2000):
+        k = slice(a, min(n, a + 2000))
+        d = r[None] - X[k, None]
+        d2 = (d * d).sum(-1)
+        s1, s2 = (size / d2.sqrt()).sum(1), M[k] * (size / d2).sum(1)
+        for gx, gm in got:
+            assert bool(((gm[k] - rm[k]).abs() <= tol * s1).all())
+            assert bool(((gx[k] - rx[k]).norm(dim=1) <= p * tol * s2).all())
+        # the bound tells zero and a wrong sign from the gradient
+        assert float((rx[k].norm(dim=1) > 2 * p * tol * s2).double().mean()) > 0.9
