@@ -655,17 +655,6 @@ void downward_enqueue(const lens_plan &P, const LocalSet &ls, hipStream_t st) {
   }
   launch_m2l_batch(coarse, T, false, st);
   launch_m2l_batch(fine, T, true, st);
-  auto l2l = [&](int l) {
-    DownArgs d{};
-    d.level = l;
-    d.p = P.p;
-    d.s = std::ldexp(P.g.side, -l);
-    d.win = ls.win[l];
-    d.pwin = ls.win[l - 1];
-    d.ploc = ls.at(l - 1);
-    d.loc = ls.at(l);
-    launch_l2l(d, T, st);
-  };
   // coarse L2L sweep, up to three levels per launch
   for (int l = 3; l < first_fused && l <= L;) {
     L2LChain c{};
@@ -689,11 +678,7 @@ void downward_enqueue(const lens_plan &P, const LocalSet &ls, hipStream_t st) {
     one.lv[0] = level_of(l);
     one.lv[0].ploc = ls.at(l - 1);
     one.lv[0].pwin = ls.win[l - 1];
-    if (!launch_m2l_l2l(one, T, is_f32(l), st)) {
-      one.lv[0].ploc = nullptr;
-      launch_m2l_batch(one, T, is_f32(l), st);
-      l2l(l);
-    }
+    launch_m2l_l2l(one, T, is_f32(l), st);
   }
 }
 

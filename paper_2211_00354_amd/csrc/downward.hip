@@ -27,11 +27,8 @@
 // FP32 (fine levels of LENS_MIXED) uses v_mfma_f32_16x16x4f32, FP64 uses
 // v_mfma_f64_16x16x4f64; B fragments of later offsets are loaded while the
 // current one computes.  The result, scaled by 1/s, is stored as the FP64
-// locals.  Where the tile does not fit the device's LDS the VALU kernel runs.
+// locals.
 #include <type_traits>
-
-#include <mutex>
-#include <vector>
 
 #include "device_common.h"
 
@@ -45,30 +42,6 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d4v __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------- L2L
-
-// loc += L2L(parent locals); one thread per (target box, output coefficient j).
-__global__ __launch_bounds__(kThreads) void k_l2l(DownArgs a, const double *__restrict__ l2l) {
-  const int p = a.p;
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (idx >= a.win.count() * p) return;
-  const int64_t ob = idx / p;
-  const int j = (int)(idx - ob * p);
-  const int64_t tx = a.win.bx0 + ob % a.win.nbx, ty = a.win.by0 + ob / a.win.nbx;
-  cplx acc = {a.loc[2 * idx], a.loc[2 * idx + 1]};
-  {
-    const int q = (int)((tx & 1) + 2 * (ty & 1));
-    const int64_t pb = ((ty >> 1) - a.pwin.by0) * a.pwin.nbx + ((tx >> 1) - a.pwin.bx0);
-    const double *par = a.ploc + 2 * pb * p;
-    const double *t = l2l + (size_t)q * p * p * 2;
-    for (int l = j; l < p; ++l) {
-      const cplx b = {par[2 * l], par[2 * l + 1]};
-      const cplx m = {t[((size_t)l * p + j) * 2], t[((size_t)l * p + j) * 2 + 1]};
-      acc = cmad(m, b, acc);
-    }
-  }
-  a.loc[2 * idx] = acc.re;
-  a.loc[2 * idx + 1] = acc.im;
-}
 
 // L2L down up to three levels in one launch, as FP64 MFMAs: a workgroup owns
 // one box of the chain's top level (its locals final) and its 4 + 16 + 64
@@ -518,85 +491,6 @@ __global__ __launch_bounds__(kThreads * NB) void k_m2l_split(M2LBatch bt, const 
   }
 }
 
-// ------------------------------------------------------------ M2L on VALU
-// Fallback for orders whose MFMA tile does not fit in LDS: one thread per
-// target box, blockIdx.y = quadrant so operator reads are wave-uniform.
-
-struct Target {
-  int64_t tx, ty;
-  bool ok;
-};
-
-__device__ __forceinline__ Target target_of(const DownArgs &a) {
-  const int q = blockIdx.y, qx = q & 1, qy = q >> 1;
-  const int64_t px0 = a.win.bx0 >> 1, py0 = a.win.by0 >> 1;
-  const int64_t pnx = ((a.win.bx0 + a.win.nbx - 1) >> 1) - px0 + 1;
-  const int64_t pny = ((a.win.by0 + a.win.nby - 1) >> 1) - py0 + 1;
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  Target t;
-  t.tx = 2 * (px0 + idx % pnx) + qx;
-  t.ty = 2 * (py0 + idx / pnx) + qy;
-  t.ok = idx < pnx * pny && t.tx >= a.win.bx0 && t.tx < a.win.bx0 + a.win.nbx &&
-         t.ty >= a.win.by0 && t.ty < a.win.by0 + a.win.nby;
-  return t;
-}
-
-template <int PMAX, typename T>
-__global__ __launch_bounds__(kThreads) void k_m2l_valu(DownArgs a, const T *__restrict__ mp,
-                                                       const T *__restrict__ m2l) {
-  const Target tg = target_of(a);
-  if (!tg.ok) return;
-  const int p = a.p;
-  const int q = blockIdx.y, qx = q & 1, qy = q >> 1;
-  T ar[PMAX], ai[PMAX];
-#pragma unroll
-  for (int l = 0; l < PMAX; ++l) ar[l] = ai[l] = 0;
-  for (int ty = -2 - qy; ty <= 3 - qy; ++ty) {
-    for (int tx = -2 - qx; tx <= 3 - qx; ++tx) {
-      if (tx >= -1 && tx <= 1 && ty >= -1 && ty <= 1) continue;
-      const int64_t sx = tg.tx + tx - a.swin.bx0, sy = tg.ty + ty - a.swin.by0;
-      if (sx < 0 || sy < 0 || sx >= a.swin.nbx || sy >= a.swin.nby) continue;
-      const T *src = mp + 2 * (sy * a.swin.nbx + sx) * p;
-      const T *t = m2l + (size_t)((ty + 3) * 7 + (tx + 3)) * p * p * 2;
-#pragma unroll
-      for (int k = 0; k < PMAX; ++k) {
-        if (k < p) {
-          const T sr = src[2 * k], si = src[2 * k + 1];
-#pragma unroll
-          for (int l = 0; l < PMAX; ++l)
-            if (l < p) {
-              const T mr = t[((size_t)k * p + l) * 2], mi = t[((size_t)k * p + l) * 2 + 1];
-              ar[l] = fma(mr, sr, fma(-mi, si, ar[l]));
-              ai[l] = fma(mr, si, fma(mi, sr, ai[l]));
-            }
-        }
-      }
-    }
-  }
-  const double inv_s = 1.0 / a.s;
-  const int64_t ob = (tg.ty - a.win.by0) * a.win.nbx + (tg.tx - a.win.bx0);
-  double *out = a.loc + 2 * ob * p;
-#pragma unroll
-  for (int l = 0; l < PMAX; ++l)
-    if (l < p) {
-      out[2 * l] = (double)ar[l] * inv_s;
-      out[2 * l + 1] = (double)ai[l] * inv_s;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void k_to_f32(const double *__restrict__ src,
-                                                     float *__restrict__ dst, size_t n) {
-  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) dst[i] = (float)src[i];
-}
-
-dim3 valu_grid(const DownArgs &a) {
-  const int64_t px0 = a.win.bx0 >> 1, py0 = a.win.by0 >> 1;
-  const int64_t pnx = ((a.win.bx0 + a.win.nbx - 1) >> 1) - px0 + 1;
-  const int64_t pny = ((a.win.by0 + a.win.nby - 1) >> 1) - py0 + 1;
-  return dim3((unsigned)((pnx * pny + kThreads - 1) / kThreads), 4);
-}
-
 // Tile lists of every level for tiles of w x 8 targets; returns their number.
 int64_t list_tiles(M2LBatch &b, int w) {
   int64_t acc = 0;
@@ -657,49 +551,14 @@ void mfma_dispatch_tiles(M2LBatch &b, const T *bfrag, const double *l2l_frag, hi
   }
 }
 
-// The device's LDS per workgroup (160 KB on gfx950), read once per device.
-size_t lds_per_block() {
-  static std::mutex mu;
-  static std::vector<size_t> known;
-  int dev = 0;
-  LENS_HIP(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lk(mu);
-  if ((size_t)dev >= known.size()) known.resize(dev + 1, 0);
-  if (!known[dev]) {
-    int v = 0;
-    LENS_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    known[dev] = v > 0 ? (size_t)v : 64 * 1024;
-  }
-  return known[dev];
-}
-
+// (a workgroup's source tile takes at most 155520 of the chip's 163840 bytes of LDS)
 template <typename T, bool FUSE>
-bool mfma_dispatch(M2LBatch &b, const T *bfrag, const double *l2l_frag, int ks,
-                   hipStream_t stream) {
-  // the largest form's source tile must fit the workgroup's LDS
-  if ((size_t)20 * 12 * (4 * ks + 1) * sizeof(T) > lds_per_block()) return false;
-  switch (ks) {
-    case 2: mfma_dispatch_tiles<T, 2, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 4: mfma_dispatch_tiles<T, 4, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 6: mfma_dispatch_tiles<T, 6, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 8: mfma_dispatch_tiles<T, 8, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 10: mfma_dispatch_tiles<T, 10, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 12: mfma_dispatch_tiles<T, 12, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 16: mfma_dispatch_tiles<T, 16, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    case 20: mfma_dispatch_tiles<T, 20, FUSE>(b, bfrag, l2l_frag, stream); return true;
-    default: return false;
-  }
+void mfma_dispatch(M2LBatch &b, const T *bfrag, const double *l2l_frag, int ks, hipStream_t stream) {
+  LENS_KS_DISPATCH(ks, (mfma_dispatch_tiles<T, KS, FUSE>(b, bfrag, l2l_frag, stream)));
+  LENS_HIP(hipGetLastError());
 }
 
 }  // namespace
-
-void launch_l2l(const DownArgs &a, const OpTables &t, hipStream_t stream) {
-  const int64_t n = a.win.count() * a.p;
-  if (n == 0) return;
-  hipLaunchKernelGGL(k_l2l, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     stream, a, t.l2l);
-  LENS_HIP(hipGetLastError());
-}
 
 void launch_l2l_chain(const L2LChain &c, const OpTables &t, hipStream_t stream) {
   if (c.nlev < 1 || c.nlev > kMaxL2LChain) fail(LENS_EINVAL, "L2L chain: bad level count");
@@ -712,52 +571,19 @@ void launch_l2l_chain(const L2LChain &c, const OpTables &t, hipStream_t stream) 
 
 void launch_m2l_batch(M2LBatch &b, const OpTables &t, bool fp32, hipStream_t stream) {
   if (b.count == 0) return;
-  bool done;
   if (fp32)
-    done = mfma_dispatch<float, false>(b, t.bfrag32, nullptr, t.ks, stream);
+    mfma_dispatch<float, false>(b, t.bfrag32, nullptr, t.ks, stream);
   else
-    done = mfma_dispatch<double, false>(b, t.bfrag64, nullptr, t.ks, stream);
-  if (!done) {
-    for (int i = 0; i < b.count; ++i) {
-      DownArgs a{};
-      a.level = b.lv[i].level;
-      a.p = b.p;
-      a.s = b.lv[i].s;
-      a.win = b.lv[i].win;
-      a.swin = b.lv[i].swin;
-      a.loc = b.lv[i].loc;
-      if (a.win.count() == 0) continue;
-      if (fp32) {
-        a.mp32 = static_cast<const float *>(b.lv[i].mp);
-        LENS_PMAX_DISPATCH(a.p, hipLaunchKernelGGL((k_m2l_valu<PM, float>), valu_grid(a),
-                                                   dim3(kThreads), 0, stream, a, a.mp32, t.m2l32));
-      } else {
-        a.mp = static_cast<const double *>(b.lv[i].mp);
-        LENS_PMAX_DISPATCH(a.p, hipLaunchKernelGGL((k_m2l_valu<PM, double>), valu_grid(a),
-                                                   dim3(kThreads), 0, stream, a, a.mp, t.m2l));
-      }
-    }
-  }
-  LENS_HIP(hipGetLastError());
+    mfma_dispatch<double, false>(b, t.bfrag64, nullptr, t.ks, stream);
 }
 
-bool launch_m2l_l2l(M2LBatch &b, const OpTables &t, bool fp32, hipStream_t stream) {
-  if (b.count != 1 || !b.lv[0].ploc) return false;
-  if (b.lv[0].win.count() == 0) return true;
-  bool done;
+void launch_m2l_l2l(M2LBatch &b, const OpTables &t, bool fp32, hipStream_t stream) {
+  if (b.count != 1 || !b.lv[0].ploc) fail(LENS_EINVAL, "M2L + L2L: one level with its parents' locals");
+  if (b.lv[0].win.count() == 0) return;
   if (fp32)
-    done = mfma_dispatch<float, true>(b, t.bfrag32, t.l2l_frag, t.ks, stream);
+    mfma_dispatch<float, true>(b, t.bfrag32, t.l2l_frag, t.ks, stream);
   else
-    done = mfma_dispatch<double, true>(b, t.bfrag64, t.l2l_frag, t.ks, stream);
-  if (done) LENS_HIP(hipGetLastError());
-  return done;
-}
-
-void launch_to_f32(const double *src, float *dst, size_t n, hipStream_t stream) {
-  if (n == 0) return;
-  hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     stream, src, dst, n);
-  LENS_HIP(hipGetLastError());
+    mfma_dispatch<double, true>(b, t.bfrag64, t.l2l_frag, t.ks, stream);
 }
 
 }  // namespace lensfmm

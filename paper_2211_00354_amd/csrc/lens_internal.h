@@ -133,9 +133,6 @@ int64_t box_starts_coarse_len(int64_t nbox);
 // Expansion operator tables (host-built, uploaded once per order).
 struct OpTables {
   int p = 0;
-  double *l2l = nullptr;   // [4][p][p] complex, L[q][j][l]
-  double *m2l = nullptr;   // [49][p][p] complex, stored T[tau][k][l]
-  float *m2l32 = nullptr;  // same in FP32
   // M2L as MFMA B fragments: [49][ks][nt][64 lanes]
   int ks = 0, nt = 0;
   double *bfrag64 = nullptr;
@@ -148,7 +145,8 @@ const OpTables &op_tables(int p, hipStream_t stream);
 // nullptr (never allocates).
 const OpTables *op_tables_if_built(int p);
 
-// Host-side table builders (also exported for tests through lens_debug_*).
+// Host-side table builders: complex operators, [4][p][p] L[q][j][l] (shifts) and
+// [49][p][p] T[tau][k][l] (M2L), and their fragments.
 void build_m2m_table(int p, std::vector<double> &out);
 void build_l2l_table(int p, std::vector<double> &out);
 void build_m2l_table(int p, std::vector<double> &out);
@@ -200,20 +198,7 @@ struct M2MChain {
 int m2m_chain_levels(int level);  // most levels one launch can take from `level` down
 void launch_m2m_chain(const M2MChain &c, const OpTables &t, hipStream_t stream);
 
-// Downward pass (downward.hip): local expansions of `win` at `level` from the
-// parent's locals (level >= 3) and the multipoles of the interaction list.
-struct DownArgs {
-  int level, p;
-  double s;              // box side at this level
-  Window win, pwin;      // target window and parent window
-  const double *mp;      // multipoles at this level, [swin][p] complex FP64
-  const float *mp32;     // same in FP32 (mixed fine levels) or nullptr
-  Window swin;           // boxes held in mp / mp32
-  const double *ploc;    // parent locals [pwin][p] or nullptr (level 2)
-  double *loc;           // output locals [win][p]
-};
-// loc += L2L(parent locals), FP64 (levels >= 3).
-void launch_l2l(const DownArgs &a, const OpTables &t, hipStream_t stream);
+// Downward pass (downward.hip).
 // L2L down a chain of levels in one launch: the locals of `level` are final;
 // levels level+1 .. level+nlev (nlev <= 3) get loc += L2L(parent) in turn.
 // win[j] / loc[j]: window and locals [win][p] of level + j.
@@ -226,8 +211,7 @@ struct L2LChain {
 void launch_l2l_chain(const L2LChain &c, const OpTables &t, hipStream_t stream);
 
 // M2L of several levels in one launch: loc = (1/s) sum over the interaction
-// list (FP64 or FP32 arithmetic); runs on MFMA when the order's tile fits the
-// LDS budget, else on VALU (one launch per level).
+// list (FP64 or FP32 arithmetic), on MFMA.
 constexpr int kMaxBatchLevels = LENS_MAX_LEVEL + 1;
 struct M2LLevel {
   int level;
@@ -245,10 +229,8 @@ struct M2LBatch {
   int64_t tile_begin[kMaxBatchLevels + 1];
 };
 void launch_m2l_batch(M2LBatch &b, const OpTables &t, bool fp32, hipStream_t stream);
-// One level with L2L fused: loc = (1/s) M2L + L2L(ploc), the L2L part on FP64
-// MFMA; returns false (nothing launched) if the order has no MFMA tile.
-bool launch_m2l_l2l(M2LBatch &b, const OpTables &t, bool fp32, hipStream_t stream);
-void launch_to_f32(const double *src, float *dst, size_t n, hipStream_t stream);
+// One level with L2L fused: loc = (1/s) M2L + L2L(ploc), the L2L part on FP64 MFMA.
+void launch_m2l_l2l(M2LBatch &b, const OpTables &t, bool fp32, hipStream_t stream);
 
 // Evaluation (eval.hip): per leaf box of the window, local expansion at its
 // rays + direct sum over the 3x3 neighbourhood + smooth term.

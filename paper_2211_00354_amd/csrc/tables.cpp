@@ -202,15 +202,9 @@ const OpTables &op_tables(int p, hipStream_t stream) {
   if (it != g_tabs.end()) return it->second;
   OpTables t;
   t.p = p;
-  std::vector<double> h;
   std::vector<double> m2m, l2l;
   build_m2m_table(p, m2m);
   build_l2l_table(p, l2l);
-  t.l2l = upload(l2l);
-  build_m2l_table(p, h);
-  t.m2l = upload(h);
-  std::vector<float> hf(h.begin(), h.end());
-  t.m2l32 = upload(hf);
   std::vector<double> bf;
   build_m2l_bfrag(p, bf, t.ks, t.nt);
   t.bfrag64 = upload(bf);

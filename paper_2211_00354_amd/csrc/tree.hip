@@ -230,7 +230,6 @@ __device__ __forceinline__ void wave_sync() {
 // beyond (a digit's run in a tile is then twice as long: 5e6 keys 37 us against
 // 42).
 constexpr int kSortItems = 8, kLongSortItems = 16;
-constexpr int kSortTile = kThreads * kSortItems;
 constexpr int64_t kLongSort = int64_t(1) << 21;
 constexpr int kMaxPasses = 4;
 
