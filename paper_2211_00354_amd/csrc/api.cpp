@@ -946,7 +946,7 @@ void fmm_explicit_eval(lens_plan &P, const ExplicitLocals &e, const double *rays
   ea.dfdz_out = dfdz;
   if (wl.count() > (int64_t)0x7fffffff) fail(LENS_EUNSUPPORTED, "leaf window too large");
   StageTimer tm("eval", st);
-  launch_eval_rays(ea, n, P.precision, st);
+  launch_eval_rays(ea, n, P.n_stars, P.precision, st);
   P.last_stream = st;
 }
 

@@ -18,6 +18,15 @@ __device__ __forceinline__ int64_t box_coord(double x, double origin, double s, 
   return (int64_t)floor(t);
 }
 
+// Orders the LDS accesses of a converged wave, whose lanes exchange data through
+// LDS: the LDS takes a wave's in their order, so nothing is waited for
+// (__syncthreads waits for the wave's stores and atomics to memory as well).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Ray i of a cell-centred grid axis: origin + (i + 0.5) * step, the product
 // and the sum each rounded once.
 __device__ __forceinline__ double grid_coord(double origin, double step, int64_t i) {
@@ -47,14 +56,6 @@ __device__ __forceinline__ cplx cmul(cplx a, cplx b) {
 // acc + a * b
 __device__ __forceinline__ cplx cmad(cplx a, cplx b, cplx acc) {
   return {fma(a.re, b.re, fma(-a.im, b.im, acc.re)), fma(a.re, b.im, fma(a.im, b.re, acc.im))};
-}
-
-struct cplxf {
-  float re, im;
-};
-
-__device__ __forceinline__ cplxf cmadf(cplxf a, cplxf b, cplxf acc) {
-  return {fmaf(a.re, b.re, fmaf(-a.im, b.im, acc.re)), fmaf(a.re, b.im, fmaf(a.im, b.re, acc.im))};
 }
 
 // Expansion orders are compiled in buckets; a kernel for bucket PM serves

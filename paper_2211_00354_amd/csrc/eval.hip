@@ -91,14 +91,6 @@ __device__ __forceinline__ void pair_update(const double (&rx)[R], const double 
   }
 }
 
-// Orders a one-wave workgroup's LDS accesses: the LDS takes a wave's in their
-// order, so nothing is waited for (__syncthreads waits for the wave's stores and
-// atomics to memory as well).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Map counts are first summed in a small per-wave table in LDS: kMapSegs rows of
 // half a 64-byte segment of the map (8 pixels) each, two 16-bit counts to a word
 // (open addressing by segment with four linear probes; a ray whose segment finds
@@ -890,25 +882,29 @@ void eval_rays(const EvalArgs &a, int64_t n, hipStream_t stream) {
 // rays 4.8 ms with one lane, 0.6 with sixteen; 30000 rays 4.8 ms with one, 1.3 with
 // four, 0.9 with sixteen).  More rays would pay for the far field that a ray's lanes
 // all sum: 30000 rays on 1e4 uniform stars in FP64 104 us with four lanes, 119 with
-// sixteen; 1e5 rays on 1e5 stars 132 with one, 155 with four.
+// sixteen; 1e5 rays on 1e5 stars 132 with one, 155 with four.  Few stars make no
+// long chain, and a wave of fewer rays waits for more of their loads (1e3 rays on
+// 1e3 stars in FP64 78 us with one lane, 84 with sixteen).
+constexpr int64_t kManyStars = 2048;
+
 template <bool MIXED>
-void eval_rays_dispatch(const EvalArgs &a, int64_t n, hipStream_t stream) {
-  if (n <= kManyLanes / 32)
+void eval_rays_dispatch(const EvalArgs &a, int64_t n, int64_t n_stars, hipStream_t stream) {
+  if (n_stars > kManyStars && n <= kManyLanes / 32)
     eval_rays<MIXED, 16>(a, n, stream);
-  else if (n <= kManyLanes / 4)
+  else if (n_stars > kManyStars && n <= kManyLanes / 4)
     eval_rays<MIXED, 4>(a, n, stream);
   else
     eval_rays<MIXED, 1>(a, n, stream);
 }
 
-void launch_eval_rays(const EvalArgs &a, int64_t n, int precision, hipStream_t stream) {
+void launch_eval_rays(const EvalArgs &a, int64_t n, int64_t n_stars, int precision, hipStream_t stream) {
   if (n == 0) return;
   if (precision == LENS_MIXED && !a.sm32)
     fail(LENS_EINVAL, "mixed-precision evaluation needs the plan's FP32 masses");
   if (precision == LENS_MIXED)
-    eval_rays_dispatch<true>(a, n, stream);
+    eval_rays_dispatch<true>(a, n, n_stars, stream);
   else
-    eval_rays_dispatch<false>(a, n, stream);
+    eval_rays_dispatch<false>(a, n, n_stars, stream);
   LENS_HIP(hipGetLastError());
 }
 

@@ -644,14 +644,6 @@ __device__ __forceinline__ double wide_weight(const IpmArgs &a, int64_t i, int64
   return signed_weight(c.q, a.cell_px / c.area);
 }
 
-// Orders the LDS accesses of a converged wave (its lanes exchange data
-// through LDS without a workgroup barrier).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ int32_t wave_excl_scan(int32_t x, int lane, int32_t &total) {
   int32_t inc = x;
 #pragma unroll

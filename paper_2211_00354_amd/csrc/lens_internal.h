@@ -264,8 +264,8 @@ struct EvalArgs {
   int32_t npix;
 };
 void launch_eval(const EvalArgs &a, int precision, hipStream_t stream);
-// a.rxy's n explicit rays, sorted by leaf box, all in a.win
-void launch_eval_rays(const EvalArgs &a, int64_t n, int precision, hipStream_t stream);
+// a.rxy's n explicit rays, sorted by leaf box, all in a.win; n_stars in all
+void launch_eval_rays(const EvalArgs &a, int64_t n, int64_t n_stars, int precision, hipStream_t stream);
 // col_start[c] = first grid column whose rays fall in box column win.bx0 + c
 // (c = 0..nbx); row_start likewise over the rows [j_begin, j_end).
 void launch_grid_ranges(const lens_grid &grid, Geometry g, Window win, int64_t j_begin,

@@ -210,13 +210,6 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *sh /*[
   return woff + incl - x;
 }
 
-// Orders the LDS accesses of a converged wave.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // ------------------------------------------------------------- radix sort
 // Stable LSD radix sort of (key, index) pairs, 8 bits a pass, two kernels a
 // pass: k_radix_count leaves every tile's digit counts and, by atomics, those

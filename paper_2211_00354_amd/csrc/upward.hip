@@ -24,14 +24,6 @@ constexpr int kWave = 64;
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-// Orders the LDS accesses of a converged wave (its lanes exchange data
-// through LDS without a workgroup barrier).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Group-cooperative P2M of one box by GL neighbouring lanes of a wave (every
 // lane of the group calls with the same box; `on` false: an empty box).  The
 // box at `level` covers 2^(L-level) rows of leaf boxes, each a contiguous

@@ -363,7 +363,7 @@ def test_adjoint_of_2_28_stars(lf):
 
 
 @pytest.mark.parametrize("precision", ["mixed", "fp64"])
-@pytest.mark.parametrize("n,leaf_level", [(1, 2), (130, 2), (1500, 2), (20000, 3), (20000, 6)])
+@pytest.mark.parametrize("n,leaf_level", [(1, 2), (2048, 2), (2049, 2), (3000, 7), (20000, 3), (20000, 6)])
 def test_explicit_rays_do_not_depend_on_their_number(lf, n, leaf_level, precision):
     # one, four and sixteen lanes to a ray (70000, 65536 and 8192 rays), whose
     # neighbourhoods hold no star to thousands: groups of stars that end before,
