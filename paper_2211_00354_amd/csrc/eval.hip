@@ -175,8 +175,8 @@ __device__ __forceinline__ bool map_table_flush(MapTable &t, int above, int32_t 
 // four rays where a Horner sum for each takes 16 p.  |z| <= 1/2, so the
 // recurrence damps its roundings.  The pair sums gain too: the four rays have
 // two columns and two rows, so a star costs them four differences, not eight.
-// 1e6 stars, 8192^2 rays, p = 12: 343 to 250 million VALU instructions, 700 to
-// 560 us.
+// 1e6 stars, 8192^2 rays, p = 12: 343 to 256 million VALU instructions, 700 to
+// 550 us.
 constexpr double kSameCentre = 0x1p-50;  // LENS_MIXED
 
 struct InverseInts {

@@ -41,7 +41,8 @@ constexpr double kFix = 1099511627776.0;  // 2^40
 // widest bounding box (in pixels) apportioned by the per-cell pair path: a pair
 // costs four edge terms, a rasterised cell its perimeter.  16384^2 rays at mu
 // = 50 into 2000^2 pixels, k_ipm + k_ipm_wide: 64 pixels 10.6 + 5.6 ms, 32
-// 9.2 + 6.6, 16 8.3 + 7.2, 4 6.9 + 11.3.
+// 9.2 + 6.6, 16 8.3 + 7.2, 4 6.9 + 11.3 (in turn on one card; on another, whose
+// statistics are kept, 9.2 + 8.6 with 16).
 constexpr int32_t kPairMax = 16;
 
 __device__ __forceinline__ double orient2(double ax, double ay, double bx, double by, double cx,
